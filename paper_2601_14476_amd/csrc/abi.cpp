@@ -49,6 +49,7 @@ struct Arena {
     char *base = nullptr;
     size_t cap = 0;
     size_t used = 0;
+    bool no_ell = false;  // plan without the streaming sweeps (their constants take 16 bytes per p-bit)
     void *carve(size_t bytes) {
         const size_t at = (used + 255) / 256 * 256;
         if (at > cap || bytes > cap - at) return nullptr;
@@ -107,7 +108,8 @@ void job_free(psa_job *j) {
         // the run arrays are the source job's
         j->d_i0 = j->d_lambda = j->d_delta = nullptr;
         j->d_thr24 = nullptr;
-        j->d_order = j->d_pp = nullptr;
+        j->d_order = nullptr;
+        j->d_pps = nullptr;
         j->d_prec = nullptr;
         j->d_pcls = nullptr;
         j->d_pcache = nullptr;
@@ -116,7 +118,8 @@ void job_free(psa_job *j) {
         // carved from memory the job does not own: forget, never free
         j->d_i0 = j->d_lambda = j->d_delta = nullptr;
         j->d_thr24 = nullptr;
-        j->d_order = j->d_ring = j->d_pp = nullptr;
+        j->d_order = j->d_ring = nullptr;
+        j->d_pps = nullptr;
         j->d_m = j->d_spins = nullptr;
         j->d_xs = nullptr;
         j->d_scratch = nullptr;
@@ -133,7 +136,7 @@ void job_free(psa_job *j) {
     dev_free(j->d_spins);
     dev_free(j->d_xs);
     dev_free(j->d_ring);
-    dev_free(j->d_pp);
+    dev_free(j->d_pps);
     dev_free(j->d_prec);
     dev_free(j->d_pcls);
     dev_free(j->d_pcache);
@@ -666,7 +669,9 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
     const uint32_t path = desc->flags & PSA_PATH_MASK;
     if (path != PSA_PATH_DENSE) {
         std::string why;
-        if (!psa::plan_anneal(g->dev, j->run, desc->trials_per_group, desc->lanes_per_task,
+        psa::DevGraph pg = g->dev;
+        if (arena && arena->no_ell) pg.e1 = nullptr;
+        if (!psa::plan_anneal(pg, j->run, desc->trials_per_group, desc->lanes_per_task,
                               desc->block, ctx->max_lds, ctx->num_cu, &j->plan, &why)) {
             if (path == PSA_PATH_CSR) {
                 set_error(std::string(who) + ": " + why);
@@ -702,17 +707,34 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
     if ((st = dev_upload(&j->d_delta, dlt.data(), dlt.size(), "job upload", &j->dev_bytes, arena)) != PSA_OK) return st;
     if ((st = dev_upload(&j->d_thr24, thr.data(), thr.size(), "job upload", &j->dev_bytes, arena)) != PSA_OK) return st;
     if ((st = dev_upload(&j->d_order, order.data(), order.size(), "job upload", &j->dev_bytes, arena)) != PSA_OK) return st;
-    if (g->dev.ell) {
-        // per-p-bit constants of the ELL four-trial sweep, one 16-byte load each
-        std::vector<int32_t> pp(4 * static_cast<size_t>(n4));
-        for (int32_t i = 0; i < n4; ++i) {
-            pp[4 * i] = g->h_host[i] - (g->row_ptr_host[i + 1] - g->row_ptr_host[i]);
-            memcpy(&pp[4 * i + 1], &lam[i], 4);
-            memcpy(&pp[4 * i + 2], &dlt[i], 4);
-            pp[4 * i + 3] = static_cast<int32_t>(thr[i]);
-        }
-        if ((st = dev_upload(&j->d_pp, pp.data(), pp.size(), "job upload", &j->dev_bytes, arena)) != PSA_OK) return st;
-        j->run.pp = j->d_pp;
+    if (g->dev.wofs && !(arena && !j->plan.ell)) {
+        // per-p-bit constants of the streaming sweeps in their task order
+        const size_t tasks = static_cast<size_t>(n4) / 4;
+        std::vector<uint32_t> pps((tasks + 63) / 64 * 64 * 16, 0u);
+        double max_lam = 0.0, max_prod = 0.0;
+        for (size_t s = 0; s < tasks; ++s)
+            for (int32_t p = 0; p < 4; ++p) {
+                const int32_t i = 4 * g->gorder_host[s] + p;
+                // exact: an integer below 2^24 in magnitude, halved
+                const float hd = 0.5f * static_cast<float>(g->h_host[i] - g->absrow_host[i]);
+                uint32_t *c = &pps[((s / 64 * 4 + static_cast<size_t>(p)) * 64 + s % 64) * 4];
+                // plain pSA: the factors of the decision's exponent; SpSA and
+                // TApSA form the pre-activation itself
+                const bool plain = desc->algorithm == PSA_ALG_PSA;
+                const float p1 = plain ? static_cast<float>(2.0 * psa::kTwoLog2eHost * lam[i]) : lam[i];
+                const float p2 = plain ? static_cast<float>(psa::kTwoLog2eHost * lam[i] * dlt[i]) : dlt[i];
+                memcpy(c, &hd, 4);
+                memcpy(c + 1, &p1, 4);
+                memcpy(c + 2, &p2, 4);
+                c[3] = thr[i];
+                if (i < n && thr[i] < psa::kGateOneHost) j->run.gated = 1;
+                max_lam = std::max(max_lam, std::fabs(static_cast<double>(lam[i])));
+                max_prod = std::max(max_prod, std::fabs(static_cast<double>(lam[i]) * dlt[i]));
+            }
+        j->run.i0_lim = static_cast<float>(std::min(max_prod > 0.0 ? psa::kEstimateLimit / max_prod : 1e30,
+                                                    max_lam > 0.0 ? 1e30 / max_lam : 1e30));
+        if ((st = dev_upload(&j->d_pps, pps.data(), pps.size(), "job upload", &j->dev_bytes, arena)) != PSA_OK) return st;
+        j->run.pps = j->d_pps;
     }
     if (desc->t_res > 0 && !j->plan.dense && j->plan.tpw == 1) {
         // period mode, one trial per workgroup: the sweep over period classes
@@ -790,7 +812,7 @@ psa_status clone_job_for_timing(psa_job *src, psa_job **out) {
     j->d_delta = src->d_delta;
     j->d_thr24 = src->d_thr24;
     j->d_order = src->d_order;
-    j->d_pp = src->d_pp;
+    j->d_pps = src->d_pps;
     j->d_prec = src->d_prec;
     j->d_pcls = src->d_pcls;
     j->d_pcache = src->d_pcache;
@@ -1167,6 +1189,12 @@ psa_status psa_anneal_noalloc(psa_ctx *ctx, const psa_graph *g, const psa_run_de
         arena.cap = PSA_NOALLOC_SCRATCH_BYTES;
         psa_job *job = nullptr;
         psa_status st = create_job("psa_anneal_noalloc", ctx, g, &d, &arena, &job);
+        if (st == PSA_ENOMEM) {
+            // a run at the edge of the scratch may fit the CSR sweeps' state
+            arena.used = 0;
+            arena.no_ell = true;
+            st = create_job("psa_anneal_noalloc", ctx, g, &d, &arena, &job);
+        }
         if (st != PSA_OK) return st;
         std::unique_ptr<psa_job, void (*)(psa_job *)> guard(job, job_free);
         if ((st = psa_job_step(job, d.steps)) != PSA_OK) return st;

@@ -92,6 +92,16 @@ constexpr double kCsrStepFloorSeconds = 1.5e-6;
 constexpr double kDenseStepFloorSeconds = 6.0e-6;
 
 double csr_step_seconds(const DevGraph &g, const DevRun &run, const AnnealPlan &plan) {
+    if (plan.ell) {
+        // streaming sweeps: lane-operations per update fitted to runs of
+        // degree 4 to 50 (four trials 35 + 4 d, one trial 50 + 7 d), on the
+        // compute units its workgroups reach
+        const double deg = g.nnz / static_cast<double>(std::max(g.n, 1));
+        const double wgs = plan.tpw == 4 ? run.t4 / 4 : run.trials;
+        const double ops = plan.tpw == 4 ? 35.0 + 4.0 * deg : 50.0 + 7.0 * deg;
+        return std::max(kCsrStepFloorSeconds, static_cast<double>(g.n) * run.trials * ops /
+                                                  (kValuOpsPerSecond * std::min(1.0, wgs / 256.0)));
+    }
     // lane-ops per update: RNG, activation and decision (about 60), plus a
     // gather per edge: a few ops from LDS, tens when the rows stream from
     // memory (latency-bound gathers of one trial per workgroup)

@@ -79,8 +79,8 @@ using TuneKey = std::array<int64_t, 7>;
 // n4 = 4 ceil(n/4) entries (h = 0) and row_ptr to n4 + 4 entries (padding rows
 // are empty).  Packed copies of the edges, when the graph allows them:
 //   pk32[e] = col | J << 16              (n <= 65536, |J| < 2^15)
-//   pk16[e] = col << 1 | (J < 0)         (every |J| == 1, n <= 32768)
 //   ux16[e] = col + (J < 0 ? n4 : 0)     (every |J| == 1, 2 n4 <= 65536)
+// and the wavefront-ordered ELL rows of the streaming sweeps (EllPlan).
 struct DevGraph {
     int32_t n = 0;
     int32_t n4 = 0;
@@ -90,14 +90,20 @@ struct DevGraph {
     const int32_t *col = nullptr;      // [nnz]
     const int32_t *val = nullptr;      // [nnz]
     const uint32_t *pk32 = nullptr;    // [nnz] or null
-    const uint16_t *pk16 = nullptr;    // [nnz] or null
     const uint16_t *ux16 = nullptr;    // [nnz] or null
-    // unit weights, degree <= 255: per-task ELL rows for the four-trial sweep
-    // streaming edges from device memory; group g = eptr[m] .. eptr[m+1]-1 of
-    // task m holds entry j of rows 4m..4m+3 as col | (J < 0) << 31, past a
-    // row's end the zero word n4
-    const uint32_t *ell = nullptr;     // [4 * groups] or null
-    const int32_t *eptr = nullptr;     // [n4/4 + 1] or null
+    // ELL rows of the streaming sweeps (ell_sweep.hpp), or null: tasks in
+    // the order gorder, wavefront w = slots 64 w .. 64 w + 63, every row
+    // padded to an even count 2 (wofs[w + 1] - wofs[w]).
+    //   e4  [2 wofs[waves]][64][4]  entry of rows 4m..4m+3: 8 col | |J| << 18
+    //       | (J < 0) << 31, past a row's end the zero pair 8 n4
+    //   e1  [wofs[waves]][64][4]    two entries as col + (J < 0 ? n4 : 0),
+    //       past a row's end the zero byte 2 n4
+    //   e1j the same shape (weights other than +-1): two |J|
+    const int32_t *gorder = nullptr;   // [64 waves], 0 past n4/4
+    const int32_t *wofs = nullptr;     // [waves + 1]
+    const uint32_t *e4 = nullptr, *e1 = nullptr, *e1j = nullptr;
+    int32_t e4_mode = -1;              // kEll*: four-trial sums, -1: none
+    int32_t ell_groups = 0;            // wofs[waves]
     const int32_t *h = nullptr;        // [n4]
     int64_t w2 = 0;                    // sum_i sum_j J_ij = 2 sum_{i<j} J_ij
 };
@@ -120,13 +126,28 @@ struct DevRun {
     int32_t *ring = nullptr;              // TApSA windows [t4/4][n4][alpha][4], else nullptr
     int32_t alpha = 1;                    // TApSA window
     int32_t t_res = 0;                    // period mode: sub-steps per cycle (thr24 holds periods)
-    // per-p-bit constants [n4][4] of the ELL four-trial sweep: h_i - deg_i,
-    // lambda_i and delta_i (float bits), thr24_i
-    const int32_t *pp = nullptr;
+    // per-p-bit constants of the streaming sweeps, [waves][4 rows][64 tasks]:
+    // (h_i - sum_j |J_ij|) / 2, 4 lambda_i log2 e, 2 lambda_i delta_i log2 e
+    // (SpSA and TApSA: lambda_i, delta_i; float bits), thr24_i
+    const uint32_t *pps = nullptr;
+    int32_t gated = 0;                    // some p-bit has thr24 < 2^24
+    float i0_lim = 0.0f;                  // |I0| up to which the decision estimate's bound holds
 };
 
 // How the persistent anneal kernel is launched for one run.
-enum CsrKind : int32_t { kCsrPair = 0, kCsrPack32 = 1, kCsrPack16 = 2, kCsrUnit = 3 };
+enum CsrKind : int32_t { kCsrPair = 0, kCsrPack32 = 1, kCsrUnit = 3 };
+// Distance between the two spin buffers of the one-trial streaming sweep:
+// n4 bytes u, n4 bytes 1 - u and a zero byte.
+__host__ __device__ constexpr size_t ell1_stride(int32_t n4) {
+    return (2 * static_cast<size_t>(n4) + 1 + 15) / 16 * 16;
+}
+// LDS of the four-trial streaming sweep: a pair of words per p-bit (step
+// parity) and a zero pair.
+__host__ __device__ constexpr size_t ell4_lds(int32_t n4) { return (8 * (static_cast<size_t>(n4) + 1) + 15) / 16 * 16; }
+// |i0 lambda delta| up to which the streaming sweeps' decision estimate holds.
+constexpr double kEstimateLimit = 30.0;
+// 2 log2(e), the factor of a pre-activation in the exponent of e^(2x).
+constexpr double kTwoLog2eHost = 2.8853900817779268;
 struct AnnealPlan {
     int32_t dense = 0;        // 1: dense int8 matrix-core path (nb below)
     int32_t nb = 4;           // dense path: 16-trial blocks per workgroup
@@ -134,6 +155,7 @@ struct AnnealPlan {
     int32_t lpt = 1;          // lanes per 4-p-bit task (tpw == 1): 1, 2 or 4
     int32_t csr = kCsrPair;   // edge encoding read by the kernel
     int32_t csr_lds = 0;      // 1: CSR, biases and per-p-bit factors staged in LDS
+    int32_t ell = 0;          // 1: streaming sweep over the graph's ELL rows
     int32_t block = 256;      // threads per workgroup
     int32_t grid = 0;         // workgroups
     size_t lds_bytes = 0;     // dynamic LDS per workgroup
@@ -146,12 +168,14 @@ struct AnnealArgs {
     const int32_t *col;
     const int32_t *val;
     const uint32_t *pk32;
-    const uint16_t *pk16;
     const uint16_t *ux16;
-    const uint32_t *ell;
-    const int32_t *eptr;
-    const int32_t *pp;
     const int32_t *h;
+    // streaming sweeps
+    const int32_t *gorder, *wofs;
+    const uint32_t *e4, *e1, *e1j, *pps;
+    int32_t groups;  // of e1; e4 holds twice as many
+    float i0_lim;
+    int32_t gated;
     const float *i0;
     const float *lam;
     const float *dlt;
@@ -180,11 +204,13 @@ enum BatchVariant : int32_t {
     kBatchP32Glb2 = 5,
     kBatchPairGlb2 = 6,
     // four trials per workgroup (work item = group of four trials)
-    kBatchP16Lds4T = 7,
-    kBatchP16Glb4T = 8,
-    kBatchP32Lds4T = 9,
-    kBatchP32Glb4T = 10,
-    kBatchPairGlb4T = 11,
+    kBatchP32Lds4T = 7,
+    kBatchP32Glb4T = 8,
+    kBatchPairGlb4T = 9,
+    // streaming sweeps: one trial (weights +-1, or any), four trials (by e4_mode)
+    kBatchEll1Unit = 10,
+    kBatchEll1 = 11,
+    kBatchEll4 = 12,  // + e4_mode
 };
 
 // One run of a batched launch, as stored in the device job table.
@@ -330,6 +356,12 @@ void task_order(const DevGraph &g, const std::vector<int32_t> &row_ptr_host,
 hipError_t launch_anneal(hipStream_t stream, const DevGraph &g, const DevRun &run,
                          const AnnealPlan &plan, const int32_t *order, int32_t t_begin,
                          int32_t t_end);
+// Streaming sweep of one run (ell.hip): plan.ell set.
+hipError_t launch_ell(hipStream_t stream, const AnnealArgs &args, const AnnealPlan &plan, int32_t e4_mode);
+// Fill a graph's ELL rows (e4, e1, e1j where not null) from its CSR.
+hipError_t launch_build_ell(hipStream_t stream, int32_t waves, int32_t tasks, int32_t n4, const int32_t *row_ptr,
+                            const int32_t *col, const int32_t *val, const int32_t *gorder, const int32_t *wofs,
+                            uint32_t *e4, uint32_t *e1, uint32_t *e1j);
 void fill_anneal_args(AnnealArgs *a, const DevGraph &g, const DevRun &run, const int32_t *order,
                       int32_t t_begin, int32_t t_end);
 // Plan of one run inside a batched launch (tpw_req 4: four trials per
@@ -399,9 +431,23 @@ struct HostGraph {
     std::vector<int32_t> col, val;
     std::vector<int32_t> h;     // [n4]
     std::vector<uint32_t> pk32;
-    std::vector<uint16_t> pk16, ux16;
-    std::vector<uint32_t> ell;
-    std::vector<int32_t> eptr;
+    std::vector<uint16_t> ux16;
+    // ELL rows of the streaming sweeps (filled on the device): task order,
+    // wavefront offsets in pairs of entries, four-trial mode; empty: none
+    std::vector<int32_t> gorder, wofs;
+    int32_t e4_mode = -1;
+    std::vector<int32_t> absrow;  // [n4] sum_j |J_ij|
+    void drop_ell() {
+        gorder.clear();
+        wofs.clear();
+        e4_mode = -1;
+    }
+    // device bytes of the ELL rows and the arrays they are found through
+    size_t ell_bytes() const {
+        if (wofs.empty()) return 0;
+        const size_t pairs = static_cast<size_t>(wofs.back()) * 64 * 16;
+        return (gorder.size() + wofs.size()) * 4 + pairs * (1 + (info.unit_weights ? 0 : 1) + (e4_mode >= 0 ? 2 : 0));
+    }
 };
 psa_status host_graph_from_edges(int32_t n, int64_t m, const int32_t *u, const int32_t *v,
                                  const int32_t *val, const int32_t *h, uint32_t flags,
@@ -541,11 +587,13 @@ struct psa_graph {
     // owning device pointers
     int32_t *d_row_ptr = nullptr, *d_col = nullptr, *d_val = nullptr, *d_h = nullptr;
     uint32_t *d_pk32 = nullptr;
-    uint16_t *d_pk16 = nullptr, *d_ux16 = nullptr;
-    uint32_t *d_ell = nullptr;
-    int32_t *d_eptr = nullptr;
+    uint16_t *d_ux16 = nullptr;
+    int32_t *d_gorder = nullptr, *d_wofs = nullptr;
+    uint32_t *d_e4 = nullptr, *d_e1 = nullptr, *d_e1j = nullptr;
     std::vector<int32_t> row_ptr_host;  // [n4+4]
     std::vector<int32_t> h_host;        // [n4]
+    std::vector<int32_t> gorder_host;   // task order of the ELL rows
+    std::vector<int32_t> absrow_host;   // [n4] sum_j |J_ij|
     std::vector<int32_t> col_host, val_host;  // for the dense matrix, on demand
     void *d_dense = nullptr;            // encoded [np][np] couplings, built on first use
     int32_t np = 0;                     // n rounded up to 128
@@ -572,7 +620,7 @@ struct psa_job {
     int8_t *d_spins = nullptr;
     float *d_xs = nullptr;       // SpSA held inputs
     int32_t *d_ring = nullptr;   // TApSA field windows
-    int32_t *d_pp = nullptr;     // per-p-bit constants of the ELL sweep
+    uint32_t *d_pps = nullptr;   // per-p-bit constants of the streaming sweeps
     // period-mode sweep (pplan.nclass > 0): records and classes
     psa::PeriodPlan pplan;
     psa::PeriodRec *d_prec = nullptr;

@@ -50,6 +50,55 @@ psa_status canonical_rows(int32_t n, const std::vector<int64_t> &row_ptr,
     return PSA_OK;
 }
 
+// ELL rows of the streaming sweeps: the order of the tasks (longest row
+// first, so that the 64 tasks of a wavefront have rows of similar length), the
+// wavefronts' offsets, and the four-trial sums' form.  Left empty when the
+// byte indices of the one-trial rows do not fit 16 bits (2 n4 is the largest),
+// a coupling's magnitude does not fit 15 bits, or the padding would multiply
+// the entries (a few rows much longer than the rest).
+void plan_ell_rows(HostGraph *g, const std::vector<int32_t> &val) {
+    const int32_t tasks = g->n4 / 4;
+    if (g->nnz == 0 || 2 * static_cast<int64_t>(g->n4) > 65535) return;
+    int32_t max_mag = 0, max_row = 0;
+    g->absrow.assign(static_cast<size_t>(g->n4), 0);
+    for (int32_t i = 0; i < g->n4; ++i) {
+        int32_t sum = 0;  // below 2^24 (the field bound)
+        for (int32_t p = g->rp32[i]; p < g->rp32[i + 1]; ++p) {
+            const int32_t mag = std::abs(val[p]);
+            max_mag = std::max(max_mag, mag);
+            sum += mag;
+        }
+        g->absrow[i] = sum;
+        max_row = std::max(max_row, sum);
+    }
+    if (max_mag > 32767) return;
+    std::vector<int32_t> len(static_cast<size_t>(tasks)), count(static_cast<size_t>(g->max_degree) + 2, 0);
+    for (int32_t m = 0; m < tasks; ++m) {
+        int32_t d = 0;
+        for (int32_t p = 0; p < 4; ++p) d = std::max(d, g->rp32[4 * m + p + 1] - g->rp32[4 * m + p]);
+        len[m] = d;
+        ++count[static_cast<size_t>(g->max_degree - d) + 1];
+    }
+    for (size_t d = 1; d < count.size(); ++d) count[d] += count[d - 1];
+    std::vector<int32_t> order(static_cast<size_t>(tasks));
+    for (int32_t m = 0; m < tasks; ++m) order[count[static_cast<size_t>(g->max_degree - len[m])]++] = m;
+    const int32_t waves = (tasks + 63) / 64;
+    std::vector<int32_t> wofs(static_cast<size_t>(waves) + 1, 0);
+    int64_t pairs = 0;
+    for (int32_t w = 0; w < waves; ++w) {
+        pairs += (len[order[64 * static_cast<size_t>(w)]] + 1) / 2;  // its first task's is the longest
+        if (pairs * 512 > 8 * g->nnz + (int64_t{1} << 20)) return;
+        wofs[w + 1] = static_cast<int32_t>(pairs);
+    }
+    order.resize(static_cast<size_t>(waves) * 64, 0);  // idle lanes of the last wavefront
+    g->gorder = std::move(order);
+    g->wofs = std::move(wofs);
+    // four-trial sums: counts of +-1 couplings or weighted sums in bytes, or
+    // weighted sums in halves (|J| in 13 bits); the LDS addresses take 18 bits
+    if (g->n4 <= 20480)
+        g->e4_mode = max_row <= 255 ? (g->info.unit_weights ? 0 : 1) : (max_row <= 65535 && max_mag <= 8191 ? 2 : -1);
+}
+
 // Statistics, bounds, padding and packed encodings of a canonical CSR.
 psa_status finish_host_graph(int32_t n, const std::vector<int64_t> &row_ptr,
                              std::vector<int32_t> &&col, std::vector<int32_t> &&val,
@@ -121,42 +170,27 @@ psa_status finish_host_graph(int32_t n, const std::vector<int64_t> &row_ptr,
     // 16-bit edge arrays are padded with zeros to a multiple of 8 entries:
     // kernels that stream rows from global memory load them 8 at a time
     const size_t nnz8 = static_cast<size_t>((nnz + 7) / 8 * 8);
-    if (n <= 32768 && info.unit_weights) {
-        g.pk16.assign(nnz8, 0);
-        for (int64_t p = 0; p < nnz; ++p)
-            g.pk16[p] = static_cast<uint16_t>((static_cast<uint32_t>(col[p]) << 1) |
-                                              (val[p] < 0 ? 1u : 0u));
-    }
     if (2 * static_cast<int64_t>(g.n4) <= 65536 && info.unit_weights) {
         g.ux16.assign(nnz8, 0);
         for (int64_t p = 0; p < nnz; ++p)
             g.ux16[p] = static_cast<uint16_t>(col[p] + (val[p] < 0 ? g.n4 : 0));
     }
-    if (n <= 32768 && info.unit_weights && max_deg <= 255) {
-        // per-task ELL: task m pads its four rows to the longest of them
-        const int32_t tasks = g.n4 / 4;
-        g.eptr.assign(static_cast<size_t>(tasks) + 1, 0);
-        for (int32_t m = 0; m < tasks; ++m) {
-            int32_t d = 0;
-            for (int32_t p = 0; p < 4; ++p) d = std::max(d, g.rp32[4 * m + p + 1] - g.rp32[4 * m + p]);
-            g.eptr[m + 1] = g.eptr[m] + d;
-        }
-        // an entry is the neighbour's word index with the coupling's sign in
-        // bit 31 (shifted out when the index becomes a byte address); past a
-        // row's end, the zero word n4
-        const uint32_t zero = static_cast<uint32_t>(g.n4);
-        g.ell.assign(4 * static_cast<size_t>(g.eptr[tasks]), zero);
-        for (int32_t m = 0; m < tasks; ++m)
-            for (int32_t p = 0; p < 4; ++p) {
-                const int32_t i = 4 * m + p;
-                for (int32_t e = g.rp32[i]; e < g.rp32[i + 1]; ++e)
-                    g.ell[4 * (static_cast<size_t>(g.eptr[m]) + (e - g.rp32[i])) + p] =
-                        static_cast<uint32_t>(col[e]) | (val[e] < 0 ? 0x80000000u : 0u);
-            }
-    }
+    plan_ell_rows(&g, val);
     g.col = std::move(col);
     g.val = std::move(val);
     *out = std::move(g);
+    return PSA_OK;
+}
+
+// Allocate count device elements; the bytes are added to *acct.
+template <typename T>
+psa_status reserve(T **dst, size_t count, size_t *acct) {
+    if (hipMalloc(reinterpret_cast<void **>(dst), count * sizeof(T)) != hipSuccess) {
+        *dst = nullptr;
+        set_error("graph upload: device allocation failed");
+        return PSA_ENOMEM;
+    }
+    *acct += count * sizeof(T);
     return PSA_OK;
 }
 
@@ -165,12 +199,8 @@ template <typename T>
 psa_status upload(T **dst, const std::vector<T> &src, size_t *acct) {
     *dst = nullptr;
     if (src.empty()) return PSA_OK;
-    if (hipMalloc(reinterpret_cast<void **>(dst), src.size() * sizeof(T)) != hipSuccess) {
-        *dst = nullptr;
-        set_error("graph upload: device allocation failed");
-        return PSA_ENOMEM;
-    }
-    *acct += src.size() * sizeof(T);
+    const psa_status st = reserve(dst, src.size(), acct);
+    if (st != PSA_OK) return st;
     const hipError_t e = hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         set_error(std::string("graph upload: ") + hipGetErrorString(e));
@@ -185,9 +215,10 @@ void graph_release(psa_graph *g) {
     if (!g) return;
     for (void *p : {static_cast<void *>(g->d_row_ptr), static_cast<void *>(g->d_col),
                     static_cast<void *>(g->d_val), static_cast<void *>(g->d_h),
-                    static_cast<void *>(g->d_pk32), static_cast<void *>(g->d_pk16),
+                    static_cast<void *>(g->d_pk32), static_cast<void *>(g->d_e4),
                     static_cast<void *>(g->d_ux16), static_cast<void *>(g->d_dense),
-                    static_cast<void *>(g->d_ell), static_cast<void *>(g->d_eptr)})
+                    static_cast<void *>(g->d_e1), static_cast<void *>(g->d_e1j),
+                    static_cast<void *>(g->d_gorder), static_cast<void *>(g->d_wofs)})
         if (p) (void)hipFree(p);
     psa_ctx *ctx = g->retained ? g->ctx : nullptr;
     delete g;
@@ -416,10 +447,27 @@ psa_status upload_graph(psa_ctx *ctx, HostGraph &&hg, psa_graph **out) {
     if ((st = upload(&g->d_val, hg.val, &g->dev_bytes)) != PSA_OK) return st;
     if ((st = upload(&g->d_h, hg.h, &g->dev_bytes)) != PSA_OK) return st;
     if ((st = upload(&g->d_pk32, hg.pk32, &g->dev_bytes)) != PSA_OK) return st;
-    if ((st = upload(&g->d_pk16, hg.pk16, &g->dev_bytes)) != PSA_OK) return st;
     if ((st = upload(&g->d_ux16, hg.ux16, &g->dev_bytes)) != PSA_OK) return st;
-    if ((st = upload(&g->d_ell, hg.ell, &g->dev_bytes)) != PSA_OK) return st;
-    if ((st = upload(&g->d_eptr, hg.eptr, &g->dev_bytes)) != PSA_OK) return st;
+    if ((st = upload(&g->d_gorder, hg.gorder, &g->dev_bytes)) != PSA_OK) return st;
+    if ((st = upload(&g->d_wofs, hg.wofs, &g->dev_bytes)) != PSA_OK) return st;
+    if (!hg.wofs.empty() && hg.wofs.back() > 0) {
+        const size_t words = static_cast<size_t>(hg.wofs.back()) * 64 * 4;
+        if ((st = reserve(&g->d_e1, words, &g->dev_bytes)) != PSA_OK) return st;
+        if (!hg.info.unit_weights && (st = reserve(&g->d_e1j, words, &g->dev_bytes)) != PSA_OK) return st;
+        if (hg.e4_mode >= 0 && (st = reserve(&g->d_e4, 2 * words, &g->dev_bytes)) != PSA_OK) return st;
+        PSA_HIP(launch_build_ell(ctx->stream, static_cast<int32_t>(hg.wofs.size()) - 1, hg.n4 / 4, hg.n4, g->d_row_ptr,
+                                 g->d_col, g->d_val, g->d_gorder, g->d_wofs, g->d_e4, g->d_e1, g->d_e1j),
+                "ELL rows");
+        g->dev.gorder = g->d_gorder;
+        g->dev.wofs = g->d_wofs;
+        g->dev.e4 = g->d_e4;
+        g->dev.e1 = g->d_e1;
+        g->dev.e1j = g->d_e1j;
+        g->dev.e4_mode = hg.e4_mode;
+        g->dev.ell_groups = hg.wofs.back();
+        g->gorder_host = std::move(hg.gorder);
+        g->absrow_host = std::move(hg.absrow);
+    }
     g->dev.n = hg.n;
     g->dev.n4 = hg.n4;
     g->dev.nnz = hg.nnz;
@@ -429,10 +477,7 @@ psa_status upload_graph(psa_ctx *ctx, HostGraph &&hg, psa_graph **out) {
     g->dev.val = g->d_val;
     g->dev.h = g->d_h;
     g->dev.pk32 = g->d_pk32;
-    g->dev.pk16 = g->d_pk16;
     g->dev.ux16 = g->d_ux16;
-    g->dev.ell = g->d_ell;
-    g->dev.eptr = g->d_eptr;
     g->dev.w2 = hg.w2;
     g->row_ptr_host = std::move(hg.rp32);
     g->h_host = std::move(hg.h);

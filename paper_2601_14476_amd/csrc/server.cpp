@@ -84,10 +84,9 @@ size_t reserve_of(const psa::HostGraph &hg, const psa_run_desc &d, bool spins) {
     const size_t t4 = static_cast<size_t>((d.trials + 3) / 4 * 4);
     auto bytes = [](const auto &v) { return v.size() * sizeof(v[0]); };
     const size_t graph = bytes(hg.rp32) + bytes(hg.col) + bytes(hg.val) + bytes(hg.h) +
-                         bytes(hg.pk32) + bytes(hg.pk16) + bytes(hg.ux16) + bytes(hg.ell) +
-                         bytes(hg.eptr);
+                         bytes(hg.pk32) + bytes(hg.ux16) + hg.ell_bytes();
     const size_t window = d.algorithm == PSA_ALG_TAPSA ? static_cast<size_t>(std::max(d.window, 1)) : 0;
-    size_t run = static_cast<size_t>(d.steps) * 4 + 3 * n4 * 4 + n4 + n * t4 + 16 * n4 +
+    size_t run = static_cast<size_t>(d.steps) * 4 + 3 * n4 * 4 + n4 + n * t4 + (hg.wofs.empty() ? 0 : 16 * ((n4 + 255) / 256 * 256)) +
                  (d.algorithm == PSA_ALG_SPSA ? n4 * t4 * 4 : 0) + n4 * t4 * 4 * window;
     const uint32_t path = d.flags & PSA_PATH_MASK;
     bool encodable = hg.n <= 32768;
@@ -174,7 +173,13 @@ void preparer(psa_server *s) {
             const psa_status r = psa::host_graph_from_edges(
                 j->n, static_cast<int64_t>(j->u.size()), j->u.data(), j->v.data(), j->val.data(),
                 j->h.empty() ? nullptr : j->h.data(), j->graph_flags, &hg);
-            if (r == PSA_OK) reserve = reserve_of(hg, j->desc, j->spins_out != nullptr);
+            if (r != PSA_OK) return r;
+            reserve = reserve_of(hg, j->desc, j->spins_out != nullptr);
+            if (reserve > static_cast<size_t>(s->opts.hbm_budget_bytes)) {
+                // without the streaming sweeps' rows the job may still fit
+                hg.drop_ell();
+                reserve = reserve_of(hg, j->desc, j->spins_out != nullptr);
+            }
             return r;
         });
         if (st != PSA_OK) msg = psa_last_error();
