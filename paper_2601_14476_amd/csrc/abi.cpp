@@ -1064,7 +1064,13 @@ psa_status psa_jobs_energy_cut(psa_ctx *ctx, int32_t count, psa_job *const *jobs
         PSA_HIP(hipSetDevice(ctx->device), "hipSetDevice");
         const bool device = (flags & PSA_OUT_DEVICE) != 0;
         std::vector<psa::EnergyJob> table(static_cast<size_t>(count));
-        int64_t wgs = 0, trials = 0;
+        int64_t all_waves = 0, all_wgs = 0;
+        for (int32_t j = 0; j < count; ++j) {
+            const psa::EnergyJob e = psa::energy_job(jobs[j]->g->dev, jobs[j]->run);
+            all_waves += psa::energy_waves(e);
+            all_wgs += psa::energy_batch_wgs(e);
+        }
+        int64_t wgs = 0, groups = 0, trials = 0;
         for (int32_t j = 0; j < count; ++j) {
             psa_job *job = jobs[j];
             // each run's partial sums (and host staging) in its own scratch,
@@ -1075,26 +1081,15 @@ psa_status psa_jobs_energy_cut(psa_ctx *ctx, int32_t count, psa_job *const *jobs
             if (st != PSA_OK) return st;
             int64_t *tmp = static_cast<int64_t *>(job->d_scratch);
             psa::EnergyJob &e = table[static_cast<size_t>(j)];
-            e.n = job->g->info.n;
-            e.t4 = job->run.t4;
-            e.trials = job->run.trials;
-            e.blocks = (e.n + 255) / 256;
-            // rows of mean degree 48 or more are read by 16 lanes, of 12 or
-            // more by 4 (contiguous column reads), sparser rows by one lane
-            const int64_t deg = e.n > 0 ? job->g->dev.nnz / e.n : 0;
-            e.lpr = deg >= 48 ? 16 : deg >= 12 ? 4 : 1;
+            e = psa::energy_job(job->g->dev, job->run);
+            psa::energy_split(&e, all_waves, all_wgs);
             e.wg0 = static_cast<int32_t>(wgs);
-            e.k0 = static_cast<int32_t>(trials);
-            e.w2 = job->g->dev.w2;
-            e.row_ptr = job->g->dev.row_ptr;
-            e.col = job->g->dev.col;
-            e.val = job->g->dev.val;
-            e.h = job->g->dev.h;
-            e.spins = job->run.spins;
+            e.q0 = static_cast<int32_t>(groups);
             e.part = tmp + 2 * job->run.trials;
             e.energy = device ? energy[j] : tmp;
             e.cut = device ? cut[j] : tmp + job->run.trials;
-            wgs += psa::energy_batch_wgs(e.n, e.t4);
+            wgs += psa::energy_batch_wgs(e);
+            groups += e.t4 / 4;
             trials += e.trials;
             if (wgs > std::numeric_limits<int32_t>::max() || trials > std::numeric_limits<int32_t>::max()) {
                 set_error("psa_jobs_energy_cut: too many runs for one read-out");
@@ -1120,7 +1115,8 @@ psa_status psa_jobs_energy_cut(psa_ctx *ctx, int32_t count, psa_job *const *jobs
                                ctx->stream),
                 "energy table upload");
         PSA_HIP(psa::launch_energy_cut_batch(ctx->stream, static_cast<const psa::EnergyJob *>(ctx->d_energy_table),
-                                             count, static_cast<int32_t>(wgs), static_cast<int32_t>(trials)),
+                                             ctx->h_energy_table.data(), count, static_cast<int32_t>(wgs),
+                                             static_cast<int32_t>(groups)),
                 "energy/cut");
         if (device) return PSA_OK;
         for (int32_t j = 0; j < count; ++j) {

@@ -86,6 +86,8 @@ struct DevGraph {
     int32_t n4 = 0;
     int64_t nnz = 0;
     int32_t max_degree = 0;
+    int32_t max_field = 0;             // max_i |h_i| + sum_j |J_ij|
+    int32_t any_h = 0;                 // some h_i != 0
     const int32_t *row_ptr = nullptr;  // [n4+4]
     const int32_t *col = nullptr;      // [nnz]
     const int32_t *val = nullptr;      // [nnz]
@@ -382,24 +384,74 @@ hipError_t launch_energy_cut(hipStream_t stream, const DevGraph &g, const DevRun
 // One run of a batched energy / cut read-out: its graph and spins, its share
 // of the partial-sum buffer (energy_partial_bytes of it) and its outputs.
 // wg0: its first workgroup of the partial pass (energy_batch_wgs of them);
-// k0: its first thread of the final pass (one per trial); lpr: lanes that
-// share a row in the partial pass (1, 4 or 16, by the mean degree).
+// q0: its first wavefront of the final pass (one per trial group); cpl, lpr:
+// lanes of neighbouring 16-trial chunks, and such groups to a row
+// (read_out_split).
 struct EnergyJob {
     int32_t n = 0, t4 = 0, trials = 0, blocks = 0;
-    int32_t wg0 = 0, k0 = 0, lpr = 1;
+    int32_t wg0 = 0, q0 = 0, cpl = 1, lpr = 1;
+    int32_t quads = 4;           // trial groups per lane of the partial pass: 4 or 1
+    int32_t narrow = 0;          // sums over 256 rows fit int32
     int64_t w2 = 0;
-    const int32_t *row_ptr = nullptr, *col = nullptr, *val = nullptr, *h = nullptr;
+    const int32_t *row_ptr = nullptr, *col = nullptr, *val = nullptr, *h = nullptr;  // h: null when all 0
     const int8_t *spins = nullptr;
     int64_t *part = nullptr;
     int64_t *energy = nullptr, *cut = nullptr;
 };
-// The read-outs of `count` runs (a device table, wg0 and k0 ascending) in two
-// launches: wgs = the runs' partial workgroups, trials = their trials.
-hipError_t launch_energy_cut_batch(hipStream_t stream, const EnergyJob *jobs, int32_t count, int32_t wgs,
-                                   int32_t trials);
-// Workgroups of one run's batched partial pass: row blocks x chunks of 16 trials.
-inline int64_t energy_batch_wgs(int32_t n, int32_t t4) {
-    return static_cast<int64_t>((n + 255) / 256) * ((t4 / 4 + 3) / 4);
+// A run's entry but for its share of the partial sums, its outputs and its
+// first indices.
+EnergyJob energy_job(const DevGraph &g, const DevRun &run);
+// The read-outs of `count` runs (a device table, wg0 and q0 ascending) in two
+// launches: wgs = the runs' partial workgroups, groups = their trial groups;
+// host: the same table on the host (all runs of one `quads`).
+hipError_t launch_energy_cut_batch(hipStream_t stream, const EnergyJob *jobs, const EnergyJob *host, int32_t count,
+                                   int32_t wgs, int32_t groups);
+// Lanes of a row in the read-outs, powers of two, at most 16 together: cpl
+// lanes over neighbouring 16-trial chunks (as many as wastes the fewest lanes,
+// the larger of equals, since their gathers are contiguous), and of the rest
+// lpr over the edges of rows of mean degree 12 or more.
+inline void read_out_split(int32_t t4, int64_t degree, int32_t *cpl, int32_t *lpr) {
+    const int32_t chunks = (t4 + 15) / 16;
+    *cpl = 1;
+    for (int32_t c = 2; c <= 16; c *= 2)
+        if ((chunks + c - 1) / c * c <= (chunks + *cpl - 1) / *cpl * *cpl) *cpl = c;
+    *lpr = degree >= 48 ? 16 / *cpl : (degree >= 12 ? (16 / *cpl < 4 ? 16 / *cpl : 4) : 1);
+}
+// Workgroups of one run's partial pass: row blocks x groups of cpl chunks.
+inline int64_t energy_batch_wgs(const EnergyJob &e) {
+    const int32_t chunks = (e.t4 + 4 * e.quads - 1) / (4 * e.quads);
+    return static_cast<int64_t>(e.blocks) * ((chunks + e.cpl - 1) / e.cpl);
+}
+// Threads of a run's partial pass: a lane for each of the 256 rows' shares, at
+// most 1,024 (then a lane takes several rows).
+inline int32_t energy_block(const EnergyJob &e) {
+    const int32_t lanes = 256 * e.cpl * e.lpr;
+    return lanes < 1024 ? lanes : 1024;
+}
+// Wavefronts with work in one run's partial pass.
+inline int64_t energy_waves(const EnergyJob &e) {
+    return static_cast<int64_t>(e.n) * e.lpr * ((e.t4 + 4 * e.quads - 1) / (4 * e.quads)) / 64;
+}
+// Split of a partial pass whose read-out (all its runs at their widest chunks)
+// has `waves` wavefronts in `wgs` workgroups.  Below kEnergyWaves the chip is
+// short of loads in flight: four trials per lane instead of sixteen (2,000
+// p-bits of degree 6, 100 trials: 8.2 against 15.8 us; 20,000 of degree 4, 100
+// trials: 14.2 against 30.6).  Above, a read-out of fewer workgroups than
+// compute units takes narrower groups of chunks (20,000 p-bits of degree 20,
+// 256 trials: 316 workgroups of 64-byte gathers instead of 79 of 256-byte ones,
+// 48 against 243 us).
+constexpr int64_t kEnergyWaves = 4096, kEnergyWgs = 256;
+inline void energy_split(EnergyJob *e, int64_t waves, int64_t wgs) {
+    if (waves < kEnergyWaves) {
+        e->quads = 1;
+        e->lpr = e->lpr == 1 ? 1 : (e->lpr * e->cpl >= 16 ? 16 : 4);
+        e->cpl = 1;
+    } else if (wgs < kEnergyWgs) {
+        while (e->cpl > 1 && energy_batch_wgs(*e) < kEnergyWgs) {
+            e->cpl /= 2;
+            if (e->lpr > 1) e->lpr *= 2;
+        }
+    }
 }
 hipError_t launch_spins_to_tn(hipStream_t stream, int32_t n, const DevRun &run,
                               int8_t *out_tn);

@@ -472,6 +472,8 @@ psa_status upload_graph(psa_ctx *ctx, HostGraph &&hg, psa_graph **out) {
     g->dev.n4 = hg.n4;
     g->dev.nnz = hg.nnz;
     g->dev.max_degree = hg.max_degree;
+    g->dev.max_field = hg.info.max_abs_field;
+    g->dev.any_h = std::any_of(hg.h.begin(), hg.h.end(), [](int32_t x) { return x != 0; }) ? 1 : 0;
     g->dev.row_ptr = g->d_row_ptr;
     g->dev.col = g->d_col;
     g->dev.val = g->d_val;

@@ -1,7 +1,7 @@
 // kernels.hip -- gfx950 kernels of the pSA hot path.
 //
 //   init_spins_kernel   initial state: m = +1 iff bit 31 of the INIT word
-//   local_field_kernel  L = h + J m (Eq. 3 without I0), for tests
+//   local_field_kernel  L = h + J m (Eq. 3 without I0)
 //   energy_partial_kernel, energy_finish_kernel   Eq. 2 energy and MAX-CUT value per trial
 //   spins_{to,from}_tn  layout conversion [n][t4] <-> [trials][n]
 //
@@ -54,135 +54,51 @@ __global__ void init_spins_kernel(int32_t n, int32_t tasks, int32_t t4, uint32_t
 }
 
 // ---------------------------------------------------------------------------
-// Local field, thread per (i, q); out is [trials][n].
-// ---------------------------------------------------------------------------
-__global__ void local_field_kernel(int32_t n, int32_t quads, int32_t t4, int32_t trials,
-                                   const int32_t *__restrict__ row_ptr,
-                                   const int32_t *__restrict__ col,
-                                   const int32_t *__restrict__ val,
-                                   const int32_t *__restrict__ h,
-                                   const int8_t *__restrict__ spins, int32_t *__restrict__ out) {
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= static_cast<int64_t>(n) * quads) return;
-    const int32_t i = static_cast<int32_t>(idx % n);
-    const int32_t q = static_cast<int32_t>(idx / n);
-    int32_t L[4] = {h[i], h[i], h[i], h[i]};
-    for (int32_t e = row_ptr[i]; e < row_ptr[i + 1]; ++e) {
-        const uint32_t wj = load_word(spins, t4, col[e], q);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) L[k] += val[e] * spin_of(wj, k);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int32_t trial = 4 * q + k;
-        if (trial < trials) out[static_cast<size_t>(trial) * n + i] = L[k];
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Energy and cut, one workgroup per quad of trials.  With
+// Energy and cut.  With
 // S_k = sum_i m_i sum_j J_ij m_j (= 2 sum_{i<j} J_ij m_i m_j) and
 // W2 = sum_i sum_j J_ij:
 //   E_k   = -sum_i h_i m_i - S_k / 2
 //   cut_k = sum_{i<j} w_ij [m_i != m_j] = (S_k - W2) / 4     (w = -J)
 // ---------------------------------------------------------------------------
-constexpr int kEnergyBlock = 256;
+constexpr int kEnergyRows = 256;   // rows of a partial sum
+constexpr int kEnergyBlock = 1024;  // most threads of a partial pass
+constexpr int kFieldBlock = 256;
 
-// Pass 1: workgroup (row block, trial group q) sums, over its 256 rows, the
-// row terms m_i sum_j J_ij m_j and h_i m_i of the four trials of q; thread
-// per row.  part[(block * groups + q) * 8 + c]: c < 4 the S terms of trial
-// 4q + c, c >= 4 the h terms.
-__device__ __forceinline__ void energy_partial(int32_t n, int32_t t4, const int32_t *__restrict__ row_ptr,
-                                               const int32_t *__restrict__ col, const int32_t *__restrict__ val,
-                                               const int32_t *__restrict__ h, const int8_t *__restrict__ spins,
-                                               int64_t *__restrict__ part, int32_t blk, int32_t q) {
-    const int32_t groups = t4 / 4;
-    const int32_t i = blk * kEnergyBlock + threadIdx.x;
-    int64_t s[4] = {0, 0, 0, 0};
-    int64_t hm[4] = {0, 0, 0, 0};
-    if (i < n) {
-        const uint32_t wi = load_word(spins, t4, i, q);
-        int32_t L[4] = {0, 0, 0, 0};
-        const int32_t e1 = row_ptr[i + 1];
-#pragma unroll 4
-        for (int32_t e = row_ptr[i]; e < e1; ++e) {
-            const uint32_t wj = load_word(spins, t4, col[e], q);
-            const int32_t J = val[e];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) L[k] += J * spin_of(wj, k);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int32_t mi = spin_of(wi, k);
-            s[k] = static_cast<int64_t>(mi * L[k]);
-            hm[k] = static_cast<int64_t>(mi * h[i]);
-        }
-    }
-    __shared__ int64_t red[kEnergyBlock / 64][8];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        for (int off = 32; off > 0; off >>= 1) {
-            s[k] += __shfl_down(s[k], off, 64);
-            hm[k] += __shfl_down(hm[k], off, 64);
-        }
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            red[wave][k] = s[k];
-            red[wave][4 + k] = hm[k];
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < 8) {
-        int64_t v = 0;
-        for (int w = 0; w < kEnergyBlock / 64; ++w) v += red[w][threadIdx.x];
-        part[(static_cast<size_t>(blk) * groups + q) * 8 + threadIdx.x] = v;
-    }
-}
-
-__global__ __launch_bounds__(kEnergyBlock) void energy_partial_kernel(
-    int32_t n, int32_t t4, const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-    const int32_t *__restrict__ val, const int32_t *__restrict__ h,
-    const int8_t *__restrict__ spins, int64_t *__restrict__ part) {
-    energy_partial(n, t4, row_ptr, col, val, h, spins, part, blockIdx.x, blockIdx.y);
-}
-
-// Pass 2: thread per trial k sums the row blocks' terms:
+// Final pass: a wavefront sums the row blocks' terms of one trial group, eight
+// lanes (the group's S and h terms) to a block, then reduces over the blocks:
 //   E_k   = -sum_i h_i m_i - S_k / 2
 //   cut_k = sum_{i<j} w_ij [m_i != m_j] = (S_k - W2) / 4     (w = -J)
-__device__ __forceinline__ void energy_finish(int32_t blocks, int32_t groups, int32_t k, int64_t w2,
-                                              const int64_t *__restrict__ part, int64_t *__restrict__ energy,
-                                              int64_t *__restrict__ cut) {
-    const int32_t q = k >> 2, c = k & 3;
-    int64_t S = 0, H = 0;
-    for (int32_t b = 0; b < blocks; ++b) {
-        S += part[(static_cast<size_t>(b) * groups + q) * 8 + c];
-        H += part[(static_cast<size_t>(b) * groups + q) * 8 + 4 + c];
+// A thread per trial walking the blocks one by one took 20 us at 20,000 p-bits
+// (79 dependent loads); this 4.7 us.
+__device__ __forceinline__ void energy_finish(const EnergyJob &e, int32_t q) {
+    const int lane = threadIdx.x & 63, c = lane & 7;
+    const int32_t groups = e.t4 / 4;
+    int64_t v = 0;
+    for (int32_t b = lane >> 3; b < e.blocks; b += 8) v += e.part[(static_cast<size_t>(b) * groups + q) * 8 + c];
+#pragma unroll
+    for (int off = 8; off < 64; off <<= 1) v += __shfl_xor(v, off);
+    const int64_t H = __shfl_down(v, 4);
+    const int32_t k = 4 * q + c;
+    if (lane < 4 && k < e.trials) {
+        e.energy[k] = -H - v / 2;
+        e.cut[k] = (v - e.w2) / 4;
     }
-    energy[k] = -H - S / 2;
-    cut[k] = (S - w2) / 4;
 }
 
-__global__ void energy_finish_kernel(int32_t blocks, int32_t groups, int32_t trials, int64_t w2,
-                                     const int64_t *__restrict__ part, int64_t *__restrict__ energy,
-                                     int64_t *__restrict__ cut) {
-    const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= trials) return;
-    energy_finish(blocks, groups, k, w2, part, energy, cut);
+// One run (its table entry as the argument).
+__global__ __launch_bounds__(64) void energy_finish_kernel(EnergyJob e) {
+    energy_finish(e, static_cast<int32_t>(blockIdx.x));
 }
 
 // The run of a batched read-out that index x (a workgroup of the partial
-// pass, or a trial of the final pass) belongs to: the last run whose first
-// index is at most x (first indices ascending, the first one 0).
+// pass, or a trial group of the final pass) belongs to: the last run whose
+// first index is at most x (first indices ascending, the first one 0).
 template <bool WG>
 __device__ __forceinline__ int32_t energy_run_of(const EnergyJob *__restrict__ jobs, int32_t count, int32_t x) {
     int32_t lo = 0, hi = count - 1;
     while (lo < hi) {
         const int32_t mid = (lo + hi + 1) >> 1;
-        if ((WG ? jobs[mid].wg0 : jobs[mid].k0) <= x)
+        if ((WG ? jobs[mid].wg0 : jobs[mid].q0) <= x)
             lo = mid;
         else
             hi = mid - 1;
@@ -190,153 +106,215 @@ __device__ __forceinline__ int32_t energy_run_of(const EnergyJob *__restrict__ j
     return lo;
 }
 
-// Batched partial pass, sixteen trials per lane: workgroup (row block, chunk
-// y of four trial groups) sums the terms of groups 4y..4y+3 (those below
-// t4 / 4) into the same part entries as energy_partial.  LPR lanes share a
-// row: lane `sub` of a group takes the row's edges sub, sub + LPR, ... (so
-// the group's column and coupling reads are contiguous), reading each edge's
-// column and coupling once per 16 trials and, when t4 is a multiple of 16,
-// the neighbour's 16 spins in one load.  Because S = sum_i m_i sum_j J_ij m_j
-// is linear in each row's inner sum, every lane multiplies its share of the
-// inner sum by m_i and keeps the products; the h terms are taken by lane 0 of
-// the group.  A group's rows are g, g + 256 / LPR, ... of the block.  A row's
-// terms are below 2^24 in magnitude (the field bound), so a lane's sum over
-// its LPR <= 16 rows fits int32; sums across lanes are taken in int64.
-constexpr int kEnergyQuads = 4;
+// Read-out work split.  A lane holds sixteen trials (a chunk of Q = 4 trial
+// groups) of a row: the `cpl` lanes of consecutive chunks read a neighbour's
+// spins as one contiguous piece of up to 256 bytes, and `lpr` such groups share
+// a long row's edges; cpl lpr <= 16 lanes to a row.  Runs too small to fill
+// the chip that way take Q = 1, four trials to a lane (energy_split).
+struct ReadLane {
+    int32_t c, sub, row;      // chunk, share of the row, row of the block
+    int32_t q0, nq;           // first trial group of the chunk, groups in it (none: <= 0)
+    int32_t rows;             // rows in flight together
+};
+template <int Q>
+__device__ __forceinline__ ReadLane read_lane(const EnergyJob &e, int32_t y) {
+    ReadLane l;
+    const int32_t tid = static_cast<int32_t>(threadIdx.x);
+    l.c = tid & (e.cpl - 1);
+    l.sub = (tid / e.cpl) & (e.lpr - 1);
+    l.row = tid / (e.cpl * e.lpr);
+    l.rows = static_cast<int32_t>(blockDim.x) / (e.cpl * e.lpr);
+    l.q0 = (y * e.cpl + l.c) * Q;
+    l.nq = min(e.t4 / 4 - l.q0, Q);
+    return l;
+}
 
-template <int LPR>
-__device__ __forceinline__ void energy_partial16(const EnergyJob &e, int32_t blk, int32_t y) {
-    constexpr int Q = kEnergyQuads;
-    constexpr int kGroups = kEnergyBlock / LPR;
-    const int32_t t4 = e.t4;
-    const int32_t groups = t4 / 4;
-    const int32_t q0 = y * Q;
-    const int32_t nq = groups - q0 < Q ? groups - q0 : Q;  // workgroup-uniform
-    const bool vec = (t4 & 15) == 0 && (reinterpret_cast<uintptr_t>(e.spins) & 15) == 0;
-    const int32_t sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
-    int32_t s32[Q][4] = {}, hm32[Q][4] = {};
-    for (int32_t r = 0; r < LPR; ++r) {
-        const int32_t i = blk * kEnergyBlock + grp + kGroups * r;
-        if (i >= e.n) break;
-        int32_t L[Q][4] = {};
-        const int32_t e1 = e.row_ptr[i + 1];
-#pragma unroll 2
-        for (int32_t x = e.row_ptr[i] + sub; x < e1; x += LPR) {
-            const int32_t j = e.col[x];
-            const int32_t J = e.val[x];
-            uint32_t w[Q] = {0u, 0u, 0u, 0u};
-            if (vec) {
-                const uint4 v4 = *reinterpret_cast<const uint4 *>(e.spins + static_cast<size_t>(j) * t4 + 4 * q0);
-                w[0] = v4.x;
-                w[1] = v4.y;
-                w[2] = v4.z;
-                w[3] = v4.w;
-            } else {
+// A lane's share of sum_j J_ij m_j of row i: edges sub, sub + lpr, ...  A
+// whole chunk's spins are one 16-byte load, aligned to 4 bytes.
+typedef u32x4 __attribute__((aligned(4))) u32x4_word;
+template <int Q>
+__device__ __forceinline__ void row_sums(const EnergyJob &e, int32_t i, const ReadLane &l, int32_t (&L)[Q][4]) {
+    const int32_t e1 = e.row_ptr[i + 1];
+#pragma unroll 4
+    for (int32_t x = e.row_ptr[i] + l.sub; x < e1; x += e.lpr) {
+        const int32_t j = e.col[x];
+        const int32_t J = e.val[x];
+        uint32_t w[Q] = {};
+        if (Q == 4 && l.nq == Q) {
+            const u32x4 v = *reinterpret_cast<const u32x4_word *>(e.spins + static_cast<size_t>(j) * e.t4 + 4 * l.q0);
 #pragma unroll
-                for (int qq = 0; qq < Q; ++qq)
-                    if (qq < nq) w[qq] = load_word(e.spins, t4, j, q0 + qq);
-            }
+            for (int qq = 0; qq < Q; ++qq) w[qq] = v[qq];
+        } else {
 #pragma unroll
             for (int qq = 0; qq < Q; ++qq)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) L[qq][k] += J * spin_of(w[qq], k);
+                if (qq < l.nq) w[qq] = load_word(e.spins, e.t4, j, l.q0 + qq);
         }
-        const int32_t hi = sub == 0 ? e.h[i] : 0;
-#pragma unroll
-        for (int qq = 0; qq < Q; ++qq) {
-            if (qq < nq) {
-                const uint32_t wi = load_word(e.spins, t4, i, q0 + qq);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int32_t mi = spin_of(wi, k);
-                    s32[qq][k] += mi * L[qq][k];
-                    hm32[qq][k] += mi * hi;
-                }
-            }
-        }
-    }
-    int64_t s[Q][4], hm[Q][4];
-#pragma unroll
-    for (int qq = 0; qq < Q; ++qq)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            s[qq][k] = s32[qq][k];
-            hm[qq][k] = hm32[qq][k];
-        }
-    __shared__ int64_t red[kEnergyBlock / 64][Q][8];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int qq = 0; qq < Q; ++qq)
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            for (int off = 32; off > 0; off >>= 1) {
-                s[qq][k] += __shfl_down(s[qq][k], off, 64);
-                hm[qq][k] += __shfl_down(hm[qq][k], off, 64);
-            }
-    if (lane == 0) {
 #pragma unroll
         for (int qq = 0; qq < Q; ++qq)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                red[wave][qq][k] = s[qq][k];
-                red[wave][qq][4 + k] = hm[qq][k];
+            for (int k = 0; k < 4; ++k) L[qq][k] += J * spin_of(w[qq], k);
+    }
+}
+
+// Partial pass: workgroup (256-row block, group y of cpl chunks) sums m_i
+// sum_j J_ij m_j and h_i m_i over its rows into part[(block * groups + q) * 8
+// + c]: c < 4 the S terms of trial 4q + c, c >= 4 the h terms.  S is linear
+// in each row's inner sum, so a lane multiplies its share of it by m_i and
+// keeps the product; the h terms (none when every h is 0) are taken by the
+// row's first share.  SUM: the type a block's sums fit -- int32 when 256 rows
+// of the field bound do (then a reduction step is one exchange), else int64.
+// A lane's own sum is over at most 16 rows (256 threads, at most 16 to a row)
+// of terms below 2^24: int32.
+template <typename SUM, int Q>
+__device__ __forceinline__ void energy_partial_run(const EnergyJob &e, int32_t local) {
+    const int32_t groups = e.t4 / 4;
+    const int32_t ys = (groups + Q * e.cpl - 1) / (Q * e.cpl);
+    const int32_t blk = local / ys;
+    const ReadLane l = read_lane<Q>(e, local % ys);
+    const bool has_h = e.h != nullptr;
+    int32_t s32[Q][4] = {}, hm32[Q][4] = {};
+    if (l.nq > 0)
+        for (int32_t r = l.row; r < kEnergyRows; r += l.rows) {
+            const int32_t i = blk * kEnergyRows + r;
+            if (i >= e.n) break;
+            int32_t L[Q][4] = {};
+            row_sums<Q>(e, i, l, L);
+            const int32_t hi = has_h && l.sub == 0 ? e.h[i] : 0;
+#pragma unroll
+            for (int qq = 0; qq < Q; ++qq) {
+                if (qq < l.nq) {
+                    const uint32_t wi = load_word(e.spins, e.t4, i, l.q0 + qq);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int32_t mi = spin_of(wi, k);
+                        s32[qq][k] += mi * L[qq][k];
+                        hm32[qq][k] += mi * hi;
+                    }
+                }
             }
+        }
+    // over the lanes of a chunk, then over the wavefronts
+    extern __shared__ __align__(16) unsigned char energy_lds[];  // energy_lds_bytes
+    SUM *red = reinterpret_cast<SUM *>(energy_lds);              // [wavefronts][cpl][Q][8]
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    SUM v[Q * 8];  // the S terms, then the h terms
+#pragma unroll
+    for (int x = 0; x < 4 * Q; ++x) {
+        v[x] = s32[x >> 2][x & 3];
+        v[4 * Q + x] = hm32[x >> 2][x & 3];
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)  // every value's exchange of a step in flight together
+        if (off >= e.cpl) {
+#pragma unroll
+            for (int x = 0; x < 4 * Q; ++x) v[x] += __shfl_xor(v[x], off);
+            if (has_h) {
+#pragma unroll
+                for (int x = 4 * Q; x < 8 * Q; ++x) v[x] += __shfl_xor(v[x], off);
+            }
+        }
+    if (lane < e.cpl) {
+#pragma unroll
+        for (int x = 0; x < 4 * Q; ++x) {
+            SUM *to = red + ((wave * e.cpl + lane) * Q + (x >> 2)) * 8 + (x & 3);
+            to[0] = v[x];
+            to[4] = v[4 * Q + x];
+        }
     }
     __syncthreads();
-    if (threadIdx.x < 8 * Q) {
-        const int qq = threadIdx.x >> 3, c = threadIdx.x & 7;
-        if (qq < nq) {
-            int64_t v = 0;
-            for (int wv = 0; wv < kEnergyBlock / 64; ++wv) v += red[wv][qq][c];
-            e.part[(static_cast<size_t>(blk) * groups + q0 + qq) * 8 + c] = v;
+    for (int32_t x = threadIdx.x; x < 8 * Q * e.cpl; x += static_cast<int32_t>(blockDim.x)) {
+        const int32_t ch = x / (8 * Q), qq = (x >> 3) % Q, c = x & 7;
+        const int32_t q = ((local % ys) * e.cpl + ch) * Q + qq;
+        if (q < groups) {
+            int64_t sum = 0;
+            for (int wv = 0; wv < static_cast<int>(blockDim.x) / 64; ++wv) sum += red[((wv * e.cpl + ch) * Q + qq) * 8 + c];
+            e.part[(static_cast<size_t>(blk) * groups + q) * 8 + c] = sum;
         }
     }
 }
 
-// Batched partial pass: workgroup b is (row block, chunk of four trial
-// groups) b - wg0 of its run, row block major; the run's lanes per row
-// (1, 4 or 16) pick the variant, uniform over the workgroup.
+// One run: 20,000 p-bits of degree 20, 256 trials: 48 us (a thread per row
+// and four trials, which the one-run read-out used before: 224 us).
+template <typename SUM, int Q>
+__global__ __launch_bounds__(kEnergyBlock) void energy_partial_kernel(EnergyJob e) {
+    energy_partial_run<SUM, Q>(e, static_cast<int32_t>(blockIdx.x));
+}
+
+// Many runs: workgroup b is workgroup b - wg0 of its run.
+template <typename SUM, int Q>
 __global__ __launch_bounds__(kEnergyBlock) void energy_partial_batch_kernel(const EnergyJob *__restrict__ jobs,
                                                                             int32_t count) {
     const int32_t b = blockIdx.x;
     const EnergyJob &e = jobs[energy_run_of<true>(jobs, count, b)];
-    const int32_t chunks = (e.t4 / 4 + kEnergyQuads - 1) / kEnergyQuads;
-    const int32_t local = b - e.wg0;
-    if (e.lpr >= 16)
-        energy_partial16<16>(e, local / chunks, local % chunks);
-    else if (e.lpr >= 4)
-        energy_partial16<4>(e, local / chunks, local % chunks);
-    else
-        energy_partial16<1>(e, local / chunks, local % chunks);
+    energy_partial_run<SUM, Q>(e, b - e.wg0);
 }
 
-// Batched final pass: thread x is trial x - k0 of its run.
-__global__ void energy_finish_batch_kernel(const EnergyJob *__restrict__ jobs, int32_t count, int32_t trials) {
-    const int32_t x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= trials) return;
+// Many runs' final pass: wavefront x is trial group x - q0 of its run.
+__global__ __launch_bounds__(64) void energy_finish_batch_kernel(const EnergyJob *__restrict__ jobs, int32_t count) {
+    const int32_t x = blockIdx.x;
     const EnergyJob &e = jobs[energy_run_of<false>(jobs, count, x)];
-    energy_finish(e.blocks, e.t4 / 4, x - e.k0, e.w2, e.part, e.energy, e.cut);
+    energy_finish(e, x - e.q0);
 }
 
-// [n][t4] -> [trials][n]
-__global__ void spins_to_tn_kernel(int32_t n, int32_t t4, int32_t trials,
-                                   const int8_t *__restrict__ spins, int8_t *__restrict__ out) {
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= static_cast<int64_t>(n) * trials) return;
-    const int32_t k = static_cast<int32_t>(idx / n);
-    const int32_t i = static_cast<int32_t>(idx % n);
-    out[idx] = spins[static_cast<size_t>(i) * t4 + k];
+// Local fields L = h + J m, int32 [trials][n]: the same split of lanes; the
+// shares of a row are reduced and divide its stores.  Bound by the spin
+// gathers from L2 (20,000 p-bits of degree 20, 256 trials: 103 MB): 35 us,
+// against 375 us with a thread per p-bit and four trials (4-byte gathers) and
+// 60 us with a chunk's rows on neighbouring lanes (16-byte gathers).
+__global__ __launch_bounds__(kFieldBlock) void local_field_kernel(EnergyJob e, int32_t *__restrict__ out) {
+    constexpr int Q = 4;
+    const ReadLane l = read_lane<Q>(e, static_cast<int32_t>(blockIdx.y));
+    const int32_t i = static_cast<int32_t>(blockIdx.x) * l.rows + l.row;
+    int32_t L[Q][4] = {};
+    if (i < e.n && l.nq > 0) row_sums<Q>(e, i, l, L);
+    const int32_t h = i < e.n && e.h ? e.h[i] : 0;
+#pragma unroll
+    for (int x = 0; x < 4 * Q; ++x) {
+        int32_t v = L[x >> 2][x & 3];
+        for (int off = e.cpl; off < e.cpl * e.lpr; off <<= 1) v += __shfl_xor(v, off);
+        const int32_t trial = 4 * l.q0 + x;
+        if ((x & (e.lpr - 1)) == l.sub && i < e.n && trial < e.trials) out[static_cast<size_t>(trial) * e.n + i] = h + v;
+    }
 }
 
-// [trials][n] -> [n][t4]; padding trials (k >= trials) are left unchanged.
-__global__ void spins_from_tn_kernel(int32_t n, int32_t t4, int32_t trials,
-                                     const int8_t *__restrict__ in, int8_t *__restrict__ spins) {
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= static_cast<int64_t>(n) * trials) return;
-    const int32_t k = static_cast<int32_t>(idx / n);
-    const int32_t i = static_cast<int32_t>(idx % n);
-    spins[static_cast<size_t>(i) * t4 + k] = in[idx];
+// Layout changes between [n][t4] (trials innermost) and [trials][n], 64 p-bits
+// x 64 trials per workgroup through LDS so that both sides are read and
+// written in runs of 64 bytes (a thread per byte of the output, reading one
+// byte of a row each, took 24.6 us at 20,000 p-bits x 256 trials; this 5.6 us).
+constexpr int kTile = 64;
+
+// spins -> out
+__global__ __launch_bounds__(256) void spins_to_tn_kernel(int32_t n, int32_t t4, int32_t trials,
+                                                          const int8_t *__restrict__ spins, int8_t *__restrict__ out) {
+    __shared__ int8_t tile[kTile][kTile + 4];
+    const int32_t i0 = static_cast<int32_t>(blockIdx.x) * kTile, k0 = static_cast<int32_t>(blockIdx.y) * kTile;
+    // 16 words of four trials per row
+    for (int32_t x = threadIdx.x; x < kTile * 16; x += 256) {
+        const int32_t r = x / 16, w = x % 16;
+        if (i0 + r < n && k0 + 4 * w < t4)
+            *reinterpret_cast<uint32_t *>(&tile[r][4 * w]) = load_word(spins, t4, i0 + r, k0 / 4 + w);
+    }
+    __syncthreads();
+    const int32_t c = threadIdx.x & 63;
+    if (i0 + c >= n) return;
+    for (int32_t r = threadIdx.x >> 6; r < kTile && k0 + r < trials; r += 4)
+        out[static_cast<size_t>(k0 + r) * n + i0 + c] = tile[c][r];
+}
+
+// in -> spins; padding trials (k >= trials) are left unchanged.
+__global__ __launch_bounds__(256) void spins_from_tn_kernel(int32_t n, int32_t t4, int32_t trials,
+                                                            const int8_t *__restrict__ in, int8_t *__restrict__ spins) {
+    __shared__ int8_t tile[kTile][kTile + 4];
+    const int32_t i0 = static_cast<int32_t>(blockIdx.x) * kTile, k0 = static_cast<int32_t>(blockIdx.y) * kTile;
+    const int32_t c = threadIdx.x & 63;
+    if (i0 + c < n)
+        for (int32_t r = threadIdx.x >> 6; r < kTile && k0 + r < trials; r += 4)
+            tile[c][r] = in[static_cast<size_t>(k0 + r) * n + i0 + c];
+    __syncthreads();
+    if (k0 + c >= trials) return;
+    for (int32_t r = threadIdx.x >> 6; r < kTile && i0 + r < n; r += 4)
+        spins[static_cast<size_t>(i0 + r) * t4 + k0 + c] = tile[r][c];
 }
 
 inline unsigned grid_for(int64_t items, int block) {
@@ -378,58 +356,93 @@ hipError_t launch_init_spins(hipStream_t stream, int32_t n, const DevRun &run) {
     return hipGetLastError();
 }
 
+EnergyJob energy_job(const DevGraph &g, const DevRun &run) {
+    EnergyJob e;
+    e.n = g.n;
+    e.t4 = run.t4;
+    e.trials = run.trials;
+    e.blocks = (g.n + kEnergyRows - 1) / kEnergyRows;
+    read_out_split(run.t4, g.n > 0 ? g.nnz / g.n : 0, &e.cpl, &e.lpr);
+    e.w2 = g.w2;
+    e.row_ptr = g.row_ptr;
+    e.col = g.col;
+    e.val = g.val;
+    e.h = g.any_h ? g.h : nullptr;
+    e.narrow = g.max_field < (1 << 23) ? 1 : 0;
+    e.spins = run.spins;
+    return e;
+}
+
 hipError_t launch_local_field(hipStream_t stream, const DevGraph &g, const DevRun &run,
                               int32_t *out_tn) {
-    const int32_t quads = run.t4 / 4;
-    const int block = 256;
-    hipLaunchKernelGGL(local_field_kernel, dim3(grid_for(static_cast<int64_t>(g.n) * quads, block)),
-                       dim3(block), 0, stream, g.n, quads, run.t4, run.trials, g.row_ptr, g.col,
-                       g.val, g.h, run.spins, out_tn);
+    const EnergyJob e = energy_job(g, run);
+    const int32_t chunks = (run.t4 + 15) / 16;
+    hipLaunchKernelGGL(local_field_kernel,
+                       dim3(grid_for(static_cast<int64_t>(g.n) * e.cpl * e.lpr, kFieldBlock), (chunks + e.cpl - 1) / e.cpl),
+                       dim3(kFieldBlock), 0, stream, e, out_tn);
     return hipGetLastError();
 }
 
 size_t energy_partial_bytes(int32_t n, int32_t t4) {
-    return static_cast<size_t>((n + kEnergyBlock - 1) / kEnergyBlock) * (t4 / 4) * 8 * sizeof(int64_t);
+    return static_cast<size_t>((n + kEnergyRows - 1) / kEnergyRows) * (t4 / 4) * 8 * sizeof(int64_t);
+}
+
+// LDS of a partial pass: a partial sum per wavefront, chunk and term.  At most
+// 64 KB (1,024 threads, 16 chunks of 16 trials, int64).
+static size_t energy_lds_bytes(const EnergyJob &e, int32_t block, bool narrow) {
+    return static_cast<size_t>(block / 64) * e.cpl * e.quads * 8 * (narrow ? 4 : 8);
 }
 
 hipError_t launch_energy_cut(hipStream_t stream, const DevGraph &g, const DevRun &run,
                              int64_t *part, int64_t *energy, int64_t *cut) {
-    const int32_t blocks = (g.n + kEnergyBlock - 1) / kEnergyBlock;
-    const int32_t groups = run.t4 / 4;
-    hipLaunchKernelGGL(energy_partial_kernel, dim3(blocks, groups), dim3(kEnergyBlock), 0, stream,
-                       g.n, run.t4, g.row_ptr, g.col, g.val, g.h, run.spins, part);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(energy_finish_kernel, dim3(grid_for(run.trials, 256)), dim3(256), 0, stream,
-                       blocks, groups, run.trials, g.w2, part, energy, cut);
+    EnergyJob e = energy_job(g, run);
+    energy_split(&e, energy_waves(e), energy_batch_wgs(e));
+    e.part = part;
+    e.energy = energy;
+    e.cut = cut;
+    auto kern = e.quads == 1 ? (e.narrow ? energy_partial_kernel<int32_t, 1> : energy_partial_kernel<int64_t, 1>)
+                             : (e.narrow ? energy_partial_kernel<int32_t, 4> : energy_partial_kernel<int64_t, 4>);
+    const int32_t block = energy_block(e);
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(energy_batch_wgs(e))), dim3(block),
+                       energy_lds_bytes(e, block, e.narrow), stream, e);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(energy_finish_kernel, dim3(run.t4 / 4), dim3(64), 0, stream, e);
     return hipGetLastError();
 }
 
-hipError_t launch_energy_cut_batch(hipStream_t stream, const EnergyJob *jobs, int32_t count, int32_t wgs,
-                                   int32_t trials) {
-    if (count <= 0 || wgs <= 0 || trials <= 0) return hipSuccess;
-    hipLaunchKernelGGL(energy_partial_batch_kernel, dim3(wgs), dim3(kEnergyBlock), 0, stream, jobs, count);
+hipError_t launch_energy_cut_batch(hipStream_t stream, const EnergyJob *jobs, const EnergyJob *host, int32_t count,
+                                   int32_t wgs, int32_t groups) {
+    if (count <= 0 || wgs <= 0 || groups <= 0) return hipSuccess;
+    int32_t block = 64;
+    bool narrow = true;
+    for (int32_t j = 0; j < count; ++j) {
+        if (host[j].quads != host[0].quads) return hipErrorInvalidValue;
+        block = std::max(block, energy_block(host[j]));
+        narrow = narrow && host[j].narrow;
+    }
+    size_t lds = 0;
+    for (int32_t j = 0; j < count; ++j) lds = std::max(lds, energy_lds_bytes(host[j], block, narrow));
+    auto kern = host[0].quads == 1
+                    ? (narrow ? energy_partial_batch_kernel<int32_t, 1> : energy_partial_batch_kernel<int64_t, 1>)
+                    : (narrow ? energy_partial_batch_kernel<int32_t, 4> : energy_partial_batch_kernel<int64_t, 4>);
+    hipLaunchKernelGGL(kern, dim3(wgs), dim3(block), lds, stream, jobs, count);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(energy_finish_batch_kernel, dim3(grid_for(trials, 256)), dim3(256), 0, stream, jobs, count,
-                       trials);
+    hipLaunchKernelGGL(energy_finish_batch_kernel, dim3(groups), dim3(64), 0, stream, jobs, count);
     return hipGetLastError();
 }
 
 hipError_t launch_spins_to_tn(hipStream_t stream, int32_t n, const DevRun &run, int8_t *out_tn) {
-    const int block = 256;
-    hipLaunchKernelGGL(spins_to_tn_kernel,
-                       dim3(grid_for(static_cast<int64_t>(n) * run.trials, block)), dim3(block), 0,
-                       stream, n, run.t4, run.trials, run.spins, out_tn);
+    hipLaunchKernelGGL(spins_to_tn_kernel, dim3(grid_for(n, kTile), grid_for(run.trials, kTile)), dim3(256), 0, stream, n,
+                       run.t4, run.trials, run.spins, out_tn);
     return hipGetLastError();
 }
 
 hipError_t launch_spins_from_tn(hipStream_t stream, int32_t n, const DevRun &run,
                                 const int8_t *in_tn) {
-    const int block = 256;
-    hipLaunchKernelGGL(spins_from_tn_kernel,
-                       dim3(grid_for(static_cast<int64_t>(n) * run.trials, block)), dim3(block), 0,
-                       stream, n, run.t4, run.trials, in_tn, run.spins);
+    hipLaunchKernelGGL(spins_from_tn_kernel, dim3(grid_for(n, kTile), grid_for(run.trials, kTile)), dim3(256), 0, stream, n,
+                       run.t4, run.trials, in_tn, run.spins);
     return hipGetLastError();
 }
 
