@@ -147,7 +147,7 @@ bool prefer_dense(const psa_graph *g, const DevRun &run, const AnnealPlan &plan)
 }
 
 // Work list of the dense runs `idx` of `table` (one encoding): items (job,
-// 256-row group, trial tile) in chunks of up to 16 items -- consecutive row
+// group of `rows` rows, trial tile) in chunks of up to 16 items -- consecutive row
 // groups, each with its trial tiles next to each other -- each chunk given
 // whole to the least loaded of the 8 XCDs, heaviest runs first.  Workgroup b
 // of a launch runs on XCD b % 8, so slot b takes item b / 8 of that XCD's
@@ -155,7 +155,7 @@ bool prefer_dense(const psa_graph *g, const DevRun &run, const AnnealPlan &plan)
 // and the trial tiles of a row group read its couplings at about the same
 // time there.
 static void dense_work_list(const std::vector<DenseJob> &table, const std::vector<int32_t> &idx,
-                            int32_t nb, std::vector<int4> *out) {
+                            int32_t nb, int32_t rows, std::vector<int4> *out) {
     constexpr int32_t kXcd = 8, kChunk = 16;
     std::vector<int32_t> order(idx);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
@@ -166,7 +166,7 @@ static void dense_work_list(const std::vector<DenseJob> &table, const std::vecto
     std::vector<double> load(kXcd, 0.0);
     for (int32_t j : order) {
         const DenseJob &d = table[j];
-        const int32_t groups = (d.np + 255) / 256, tiles = d.tp / (16 * nb);
+        const int32_t groups = (d.np + rows - 1) / rows, tiles = d.tp / (16 * nb);
         const int32_t span = std::max(1, kChunk / tiles);  // row groups per chunk
         for (int32_t g0 = 0; g0 < groups; g0 += span) {
             const int32_t g1 = std::min(groups, g0 + span);
@@ -189,21 +189,21 @@ static void dense_work_list(const std::vector<DenseJob> &table, const std::vecto
 // use_graph false, or a single step -- launched one by one.  *graph: it ran
 // as a graph.
 static psa_status dense_sequence(psa_ctx *ctx, hipStream_t s, const DenseJob *table, const int4 *work,
-                                 int32_t nwork, int32_t nb, int32_t enc, int32_t mode, int32_t steps,
-                                 bool use_graph, bool *graph) {
+                                 int32_t nwork, int32_t nb, bool split, const DenseJob *one, int32_t enc, int32_t mode,
+                                 int32_t steps, bool use_graph, bool *graph) {
     *graph = false;
     if (!use_graph || steps < kDenseGraphMinSteps) {
-        PSA_HIP(launch_dense_steps(s, table, work, nwork, nb, enc, mode, steps), "dense step launch");
+        PSA_HIP(launch_dense_steps(s, table, work, nwork, nb, split, one, enc, mode, steps), "dense step launch");
         return PSA_OK;
     }
     auto &cache = ctx->dense_graph_cache;
     auto it = std::find_if(cache.begin(), cache.end(), [&](const DenseGraph &d) {
         return d.table == table && d.work == work && d.nwork == nwork && d.nb == nb && d.enc == enc &&
-               d.mode == mode && d.steps == steps;
+               d.mode == mode && d.steps == steps && d.split == split;
     });
     if (it == cache.end()) {
         PSA_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed), "hipStreamBeginCapture");
-        const hipError_t le = launch_dense_steps(s, table, work, nwork, nb, enc, mode, steps);
+        const hipError_t le = launch_dense_steps(s, table, work, nwork, nb, split, nullptr, enc, mode, steps);
         hipGraph_t g = nullptr;
         const hipError_t ce = hipStreamEndCapture(s, &g);
         if (le != hipSuccess || ce != hipSuccess) {
@@ -219,7 +219,7 @@ static psa_status dense_sequence(psa_ctx *ctx, hipStream_t s, const DenseJob *ta
             (void)hipGraphExecDestroy(cache.front().exec);
             cache.erase(cache.begin());
         }
-        cache.push_back(DenseGraph{table, work, nwork, nb, enc, mode, steps, exec});
+        cache.push_back(DenseGraph{table, work, nwork, nb, enc, mode, steps, split, exec});
         it = cache.end() - 1;
     } else {
         std::rotate(it, it + 1, cache.end());  // most recently used last
@@ -322,13 +322,35 @@ psa_status dense_step_jobs(psa_ctx *ctx, psa_job *const *jobs, int32_t count, in
     const int32_t how = max_steps >= kDenseGraphMinSteps ? ctx->dense_launch : kDenseLaunchSteps;
     std::vector<int4> work, part;
     size_t off[kE] = {0, 0, 0}, len[kE] = {0, 0, 0};
+    bool split[kE] = {false, false, false};
     DenseQueues queues[kE] = {};
     for (int e = 0; e < kE; ++e) {
         if (by_enc[e].empty()) continue;
         if (how == kDenseLaunchPersistent && plain[e])
             dense_task_list(table, by_enc[e], nb[e], &part, &queues[e]);
-        else
-            dense_work_list(table, by_enc[e], nb[e], &part);
+        else {
+            // fewer 256-row items than compute units: 64-row items whose waves
+            // split the columns, in the narrowest trial tiles that keep them
+            // to two per compute unit (graphs of density 0.06, us per step: 3,000
+            // p-bits x 64 trials, 24 items, 10.6 -> 5.0, with 32-trial tiles 6.2;
+            // 4,000 x 256, 128 items, 13.2 -> 9.9; 2,000 x 1,024, 256 items, 10.6
+            // either way; 4,000 x 1,024, 512 items, 17.1 against 23.5 split: each
+            // 64 rows read the trial tile's spins again)
+            int64_t items = 0;
+            for (int32_t j : by_enc[e]) items += static_cast<int64_t>((table[j].np + 255) / 256) * (table[j].tp / (16 * nb[e]));
+            split[e] = items < kDenseSplitItems;
+            if (split[e]) {
+                const int32_t most = nb[e];
+                auto fine = [&](int32_t b) {
+                    int64_t n64 = 0;
+                    for (int32_t j : by_enc[e]) n64 += static_cast<int64_t>(table[j].np / 64) * (table[j].tp / (16 * b));
+                    return n64;
+                };
+                nb[e] = 1;
+                while (nb[e] < most && fine(nb[e]) > 2 * kDenseSplitItems) nb[e] *= 2;
+            }
+            dense_work_list(table, by_enc[e], nb[e], split[e] ? 64 : 256, &part);
+        }
         off[e] = work.size();
         len[e] = part.size();
         work.insert(work.end(), part.begin(), part.end());
@@ -414,7 +436,8 @@ psa_status dense_step_jobs(psa_ctx *ctx, psa_job *const *jobs, int32_t count, in
         bool graph = false;
         hipStream_t s = side && !first ? ctx->stream3 : ctx->stream2;
         first = false;
-        if ((st = dense_sequence(ctx, s, dtable, dwork + off[e], static_cast<int32_t>(len[e]), nb[e], enc, mode,
+        if ((st = dense_sequence(ctx, s, dtable, dwork + off[e], static_cast<int32_t>(len[e]), nb[e], split[e],
+                                 split[e] && by_enc[e].size() == 1 ? &table[static_cast<size_t>(by_enc[e][0])] : nullptr, enc, mode,
                                  max_steps, how == kDenseLaunchGraph, &graph)) != PSA_OK)
             return st;
         launches += max_steps;

@@ -71,6 +71,7 @@
 #include <type_traits>
 
 #include "device_math.hpp"
+#include "ell_sweep.hpp"
 #include "engine.hpp"
 
 namespace psa {
@@ -157,6 +158,216 @@ enum : int { kDenseAny = 0, kDensePlain = 1, kDenseIdentity = 2 };
 // cache write-back or invalidation between dependent steps.
 constexpr int kCohAux = 16;                  // cache policy bits: device scope
 constexpr int kRsrcWord3 = 0x00020000;       // raw buffer resource, gfx9 family
+
+// The p-bit updates of R 16-row blocks x NB 16-trial blocks whose neighbour
+// sums a wavefront holds: lane owns p-bits 4m..4m+3 of each row block
+// (rows row0 + 16 rb + 4 (lane / 16)) for trial columns trial0 + 16 nb + lane %
+// 16.  The sum of a p-bit is exact in either accumulator type, and so is its
+// conversion: L = h + scale * sum as an integer, or (float)L by one fma (scale
+// * sum and the total are integers below 2^24).  cur / nxt: the buffers of the
+// step's parity (rcur / rnxt: the same as buffer resources, COH).
+//
+// A random block's parts that depend only on step, trial and purpose are
+// formed once per trial block (block_prefix) and shared by its R row blocks.
+// Each decision is the sign of decision_distance (ell_sweep.hpp); when some
+// lane of the wave holds a distance within kCloseD of 0 the four are taken
+// from the exact recipe -- one uniform branch per block of four.
+template <int R, int NB, int ENC, int MODE, bool COH>
+__device__ __forceinline__ void dense_epilogue(const DenseJob &jb, const typename Enc<ENC>::Acc (&acc)[R][NB],
+                                               int32_t row0, int32_t trial0, uint32_t tau, int32_t t, float i0t,
+                                               const int8_t *cur, int8_t *nxt, __amdgpu_buffer_rsrc_t rcur,
+                                               __amdgpu_buffer_rsrc_t rnxt) {
+    using E = Enc<ENC>;
+    using Acc = typename E::Acc;
+    constexpr bool kFp4 = ENC != kDenseI8;
+    constexpr bool PLAIN = MODE != kDenseAny;
+    const bool period_mode = !PLAIN && jb.t_res > 0;
+    const int32_t rowb = jb.np * E::kBits / 8;
+    const int lane = threadIdx.x & 63;
+    const int lr = lane & 15;
+    // the spins of p-bits i0..i0+3 of trial k in a buffer, 32 or 16 bits
+    auto spin_off = [&](uint32_t k, int32_t i0) {
+        return static_cast<int32_t>(k) * rowb + (i0 * E::kBits >> 3);
+    };
+    auto store4 = [&](uint32_t k, int32_t i0, uint32_t out) {
+        const int32_t off = spin_off(k, i0);
+        if constexpr (COH && kFp4)
+            __builtin_amdgcn_raw_buffer_store_b16(static_cast<uint16_t>(out), rnxt, off, 0, kCohAux);
+        else if constexpr (COH)
+            __builtin_amdgcn_raw_buffer_store_b32(out, rnxt, off, 0, kCohAux);
+        else if constexpr (kFp4)
+            *reinterpret_cast<uint16_t *>(nxt + off) = static_cast<uint16_t>(out);
+        else
+            *reinterpret_cast<uint32_t *>(nxt + off) = out;
+    };
+    auto load4 = [&](uint32_t k, int32_t i0) -> uint32_t {
+        const int32_t off = spin_off(k, i0);
+        if constexpr (COH && kFp4)
+            return __builtin_amdgcn_raw_buffer_load_b16(rcur, off, 0, kCohAux);
+        else if constexpr (COH)
+            return __builtin_amdgcn_raw_buffer_load_b32(rcur, off, 0, kCohAux);
+        else if constexpr (kFp4)
+            return *reinterpret_cast<const uint16_t *>(cur + off);
+        else
+            return *reinterpret_cast<const uint32_t *>(cur + off);
+    };
+    const float scalef = static_cast<float>(jb.scale);
+    const RoundKeys keys = round_keys(jb.k0, jb.k1);
+    // codes of four up spins, and the bits that turn a code into down
+    constexpr uint32_t kUp4 = kFp4 ? 0x2222u : 0x01010101u;
+    constexpr uint32_t kFlip = kFp4 ? 0x8u : 0xFEu;
+    if constexpr (MODE == kDenseIdentity) {
+        // one r block and four products per (row block, trial block) pair.
+        // Padding p-bits and trials are written too (their rows and columns of
+        // J are zero, and the read-out skips them).
+        const gptr<v4i> hvec = as_global<v4i>(jb.h);
+        const float vt = i0t * kTwoLog2e;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const uint32_t k = static_cast<uint32_t>(trial0 + nb * 16 + lr);
+            const BlockPrefix pr = block_prefix(tau, k, kTagR, jb.k0, jb.k1);
+#pragma unroll
+            for (int rb = 0; rb < R; ++rb) {
+                const int32_t i0 = row0 + rb * 16 + (lane >> 4) * 4;
+                const v4i hh = hvec[(i0 < jb.n4 ? i0 : 0) >> 2];
+                const Words4 r = block_of_task(static_cast<uint32_t>(i0 >> 2), pr, keys);
+                const int32_t hv[4] = {hh[0], hh[1], hh[2], hh[3]};
+                const uint32_t rw[4] = {r.x, r.y, r.z, r.w};
+                float Lf[4], d[4];
+                bool close = false;
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    if constexpr (kFp4)
+                        Lf[p] = fmaf(scalef, acc[rb][nb][p], static_cast<float>(hv[p]));
+                    else
+                        Lf[p] = static_cast<float>(hv[p] + jb.scale * acc[rb][nb][p]);
+                    d[p] = decision_distance(vt * Lf[p], rw[p]);
+                    close = close || !(fabsf(d[p]) > kCloseD);
+                }
+                if (__ballot(close) != 0u) {
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) d[p] = tanh_f32(i0t * Lf[p]) > r_of(rw[p]) ? -1.0f : 1.0f;
+                }
+                uint32_t out = kUp4;
+#pragma unroll
+                for (int p = 0; p < 4; ++p)  // a negative distance is up
+                    out ^= ~sign_mask(__float_as_uint(d[p])) & (kFlip << (E::kBits * p));
+                store4(k, i0, out);
+                if (rb & 1) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        return;
+    }
+    // the other modes: the (row block, trial block) pairs run as a loop with a
+    // uniform index, so the body -- Philox blocks and four activations -- is
+    // emitted once per pass, keeping few registers live.
+    const int32_t scale = jb.scale;
+    const InputState st{jb.xs, jb.stall24, jb.ring, jb.alpha, jb.n4};
+    auto update = [&](int e, const Acc a4) __attribute__((always_inline)) {
+        const int nb = e / R, rb = e % R;
+        const int32_t i0 = row0 + rb * 16 + (lane >> 4) * 4;
+        const int32_t k = trial0 + nb * 16 + lr;
+        // lanes past the padded p-bits or trials compute on clamped inputs
+        // and store nothing (straight-line code, so that two passes interleave)
+        const bool valid = i0 < jb.n4 && k < jb.t4;
+        const int32_t ic = valid ? i0 : 0;
+        const int32_t m = i0 >> 2;
+        const int4 hh = *reinterpret_cast<const int4 *>(jb.h + ic);
+        const uint4 th = *reinterpret_cast<const uint4 *>(jb.thr + ic);
+        const float4 lm = *reinterpret_cast<const float4 *>(jb.lam + ic);
+        const float4 dl = *reinterpret_cast<const float4 *>(jb.dlt + ic);
+        const InputState sv{valid ? st.xs : nullptr, st.s24, valid ? st.ring : nullptr, st.alpha, st.n4};
+        const int32_t hv[4] = {hh.x, hh.y, hh.z, hh.w};
+        const uint32_t tv[4] = {th.x, th.y, th.z, th.w};
+        const float av[4] = {i0t * lm.x, i0t * lm.y, i0t * lm.z, i0t * lm.w};
+        const float dv[4] = {dl.x, dl.y, dl.z, dl.w};
+        const bool need_gate = !period_mode && ((tv[0] < kGateOne) | (tv[1] < kGateOne) |
+                                                (tv[2] < kGateOne) | (tv[3] < kGateOne));
+        const uint32_t mk = static_cast<uint32_t>(m), kk = static_cast<uint32_t>(k);
+        uint32_t old = 0u;
+        uint32_t gw[4] = {0u, 0u, 0u, 0u};
+        if (need_gate || period_mode)  // p-bits that do not fire keep these
+            old = load4(static_cast<uint32_t>(k), i0);
+        if (need_gate) {
+            const Words4 g = block_of_task(mk, block_prefix(tau, kk, kTagGate, jb.k0, jb.k1), keys);
+            gw[0] = g.x;
+            gw[1] = g.y;
+            gw[2] = g.z;
+            gw[3] = g.w;
+        }
+        const Words4 r = block_of_task(mk, block_prefix(tau, kk, kTagR, jb.k0, jb.k1), keys);
+        const uint32_t rw[4] = {r.x, r.y, r.z, r.w};
+        uint32_t sw[4] = {0u, 0u, 0u, 0u};
+        if (!PLAIN && sv.xs != nullptr && t > 0) {
+            const Words4 b = philox4x32_10(static_cast<uint32_t>(t), static_cast<uint32_t>(m),
+                                           static_cast<uint32_t>(k), kTagStall, jb.k0, jb.k1);
+            sw[0] = b.x;
+            sw[1] = b.y;
+            sw[2] = b.z;
+            sw[3] = b.w;
+        }
+        constexpr uint32_t kMask = (1u << E::kBits) - 1u;
+        float x[4], d[4];
+        bool close = false;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const int32_t L = hv[p] + scale * static_cast<int32_t>(a4[p]);
+            x[p] = PLAIN ? input_of<kAlgPsa>(av[p], dv[p], L, sv, i0 + p, kk, static_cast<uint32_t>(t), sw[p])
+                         : input_any(av[p], dv[p], L, sv, i0 + p, kk, static_cast<uint32_t>(t), sw[p]);
+            d[p] = decision_distance(x[p] * kTwoLog2e, rw[p]);
+            close = close || !(fabsf(d[p]) > kCloseD);
+        }
+        if (__ballot(close) != 0u) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) d[p] = tanh_f32(x[p]) > r_of(rw[p]) ? -1.0f : 1.0f;
+        }
+        uint32_t out = 0u;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const bool fire = period_mode ? period_fires(tau, tv[p]) : fires(gw[p], tv[p]);
+            const uint32_t ob = (old >> (E::kBits * p)) & kMask;
+            out |= (fire ? (d[p] < 0.0f ? E::kUp : E::kDown) : ob) << (E::kBits * p);
+        }
+        if (valid) store4(static_cast<uint32_t>(k), i0, out);
+    };
+    // The accumulators move through a queue read only at its head (constant
+    // register indices; a loop index into the array would force it into
+    // scratch memory).  Two (row block, trial block) pairs per pass: their
+    // Philox chains are independent, which doubles the instruction-level
+    // parallelism.
+    Acc q[R * NB];
+#pragma unroll
+    for (int e = 0; e < R * NB; ++e) q[e] = acc[e % R][e / R];
+    if constexpr (R * NB == 1) {
+        update(0, q[0]);
+    } else {
+#pragma unroll 1
+        for (int e = 0; e < R * NB; e += 2) {
+            update(e, q[0]);
+            update(e + 1, q[1]);
+#pragma unroll
+            for (int j = 0; j + 2 < R * NB; ++j) q[j] = q[j + 2];
+        }
+    }
+}
+
+// One matrix instruction: k-step kt of a chunk, row block rb, one trial block.
+template <int ENC>
+__device__ __forceinline__ typename Enc<ENC>::Acc dense_mfma(const AFrag<ENC> &f, int kt, int rb, const v4i b,
+                                                             const typename Enc<ENC>::Acc c) {
+    if constexpr (ENC == kDenseI8) {
+        return __builtin_amdgcn_mfma_i32_16x16x64_i8(f.v[kt][rb], b, c, 0, 0, 0);
+    } else {
+        v8i a;
+        if constexpr (ENC == kDenseT2) {
+            const v4i &qw = f.q[kt * 2 + (rb >> 1)];
+            a = f4_operand(static_cast<uint32_t>(qw[(rb & 1) * 2]), static_cast<uint32_t>(qw[(rb & 1) * 2 + 1]));
+        } else {
+            a = b1_operand(static_cast<uint32_t>(f.h[kt][rb]));
+        }
+        return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, f4_widen(b), c, 4, 4, 0, 0, 0, 0);  // fp4 x fp4, no scaling
+    }
+}
 
 // One work item of one step: w = (job, row group, trial tile, -), job < 0 an
 // empty slot; bt the workgroup's two LDS spin chunks.  Every thread of the
@@ -269,24 +480,8 @@ __device__ __forceinline__ void dense_task(const DenseJob *__restrict__ jobs, co
                 b[nb] = *reinterpret_cast<const v4i *>(&bt[buf][(nb * 16 + lr) * kLdsStride + kt * 64 + kgrp]);
 #pragma unroll
             for (int rb = 0; rb < 4; ++rb) {
-                if constexpr (ENC == kDenseI8) {
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[rb][nb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af.v[kt][rb], b[nb], acc[rb][nb], 0, 0, 0);
-                } else {
-                    v8i a;
-                    if constexpr (ENC == kDenseT2) {
-                        const v4i &qw = af.q[kt * 2 + (rb >> 1)];
-                        a = f4_operand(static_cast<uint32_t>(qw[(rb & 1) * 2]),
-                                       static_cast<uint32_t>(qw[(rb & 1) * 2 + 1]));
-                    } else {
-                        a = b1_operand(static_cast<uint32_t>(af.h[kt][rb]));
-                    }
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[rb][nb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                            a, f4_widen(b[nb]), acc[rb][nb], 4, 4, 0, 0, 0, 0);  // fp4 x fp4, no scaling
-                }
+                for (int nb = 0; nb < NB; ++nb) acc[rb][nb] = dense_mfma<ENC>(af, kt, rb, b[nb], acc[rb][nb]);
             }
         }
     };
@@ -317,174 +512,7 @@ __device__ __forceinline__ void dense_task(const DenseJob *__restrict__ jobs, co
     }
     if (!active) return;
 
-    // epilogue: lane owns p-bits 4m..4m+3 of each row block for trial columns
-    // nb.  The sum of a p-bit is exact in either accumulator type, and so is
-    // its conversion: L = h + scale * sum as an integer, or (float)L by one
-    // fma (scale * sum and the total are integers below 2^24).
-    const float i0t = jb.i0[t];
-    // the spins of p-bits i0..i0+3 of trial k in a buffer, 32 or 16 bits
-    auto spin_off = [&](uint32_t k, int32_t i0) {
-        return static_cast<int32_t>(k) * rowb + (i0 * E::kBits >> 3);
-    };
-    auto store4 = [&](uint32_t k, int32_t i0, uint32_t out) {
-        const int32_t off = spin_off(k, i0);
-        if constexpr (COH && kFp4)
-            __builtin_amdgcn_raw_buffer_store_b16(static_cast<uint16_t>(out), rnxt, off, 0, kCohAux);
-        else if constexpr (COH)
-            __builtin_amdgcn_raw_buffer_store_b32(out, rnxt, off, 0, kCohAux);
-        else if constexpr (kFp4)
-            *reinterpret_cast<uint16_t *>(nxt + off) = static_cast<uint16_t>(out);
-        else
-            *reinterpret_cast<uint32_t *>(nxt + off) = out;
-    };
-    auto load4 = [&](uint32_t k, int32_t i0) -> uint32_t {
-        const int32_t off = spin_off(k, i0);
-        if constexpr (COH && kFp4)
-            return __builtin_amdgcn_raw_buffer_load_b16(rcur, off, 0, kCohAux);
-        else if constexpr (COH)
-            return __builtin_amdgcn_raw_buffer_load_b32(rcur, off, 0, kCohAux);
-        else if constexpr (kFp4)
-            return *reinterpret_cast<const uint16_t *>(cur + off);
-        else
-            return *reinterpret_cast<const uint32_t *>(cur + off);
-    };
-    if constexpr (MODE == kDenseIdentity) {
-        // one r block and four products per (row block, trial block) pair; the
-        // pairs unrolled with constant accumulator indices, two per scheduling
-        // region (their chains are independent), the key schedule formed once.
-        // Each decision is taken from the tanh estimate, its spin code from
-        // the sign of the estimate's distance to r; when some lane of the wave
-        // holds an estimate within 2^-16 of r (about one pair in 250), the
-        // pair's codes are taken from the exact recipe instead -- one uniform
-        // branch per pair, none per p-bit.  Padding p-bits and trials are
-        // written too (their rows and columns of J are zero, and the read-out
-        // skips them).
-        const int32_t scale = jb.scale;
-        const float scalef = static_cast<float>(scale);
-        const uint32_t kpos = static_cast<uint32_t>(trial0 + lr);
-        const PhiloxKeys keys = philox_keys(jb.k0, jb.k1);
-        const gptr<v4i> hvec = as_global<v4i>(jb.h);
-        // codes of four up spins, and the bits that turn a code into down
-        constexpr uint32_t kUp4 = kFp4 ? 0x2222u : 0x01010101u;
-        constexpr uint32_t kFlip = kFp4 ? 0x8u : 0xFEu;
-#pragma unroll
-        for (int e = 0; e < 4 * NB; ++e) {
-            const int rb = e / NB, nb = e % NB;
-            const int32_t i0 = wrow0 + rb * 16 + (lane >> 4) * 4;
-            const uint32_t k = kpos + static_cast<uint32_t>(nb * 16);
-            const v4i hh = hvec[(i0 < jb.n4 ? i0 : 0) >> 2];
-            const Words4 r = philox4x32_10(tau, static_cast<uint32_t>(i0 >> 2), k, kTagR, keys);
-            const int32_t hv[4] = {hh[0], hh[1], hh[2], hh[3]};
-            const uint32_t rw[4] = {r.x, r.y, r.z, r.w};
-            float x[4];
-            uint32_t out = kUp4;
-            bool close = false;
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                float Lf;
-                if constexpr (kFp4)
-                    Lf = fmaf(scalef, acc[rb][nb][p], static_cast<float>(hv[p]));
-                else
-                    Lf = static_cast<float>(hv[p] + scale * acc[rb][nb][p]);
-                x[p] = i0t * Lf;
-                const float diff = tanh_estimate_minus(x[p], r_of(rw[p]));
-                close = close || !estimate_decides(diff);
-                // diff < 0 (sign bit set): down
-                const uint32_t neg = static_cast<uint32_t>(static_cast<int32_t>(__float_as_uint(diff)) >> 31);
-                out ^= (neg & kFlip) << (E::kBits * p);
-            }
-            if (__ballot(close) != 0u) {
-                out = 0u;
-#pragma unroll
-                for (int p = 0; p < 4; ++p)
-                    out |= (tanh_f32(x[p]) > r_of(rw[p]) ? E::kUp : E::kDown) << (E::kBits * p);
-            }
-            store4(k, i0, out);
-            if (e & 1) __builtin_amdgcn_sched_barrier(0);
-        }
-        return;
-    }
-    // the other modes: the (row block, trial block) pairs run as a loop with a
-    // uniform index, so the body -- Philox blocks and four activations -- is
-    // emitted once per pass, keeping few registers live.
-    const int32_t scale = jb.scale;
-    const InputState st{jb.xs, jb.stall24, jb.ring, jb.alpha, jb.n4};
-    auto update = [&](int e, const Acc a4) __attribute__((always_inline)) {
-        const int rb = e / NB, nb = e % NB;
-        const int32_t i0 = wrow0 + rb * 16 + (lane >> 4) * 4;
-        const int32_t k = trial0 + nb * 16 + lr;
-        // lanes past the padded p-bits or trials compute on clamped inputs
-        // and store nothing (straight-line code, so that two passes interleave)
-        const bool valid = i0 < jb.n4 && k < jb.t4;
-        const int32_t ic = valid ? i0 : 0;
-        const int32_t m = i0 >> 2;
-        const int4 hh = *reinterpret_cast<const int4 *>(jb.h + ic);
-        const uint4 th = *reinterpret_cast<const uint4 *>(jb.thr + ic);
-        const float4 lm = *reinterpret_cast<const float4 *>(jb.lam + ic);
-        const float4 dl = *reinterpret_cast<const float4 *>(jb.dlt + ic);
-        const InputState sv{valid ? st.xs : nullptr, st.s24, valid ? st.ring : nullptr, st.alpha, st.n4};
-        const int32_t hv[4] = {hh.x, hh.y, hh.z, hh.w};
-        const uint32_t tv[4] = {th.x, th.y, th.z, th.w};
-        const float av[4] = {i0t * lm.x, i0t * lm.y, i0t * lm.z, i0t * lm.w};
-        const float dv[4] = {dl.x, dl.y, dl.z, dl.w};
-        const bool need_gate = !period_mode && ((tv[0] < kGateOne) | (tv[1] < kGateOne) |
-                                                (tv[2] < kGateOne) | (tv[3] < kGateOne));
-        uint32_t old = 0u;
-        uint32_t gw[4] = {0u, 0u, 0u, 0u};
-        if (need_gate || period_mode)  // p-bits that do not fire keep these
-            old = load4(static_cast<uint32_t>(k), i0);
-        if (need_gate) {
-            const Words4 g = philox4x32_10(tau, static_cast<uint32_t>(m),
-                                           static_cast<uint32_t>(k), kTagGate, jb.k0, jb.k1);
-            gw[0] = g.x;
-            gw[1] = g.y;
-            gw[2] = g.z;
-            gw[3] = g.w;
-        }
-        const Words4 r = philox4x32_10(tau, static_cast<uint32_t>(m),
-                                       static_cast<uint32_t>(k), kTagR, jb.k0, jb.k1);
-        const uint32_t rw[4] = {r.x, r.y, r.z, r.w};
-        uint32_t sw[4] = {0u, 0u, 0u, 0u};
-        if (!PLAIN && sv.xs != nullptr && t > 0) {
-            const Words4 b = philox4x32_10(static_cast<uint32_t>(t), static_cast<uint32_t>(m),
-                                           static_cast<uint32_t>(k), kTagStall, jb.k0, jb.k1);
-            sw[0] = b.x;
-            sw[1] = b.y;
-            sw[2] = b.z;
-            sw[3] = b.w;
-        }
-        constexpr uint32_t kMask = (1u << E::kBits) - 1u;
-        uint32_t out = 0u;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const int32_t L = hv[p] + scale * static_cast<int32_t>(a4[p]);
-            const float x = PLAIN ? input_of<kAlgPsa>(av[p], dv[p], L, sv, i0 + p, static_cast<uint32_t>(k),
-                                                      static_cast<uint32_t>(t), sw[p])
-                                  : input_any(av[p], dv[p], L, sv, i0 + p, static_cast<uint32_t>(k),
-                                      static_cast<uint32_t>(t), sw[p]);
-            const bool up = pbit_up(x, rw[p]);
-            const bool fire = period_mode ? period_fires(tau, tv[p])
-                                          : (tv[p] >= kGateOne || fires(gw[p], tv[p]));
-            const uint32_t ob = (old >> (E::kBits * p)) & kMask;
-            out |= (fire ? (up ? E::kUp : E::kDown) : ob) << (E::kBits * p);
-        }
-        if (valid) store4(static_cast<uint32_t>(k), i0, out);
-    };
-    // The accumulators move through a queue read only at its head (constant
-    // register indices; a loop index into the array would force it into
-    // scratch memory).  Two (row block, trial block) pairs per pass: their
-    // Philox chains are independent, which doubles the instruction-level
-    // parallelism.
-    Acc q[4 * NB];
-#pragma unroll
-    for (int e = 0; e < 4 * NB; ++e) q[e] = acc[e / NB][e % NB];
-#pragma unroll 1
-    for (int e = 0; e < 4 * NB; e += 2) {
-        update(e, q[0]);
-        update(e + 1, q[1]);
-#pragma unroll
-        for (int j = 0; j + 2 < 4 * NB; ++j) q[j] = q[j + 2];
-    }
+    dense_epilogue<4, NB, ENC, MODE, COH>(jb, acc, wrow0, trial0, tau, t, jb.i0[t], cur, nxt, rcur, rnxt);
 }
 
 template <int NB, int ENC, int MODE>
@@ -492,6 +520,121 @@ __global__ __launch_bounds__(256, ENC != kDenseI8 ? 3 : 2) void dense_step_kerne
                                                          const int4 *__restrict__ work, int32_t t_off) {
     __shared__ __align__(16) int8_t bt[2][16 * NB * kLdsStride];
     dense_task<NB, ENC, MODE, false>(jobs, work[blockIdx.x], t_off, bt);
+}
+
+// The same step with 64-row work items, for lists of few items: the four waves
+// split the columns (wave v takes chunks v, v + 4, ...), each with its own
+// coupling and spin loads straight from memory, and add their sums through LDS;
+// then wave v updates row block v.  A 256-row item streams its chunks one
+// after the other, about 0.7 us of latency each, and 3,000 p-bits x 64 trials
+// are only 24 of them: 9.6 us per launch; as 188 items of 16 trials and three
+// chunks a wave, 4.9 us (an empty launch takes 1.6).  The price is that every item reads its trial tile's spins: 64 rows
+// share them instead of 256.
+// A list of one run (dense_split_one_kernel) takes the run as its argument and
+// its items from the workgroup index (trial tiles of a row tile next to each
+// other on one XCD), which saves two dependent loads of a launch.
+template <int NB, int ENC, int MODE>
+__device__ __forceinline__ void dense_split(const DenseJob &jb, const int4 w, int32_t t_off) {
+    using E = Enc<ENC>;
+    using Acc = typename E::Acc;
+    __shared__ __align__(16) Acc red[4][4][NB][64];
+    const int32_t u = MODE == kDenseAny && jb.t_res > 0 ? jb.t_res : 1;
+    if (t_off >= (jb.t_end - jb.t) * u) return;
+    const uint32_t tau = static_cast<uint32_t>(jb.t * u + t_off);
+    const int32_t t = static_cast<int32_t>(tau / static_cast<uint32_t>(u));
+    const int32_t np = jb.np, rowb = np * E::kBits / 8, nkc = np / E::kCols;
+    const int32_t row0 = w.y * kWaveRows, trial0 = w.z * 16 * NB;
+    const int8_t *__restrict__ cur = (t_off & 1) ? jb.m1 : jb.m0;
+    int8_t *__restrict__ nxt = (t_off & 1) ? jb.m0 : jb.m1;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int lr = lane & 15, kgrp = (lane >> 4) * 16;
+    const gptr<int8_t> gcur = as_global<int8_t>(cur) + static_cast<size_t>(trial0 + lr) * rowb + kgrp;
+    const float i0t = load_uniform(jb.i0 + t);  // before the loads it would wait behind
+    struct Frag {
+        AFrag<ENC> a;
+        v4i b[2][NB];
+    };
+    auto fetch = [&](int kc, Frag &f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                f.b[kt][nb] = *as_global<v4i>(gcur + static_cast<size_t>(nb) * 16 * rowb + kc * kChunkBytes + kt * 64);
+        if constexpr (ENC == kDenseI8) {
+            const gptr<int8_t> J = as_global<int8_t>(jb.J);
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int rb = 0; rb < 4; ++rb)
+                    f.a.v[kt][rb] = *as_global<v4i>(J + static_cast<size_t>(row0 + rb * 16 + lr) * np + kc * E::kCols +
+                                                    kt * 64 + kgrp);
+        } else if constexpr (ENC == kDenseT2) {
+            const gptr<v4i> J = as_global<v4i>(jb.J) + (static_cast<size_t>(w.y) * nkc + kc) * 4 * 64;
+#pragma unroll
+            for (int qq = 0; qq < 4; ++qq) f.a.q[qq] = J[qq * 64 + lane];
+        } else {
+            const gptr<v4i> J = as_global<v4i>(jb.J) + (static_cast<size_t>(w.y) * nkc + kc) * 2 * 64;
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) f.a.h[hh] = J[hh * 64 + lane];
+        }
+    };
+    Acc acc[4][NB];
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[rb][nb] = Acc{0, 0, 0, 0};
+    auto compute = [&](const Frag &f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int rb = 0; rb < 4; ++rb) {
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) acc[rb][nb] = dense_mfma<ENC>(f.a, kt, rb, f.b[kt][nb], acc[rb][nb]);
+            }
+    };
+    Frag f0, f1;
+    if (wave < nkc) fetch(wave, f0);
+    for (int kc = wave; kc < nkc; kc += 8) {
+        // the next chunk in flight while this one is multiplied
+        const bool two = kc + 4 < nkc;
+        if (two) fetch(kc + 4, f1);
+        compute(f0);
+        if (kc + 8 < nkc) fetch(kc + 8, f0);
+        if (two) compute(f1);
+    }
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) red[wave][rb][nb][lane] = acc[rb][nb];
+    __syncthreads();
+    Acc sum[1][NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+        sum[0][nb] = (red[0][wave][nb][lane] + red[1][wave][nb][lane]) + (red[2][wave][nb][lane] + red[3][wave][nb][lane]);
+    const int32_t buf_bytes = jb.tp * rowb;
+    const __amdgpu_buffer_rsrc_t rcur =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(cur), 0, buf_bytes, kRsrcWord3);
+    const __amdgpu_buffer_rsrc_t rnxt = __builtin_amdgcn_make_buffer_rsrc(nxt, 0, buf_bytes, kRsrcWord3);
+    dense_epilogue<1, NB, ENC, MODE, false>(jb, sum, row0 + wave * 16, trial0, tau, t, i0t, cur, nxt, rcur, rnxt);
+}
+
+template <int NB, int ENC, int MODE>
+__global__ __launch_bounds__(256, 2) void dense_split_kernel(const DenseJob *__restrict__ jobs,
+                                                             const int4 *__restrict__ work, int32_t t_off) {
+    const int4 w = work[blockIdx.x];
+    if (w.x < 0) return;
+    dense_split<NB, ENC, MODE>(jobs[w.x], w, t_off);
+}
+template <int NB, int ENC, int MODE>
+__global__ __launch_bounds__(256, 2) void dense_split_one_kernel(DenseJob job, int32_t tiles, int32_t items,
+                                                                 int32_t t_off) {
+    // slot s of XCD x = blockIdx % 8: items x per, x per + 1, ..
+    const int32_t per = (items + 7) / 8;
+    const int32_t slot = static_cast<int32_t>(blockIdx.x) / 8;
+    const int32_t item = static_cast<int32_t>(blockIdx.x) % 8 * per + slot;
+    if (slot >= per || item >= items) return;
+    dense_split<NB, ENC, MODE>(job, make_int4(0, item / tiles, item % tiles, 0), t_off);
 }
 
 // All `steps` steps of a work list in one launch.  The work list is split
@@ -635,25 +778,38 @@ __global__ void from_dense_f4_kernel(int32_t n, int32_t t4, int32_t np, const ui
     spins[idx] = nib == 0x2u ? int8_t(1) : int8_t(-1);
 }
 
+template <int NB, int ENC, int MODE>
+hipError_t launch_dense_tile(hipStream_t stream, const DenseJob *jobs, const int4 *work, int32_t nwork, bool split,
+                             const DenseJob *one, int32_t s) {
+    if (one) {
+        const int32_t tiles = one->tp / (16 * NB), items = one->np / kWaveRows * tiles;
+        hipLaunchKernelGGL((dense_split_one_kernel<NB, ENC, MODE>), dim3((items + 7) / 8 * 8), dim3(256), 0, stream, *one,
+                           tiles, items, s);
+    } else if (split)
+        hipLaunchKernelGGL((dense_split_kernel<NB, ENC, MODE>), dim3(nwork), dim3(256), 0, stream, jobs, work, s);
+    else
+        hipLaunchKernelGGL((dense_step_kernel<NB, ENC, MODE>), dim3(nwork), dim3(256), 0, stream, jobs, work, s);
+    return hipGetLastError();
+}
+
 template <int ENC, int MODE>
 hipError_t launch_dense_enc(hipStream_t stream, const DenseJob *jobs, const int4 *work, int32_t nwork,
-                            int32_t nb, int32_t s) {
+                            int32_t nb, bool split, const DenseJob *one, int32_t s) {
     switch (nb) {
-        case 1: hipLaunchKernelGGL((dense_step_kernel<1, ENC, MODE>), dim3(nwork), dim3(256), 0, stream, jobs, work, s); break;
-        case 2: hipLaunchKernelGGL((dense_step_kernel<2, ENC, MODE>), dim3(nwork), dim3(256), 0, stream, jobs, work, s); break;
-        case 4: hipLaunchKernelGGL((dense_step_kernel<4, ENC, MODE>), dim3(nwork), dim3(256), 0, stream, jobs, work, s); break;
+        case 1: return launch_dense_tile<1, ENC, MODE>(stream, jobs, work, nwork, split, one, s);
+        case 2: return launch_dense_tile<2, ENC, MODE>(stream, jobs, work, nwork, split, one, s);
+        case 4: return launch_dense_tile<4, ENC, MODE>(stream, jobs, work, nwork, split, one, s);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 template <int ENC>
 hipError_t launch_dense_mode(hipStream_t stream, const DenseJob *jobs, const int4 *work, int32_t nwork,
-                             int32_t nb, int32_t mode, int32_t s) {
+                             int32_t nb, bool split, const DenseJob *one, int32_t mode, int32_t s) {
     switch (mode) {
-        case kDenseAny: return launch_dense_enc<ENC, kDenseAny>(stream, jobs, work, nwork, nb, s);
-        case kDensePlain: return launch_dense_enc<ENC, kDensePlain>(stream, jobs, work, nwork, nb, s);
-        case kDenseIdentity: return launch_dense_enc<ENC, kDenseIdentity>(stream, jobs, work, nwork, nb, s);
+        case kDenseAny: return launch_dense_enc<ENC, kDenseAny>(stream, jobs, work, nwork, nb, split, one, s);
+        case kDensePlain: return launch_dense_enc<ENC, kDensePlain>(stream, jobs, work, nwork, nb, split, one, s);
+        case kDenseIdentity: return launch_dense_enc<ENC, kDenseIdentity>(stream, jobs, work, nwork, nb, split, one, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -661,12 +817,13 @@ hipError_t launch_dense_mode(hipStream_t stream, const DenseJob *jobs, const int
 }  // namespace
 
 hipError_t launch_dense_steps(hipStream_t stream, const DenseJob *jobs, const int4 *work,
-                              int32_t nwork, int32_t nb, int32_t enc, int32_t mode, int32_t steps) {
+                              int32_t nwork, int32_t nb, bool split, const DenseJob *one, int32_t enc, int32_t mode,
+                              int32_t steps) {
     if (nwork <= 0) return hipSuccess;
     for (int32_t s = 0; s < steps; ++s) {
-        const hipError_t e = enc == kDenseB1   ? launch_dense_mode<kDenseB1>(stream, jobs, work, nwork, nb, mode, s)
-                             : enc == kDenseT2 ? launch_dense_mode<kDenseT2>(stream, jobs, work, nwork, nb, mode, s)
-                                               : launch_dense_mode<kDenseI8>(stream, jobs, work, nwork, nb, mode, s);
+        const hipError_t e = enc == kDenseB1   ? launch_dense_mode<kDenseB1>(stream, jobs, work, nwork, nb, split, one, mode, s)
+                             : enc == kDenseT2 ? launch_dense_mode<kDenseT2>(stream, jobs, work, nwork, nb, split, one, mode, s)
+                                               : launch_dense_mode<kDenseI8>(stream, jobs, work, nwork, nb, split, one, mode, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -314,20 +314,25 @@ struct DenseGraph {
     const DenseJob *table;
     const int4 *work;
     int32_t nwork, nb, enc, mode, steps;
+    bool split;
     hipGraphExec_t exec;
 };
 constexpr size_t kDenseGraphCache = 8;    // graphs kept per context
 constexpr int32_t kDenseGraphMinSteps = 2;
 
 // Dense path launchers (dense.hip).  launch_dense_steps issues `steps`
-// launches; launch s advances every run of the work list (job, 256-row group,
-// trial tile of 16 nb; job -1 = empty slot) by its step t + s.  All runs of
+// launches; launch s advances every run of the work list (job, 256-row group --
+// 64-row with `split` --, trial tile of 16 nb; job -1 = empty slot) by its
+// step t + s.  one (with split): the list's only run, launched from a copy
+// instead of the table (not for launches that are captured and replayed).  All runs of
 // one work list share the encoding `enc`; `mode` 1 (plain) may be set only
 // when every run of the list is pSA without held inputs, windows or periods,
 // 2 (identity) only when besides every p-bit has lambda = 1, delta = 0 and
 // thr24 >= 2^24 (no timing gate); 0 tests each run's mode at run time.
 hipError_t launch_dense_steps(hipStream_t stream, const DenseJob *jobs, const int4 *work,
-                              int32_t nwork, int32_t nb, int32_t enc, int32_t mode, int32_t steps);
+                              int32_t nwork, int32_t nb, bool split, const DenseJob *one, int32_t enc, int32_t mode,
+                              int32_t steps);
+constexpr int64_t kDenseSplitItems = 256;  // 256-row items below which a list is split
 // The same `steps` steps in one launch (dense_steps_kernel): the work list
 // split into kDenseQueues queues of whole runs (queue x: items off[x] ..
 // off[x+1]-1), tasks taken in step order from each queue's ticket counter,
