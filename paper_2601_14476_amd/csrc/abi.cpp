@@ -643,6 +643,7 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
     const_cast<psa_graph *>(g)->refs.fetch_add(1);
     j->graph_ref = const_cast<psa_graph *>(g);
     j->g = g;
+    j->auto_tpw = desc->trials_per_group == 0;
     j->run.trials = desc->trials;
     j->run.t4 = (desc->trials + 3) / 4 * 4;
     j->run.steps = S;
@@ -696,6 +697,14 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
     j->identity_factors = desc->algorithm == PSA_ALG_PSA && desc->t_res == 0;
     for (int32_t i = 0; i < n && j->identity_factors; ++i)
         j->identity_factors = lam[i] == 1.0f && dlt[i] == 0.0f && thr[i] >= psa::kGateOneHost;
+    double max_lam = 0.0, max_prod = 0.0;
+    for (int32_t i = 0; i < n; ++i) {
+        if (thr[i] < psa::kGateOneHost) j->run.gated = 1;
+        max_lam = std::max(max_lam, std::fabs(static_cast<double>(lam[i])));
+        max_prod = std::max(max_prod, std::fabs(static_cast<double>(lam[i]) * dlt[i]));
+    }
+    j->run.i0_lim = static_cast<float>(std::min(max_prod > 0.0 ? psa::kEstimateLimit / max_prod : 1e30,
+                                                max_lam > 0.0 ? 1e30 / max_lam : 1e30));
     // per-p-bit arrays padded to n4: padding p-bits never fire
     lam.resize(static_cast<size_t>(n4), 1.0f);
     dlt.resize(static_cast<size_t>(n4), 0.0f);
@@ -711,7 +720,6 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
         // per-p-bit constants of the streaming sweeps in their task order
         const size_t tasks = static_cast<size_t>(n4) / 4;
         std::vector<uint32_t> pps((tasks + 63) / 64 * 64 * 16, 0u);
-        double max_lam = 0.0, max_prod = 0.0;
         for (size_t s = 0; s < tasks; ++s)
             for (int32_t p = 0; p < 4; ++p) {
                 const int32_t i = 4 * g->gorder_host[s] + p;
@@ -727,12 +735,7 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
                 memcpy(c + 1, &p1, 4);
                 memcpy(c + 2, &p2, 4);
                 c[3] = thr[i];
-                if (i < n && thr[i] < psa::kGateOneHost) j->run.gated = 1;
-                max_lam = std::max(max_lam, std::fabs(static_cast<double>(lam[i])));
-                max_prod = std::max(max_prod, std::fabs(static_cast<double>(lam[i]) * dlt[i]));
             }
-        j->run.i0_lim = static_cast<float>(std::min(max_prod > 0.0 ? psa::kEstimateLimit / max_prod : 1e30,
-                                                    max_lam > 0.0 ? 1e30 / max_lam : 1e30));
         if ((st = dev_upload(&j->d_pps, pps.data(), pps.size(), "job upload", &j->dev_bytes, arena)) != PSA_OK) return st;
         j->run.pps = j->d_pps;
     }
@@ -806,6 +809,7 @@ psa_status clone_job_for_timing(psa_job *src, psa_job **out) {
     j->pplan = src->pplan;
     j->tp = src->tp;
     j->identity_factors = src->identity_factors;
+    j->auto_tpw = src->auto_tpw;
     j->shares = src;
     j->d_i0 = src->d_i0;
     j->d_lambda = src->d_lambda;

@@ -74,9 +74,18 @@ bool plan_anneal(const DevGraph &g, const DevRun &run, int32_t tpw_req, int32_t 
     if (tpw_req == 1 || tpw_req == 4) {
         p.tpw = tpw_req;
     } else {
-        // four trials per workgroup share each CSR walk; one trial per
-        // workgroup exposes four times the workgroups
-        p.tpw = (run.t4 / 4 >= num_cu) ? 4 : 1;
+        // One trial per workgroup exposes four times the workgroups; four
+        // share each walk of the rows and issue fewer instructions.  On the
+        // streaming sweep four pay once the one-trial workgroups would take
+        // three rounds or more of the compute units (a unit runs 1,024 of
+        // their threads at once; us per step, one and four trials: 2,000 p-bits of
+        // degree 6, 512 trials 2.9 and 3.7, 600 4.1 and 3.7; 4,000, 512 5.8 and
+        // 6.0, 600 8.1 and 5.9; 250, 1,024 1.7 and 2.6, 2,048 2.8 and 2.8).
+        AnnealPlan one;
+        if (ell_ok && g.e4_mode >= 0 && plan_anneal(g, run, 1, lpt_req, block_req, max_lds, num_cu, &one, nullptr))
+            p.tpw = static_cast<int64_t>(run.trials) * one.block > 2 * static_cast<int64_t>(num_cu) * 1024 ? 4 : 1;
+        else
+            p.tpw = (run.t4 / 4 >= num_cu) ? 4 : 1;
     }
     p.grid = p.tpw == 4 ? run.t4 / 4 : run.trials;
     if (p.tpw == 4) {

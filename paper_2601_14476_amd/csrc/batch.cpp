@@ -46,29 +46,46 @@ psa_status ensure(void **buf, size_t *cap, size_t bytes) {
 
 namespace psa {
 
-// Build the XCD-aware work list for `jobs` (cost = trials * n4 * steps).
-void build_work_list(const std::vector<int32_t> &trials, const std::vector<double> &cost,
+// Build the XCD-aware work list of a batch: items[j] work items of job j, each
+// of modelled time cost[j]; `slots` workgroups run at once on an XCD.  Chunks of
+// a job's items go whole to one XCD, costliest first, to the one that then ends
+// first: an XCD ends with its longest item as long as its items all run at
+// once, past that with its work spread over its slots, if that is later, and
+// one item more.  A list that fits the slots leaves no XCD more items than slots
+// (12 graphs and a denser one, 256 items for 256 compute units: dealt by work
+// alone 5.9 ms, with the second rule alone 4.1, this way 3.4).
+void build_work_list(const std::vector<int32_t> &items, const std::vector<double> &cost, int32_t slots,
                      std::vector<int2> *work) {
     struct Chunk {
         int32_t job, q0, q1;
-        double cost;
     };
     std::vector<Chunk> chunks;
-    for (size_t j = 0; j < trials.size(); ++j) {
-        const double per = trials[j] > 0 ? cost[j] / trials[j] : 0.0;
-        for (int32_t q = 0; q < trials[j]; q += kChunk) {
-            const int32_t q1 = std::min(trials[j], q + kChunk);
-            chunks.push_back(Chunk{static_cast<int32_t>(j), q, q1, per * (q1 - q)});
-        }
-    }
+    for (size_t j = 0; j < items.size(); ++j)
+        for (int32_t q = 0; q < items[j]; q += kChunk)
+            chunks.push_back(Chunk{static_cast<int32_t>(j), q, std::min(items[j], q + kChunk)});
     std::stable_sort(chunks.begin(), chunks.end(),
-                     [](const Chunk &a, const Chunk &b) { return a.cost > b.cost; });
+                     [&](const Chunk &a, const Chunk &b) { return cost[static_cast<size_t>(a.job)] > cost[static_cast<size_t>(b.job)]; });
+    const bool all_run = std::accumulate(items.begin(), items.end(), int64_t{0}) <= int64_t{kXcds} * slots;
     std::vector<std::vector<int2>> queue(kXcds);
-    std::vector<double> load(kXcds, 0.0);
+    std::vector<double> sum(kXcds, 0.0), longest(kXcds, 0.0);
     for (const Chunk &c : chunks) {
-        const int x = static_cast<int>(std::min_element(load.begin(), load.end()) - load.begin());
-        for (int32_t q = c.q0; q < c.q1; ++q) queue[x].push_back(make_int2(c.job, q));
-        load[x] += c.cost;
+        const double each = cost[static_cast<size_t>(c.job)];
+        const int32_t n = c.q1 - c.q0;
+        int best = 0;
+        double best_end = 0.0;
+        for (int x = 0; x < kXcds; ++x) {
+            const double most = std::max(longest[x], each);
+            const int64_t count = static_cast<int64_t>(queue[x].size()) + n;
+            const double end = count <= slots ? most
+                                              : std::max(most, (sum[x] + n * each) / slots) + (all_run ? 1e30 : each);
+            if (x == 0 || end < best_end || (end == best_end && sum[x] < sum[best])) {
+                best = x;
+                best_end = end;
+            }
+        }
+        for (int32_t q = c.q0; q < c.q1; ++q) queue[best].push_back(make_int2(c.job, q));
+        sum[best] += n * each;
+        longest[best] = std::max(longest[best], each);
     }
     size_t len = 0;
     for (const auto &qu : queue) len = std::max(len, qu.size());
@@ -77,19 +94,22 @@ void build_work_list(const std::vector<int32_t> &trials, const std::vector<doubl
         for (size_t s = 0; s < queue[x].size(); ++s) (*work)[s * kXcds + x] = queue[x][s];
 }
 
-// Automatic path choice.  Whole-device estimates per step (above the floors
-// below): the CSR walk issues ~60 + 3 d lane-operations per update (d = mean
-// degree) at 39.3 T lane-ops/s; the dense product costs 2 np^2 tp operations
-// at half the int8 (or, 1- and 2-bit couplings, fp4) matrix peak, or the
-// bytes of J once per trial tile at the HBM peak, whichever is larger, plus
-// ~60 lane-operations of epilogue per update.
+// Automatic path choice.  Estimates per step (above the floors below): the CSR
+// sweeps' lane-operations per update (csr_step_seconds); the dense product's 2
+// np^2 tp operations at two fifths of the int8 (or, 1- and 2-bit couplings,
+// fp4) matrix peak, or the bytes of J once per trial tile at the HBM peak,
+// whichever is larger, plus 40 lane-operations of epilogue per update (+-1
+// couplings of density 0.06, us per step, estimate and measured: 3,000 p-bits x 64
+// trials 4.7 and 5.0, 4,000 x 64 5.0 and 6.0, 2,000 x 1,024 8.5 and 10.6, 4,000
+// x 1,024 17.0 and 17.1; int8 3,000 x 64 8.6 and 11.6).
 // Latency floors of a step: the CSR sweep's step is a barrier and a chain of
 // LDS reads inside one persistent launch; the dense step is a launch of its
 // own.  They decide for small runs, whose throughput terms are tiny (a G1-
 // sized run of 10 trials: 2 us per CSR step measured, several times that per
 // dense step).
 constexpr double kCsrStepFloorSeconds = 1.5e-6;
-constexpr double kDenseStepFloorSeconds = 6.0e-6;
+constexpr double kDenseStepFloorSeconds = 4.2e-6;    // fp4 couplings
+constexpr double kDenseI8StepFloorSeconds = 8.0e-6;  // int8
 
 double csr_step_seconds(const DevGraph &g, const DevRun &run, const AnnealPlan &plan) {
     if (plan.ell) {
@@ -112,13 +132,14 @@ double csr_step_seconds(const DevGraph &g, const DevRun &run, const AnnealPlan &
 }
 
 double dense_step_seconds(int32_t n, int32_t t4, bool two_bit, bool one_bit) {
-    two_bit = two_bit || one_bit;
-    const double np = two_bit ? (n + 255) / 256 * 256 : (n + 127) / 128 * 128;
+    const bool fp4 = two_bit || one_bit;
+    const double np = fp4 ? (n + 255) / 256 * 256 : (n + 127) / 128 * 128;
     const int32_t nb = t4 >= 64 ? 4 : (t4 >= 32 ? 2 : 1);
     const double tp = std::ceil(t4 / (16.0 * nb)) * 16.0 * nb;
-    const double mfma = 2.0 * np * np * tp / (0.5 * (two_bit ? kMfmaF4OpsPerSecond : kMfmaI8OpsPerSecond));
+    const double mfma = 2.0 * np * np * tp / (0.4 * (fp4 ? kMfmaF4OpsPerSecond : kMfmaI8OpsPerSecond));
     const double bytes = np * np * (one_bit ? 0.125 : (two_bit ? 0.25 : 1.0)) * (tp / (16.0 * nb)) / kHbmBytesPerSecond;
-    return kDenseStepFloorSeconds + std::max(mfma, bytes) + static_cast<double>(n) * t4 * 60.0 / kValuOpsPerSecond;
+    return (fp4 ? kDenseStepFloorSeconds : kDenseI8StepFloorSeconds) + std::max(mfma, bytes) +
+           static_cast<double>(n) * t4 * 40.0 / kValuOpsPerSecond;
 }
 
 bool dense_two_bit(const psa_graph *g) {
@@ -463,6 +484,76 @@ psa_status dense_step_jobs(psa_ctx *ctx, psa_job *const *jobs, int32_t count, in
 
 }  // namespace psa
 
+namespace {
+
+// Time of one workgroup's step, in lane-operations at a compute unit's rate,
+// fitted to runs of degree 4 to 50 on the streaming sweeps.
+double item_ops(const psa_job *job, int32_t tpw) {
+    const psa::DevGraph &g = job->g->dev;
+    const double d = g.nnz / static_cast<double>(std::max(g.n, 1));
+    return g.n * (tpw == 4 ? 4.0 * (25.0 + 2.6 * d) : 50.0 + 7.0 * d) * std::max(job->run.t_res, 1);
+}
+
+// Which runs of a batch take four trials per workgroup (those whose trials per
+// workgroup are the library's choice and whose rows the four-trial streaming
+// sweep reads).  A four-trial workgroup walks its rows once for the four and
+// issues 1.6 to 2.5 times fewer instructions per update, but takes about twice
+// as long per step.  The batch ends with its longest workgroup or with the
+// work spread over the compute units, whichever is later: every run starts
+// with four, and the run with the longest workgroup goes back to one as long as
+// that end comes earlier.  Measured (12 graphs of degree 4-8 and 2,069 to 4,044 p-bits,
+// 500 steps, one and four trials): 64 trials 4.55 and 3.17 ms, 32 3.15 and
+// 3.14, 16 1.73 and 3.15; 16 requests of 4,951 to 19,606 p-bits, degree 4 to 50,
+// 250 steps, 32.7 and 18.7 ms.
+std::vector<char> choose_four_trials(const psa_ctx *ctx, psa_job *const *jobs, const std::vector<int32_t> &idx,
+                                     const std::vector<int32_t> &t_end) {
+    const size_t count = idx.size();
+    std::vector<char> four(count, 0), fixed(count, 1);
+    std::vector<double> one_t(count, 0.0), four_t(count, 0.0);
+    double load = 0.0;  // of the chosen forms, over the compute units
+    for (size_t x = 0; x < count; ++x) {
+        const psa_job *job = jobs[idx[x]];
+        const psa::DevGraph &g = job->g->dev;
+        const double steps = t_end[static_cast<size_t>(idx[x])] - job->t;
+        one_t[x] = steps * item_ops(job, 1);
+        four_t[x] = steps * item_ops(job, 4);
+        psa::AnnealPlan plan;
+        int32_t variant = 0;
+        fixed[x] = !(job->auto_tpw && job->plan.tpw == 1 && job->run.pps &&
+                     psa::plan_batch_item(g, job->run, 4, 0, ctx->max_lds, &plan, &variant, nullptr) && plan.ell);
+        four[x] = fixed[x] ? job->plan.tpw == 4 : 1;
+        load += (four[x] ? four_t[x] * (job->run.t4 / 4) : one_t[x] * job->run.trials) / ctx->num_cu;
+    }
+    auto longest = [&](size_t *at) {
+        double most = 0.0;
+        for (size_t x = 0; x < count; ++x) {
+            const double t = four[x] ? four_t[x] : one_t[x];
+            if (t > most) {
+                most = t;
+                *at = x;
+            }
+        }
+        return most;
+    };
+    for (;;) {
+        size_t x = count;
+        const double end = std::max(longest(&x), load);
+        if (x == count || !four[x] || fixed[x]) break;
+        const psa_job *job = jobs[idx[x]];
+        const double change = (one_t[x] * job->run.trials - four_t[x] * (job->run.t4 / 4)) / ctx->num_cu;
+        four[x] = 0;
+        size_t y = count;
+        if (std::max(longest(&y), load + change) >= end) {
+            four[x] = 1;
+            break;
+        }
+        load += change;
+    }
+    return four;
+}
+
+}  // namespace
+
 extern "C" {
 
 psa_status psa_jobs_step_batch(psa_ctx *ctx, int32_t count, psa_job *const *jobs, int32_t k) {
@@ -478,6 +569,7 @@ psa_status psa_jobs_step_batch(psa_ctx *ctx, int32_t count, psa_job *const *jobs
         std::vector<psa_job *> dense_jobs;
         size_t lds = 0;
         int32_t max_lanes = 0;
+        std::vector<int32_t> sweep_jobs;  // indices of the runs on the CSR path
         double dense_s = 0.0, csr_s = 0.0;  // model estimates of the two families' device time
         for (int32_t j = 0; j < count; ++j) {
             psa_job *job = jobs[j];
@@ -502,11 +594,18 @@ psa_status psa_jobs_step_batch(psa_ctx *ctx, int32_t count, psa_job *const *jobs
                            (te - job->t);
                 continue;
             }
+            sweep_jobs.push_back(j);
+        }
+        std::vector<char> four = choose_four_trials(ctx, jobs, sweep_jobs, t_end);
+        for (size_t x = 0; x < sweep_jobs.size(); ++x) {
+            const int32_t j = sweep_jobs[x];
+            psa_job *job = jobs[j];
+            const int32_t te = t_end[static_cast<size_t>(j)];
             psa::AnnealPlan plan;
             int32_t variant = 0;
             std::string why;
-            if (!psa::plan_batch_item(job->g->dev, job->run, job->plan.tpw,
-                                      job->plan.tpw == 1 ? job->plan.lpt : 0, ctx->max_lds, &plan,
+            const int32_t tpw = four[x] ? 4 : job->plan.tpw;
+            if (!psa::plan_batch_item(job->g->dev, job->run, tpw, tpw == 1 ? job->plan.lpt : 0, ctx->max_lds, &plan,
                                       &variant, &why)) {
                 set_error("psa_jobs_step_batch: " + why);
                 return PSA_EUNSUPPORTED;
@@ -517,7 +616,7 @@ psa_status psa_jobs_step_batch(psa_ctx *ctx, int32_t count, psa_job *const *jobs
             bj.variant = variant;
             table.push_back(bj);
             trials.push_back(plan.tpw == 4 ? job->run.t4 / 4 : job->run.trials);  // work items
-            cost.push_back(static_cast<double>(job->run.trials) * job->g->dev.n4 * (te - job->t));
+            cost.push_back(item_ops(job, plan.tpw) * (te - job->t));
             lds = std::max(lds, plan.lds_bytes);
             max_lanes = std::max(max_lanes, job->g->dev.n4 / 4 * plan.lpt);
         }
@@ -539,8 +638,12 @@ psa_status psa_jobs_step_batch(psa_ctx *ctx, int32_t count, psa_job *const *jobs
                 PSA_HIP(hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0), "hipStreamWaitEvent");
             return PSA_OK;
         }
+        // a lane for every task of the longest run that keeps its tasks in lanes
+        // (2,000 p-bits of degree 6, 256 trials: 4.4 us per step with 512
+        // threads, 1.75 with 1,024)
+        const int32_t block = max_lanes > 512 ? 1024 : (max_lanes > 256 ? 512 : 256);
         std::vector<int2> work;
-        psa::build_work_list(trials, cost, &work);
+        psa::build_work_list(trials, cost, ctx->num_cu / kXcds * (1024 / block), &work);
         // the staging buffers are reused: the previous batched launch must be done
         PSA_HIP(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
         psa_status st;
@@ -557,7 +660,6 @@ psa_status psa_jobs_step_batch(psa_ctx *ctx, int32_t count, psa_job *const *jobs
         PSA_HIP(hipMemcpyAsync(ctx->d_batch_work, ctx->h_batch_work.data(), work.size() * sizeof(int2),
                                hipMemcpyHostToDevice, ctx->stream),
                 "batch work upload");
-        const int32_t block = max_lanes > 1024 ? 1024 : (max_lanes > 256 ? 512 : 256);
         hipEvent_t ev = nullptr;
         if ((st = psa::time_begin(ctx, ctx->stream, &ev)) != PSA_OK) return st;
         PSA_HIP(psa::launch_anneal_batch(ctx->stream, static_cast<const psa::BatchJob *>(ctx->d_batch_table),
@@ -599,7 +701,6 @@ psa_status psa_anneal_batch(psa_ctx *ctx, int32_t count, const psa_batch_item *i
                         return st;
                     }
                 }
-                if (d.trials_per_group == 0) d.trials_per_group = 1;
             }
             psa_job *job = nullptr;
             psa_status st = psa_job_create(ctx, items[j].graph, &d, &job);

@@ -49,12 +49,17 @@ __device__ __forceinline__ uint32_t in_vgpr(uint32_t x) {
 struct RoundKeys {
     uint32_t k0[7], k1[7];
 };
+template <bool VGPR = true>
 __device__ __forceinline__ RoundKeys round_keys(uint32_t k0, uint32_t k1) {
     RoundKeys K;
 #pragma unroll
     for (int i = 0; i < 7; ++i) {
-        K.k0[i] = in_vgpr(k0 + static_cast<uint32_t>(i + 3) * 0x9E3779B9u);
-        K.k1[i] = in_vgpr(k1 + static_cast<uint32_t>(i + 3) * 0xBB67AE85u);
+        K.k0[i] = k0 + static_cast<uint32_t>(i + 3) * 0x9E3779B9u;
+        K.k1[i] = k1 + static_cast<uint32_t>(i + 3) * 0xBB67AE85u;
+        if constexpr (VGPR) {
+            K.k0[i] = in_vgpr(K.k0[i]);
+            K.k1[i] = in_vgpr(K.k1[i]);
+        }
     }
     return K;
 }
@@ -198,7 +203,6 @@ __device__ __forceinline__ void ell4_steps(const AnnealArgs &a, int32_t q, unsig
     const uint32_t ones = in_vgpr(0x01010101u);
     const bool need_gate = ALG != kAlgPeriod && a.gated != 0;
     const RoundKeys keys = round_keys(a.k0, a.k1);
-    const InputState st{a.xs, a.stall24, a.ring, a.alpha, n4};
     const bool resident = tasks <= static_cast<int32_t>(blockDim.x);
     const int32_t nsub = ALG == kAlgPeriod ? a.t_res : 1;
     u32x4 c[4] = {};
@@ -281,6 +285,23 @@ __device__ __forceinline__ void ell4_steps(const AnnealArgs &a, int32_t q, unsig
                     th[p] = c[p].w;
                 }
                 const int32_t i0 = static_cast<int32_t>(4 * m);
+                // TApSA window sums (without this step's field) and SpSA held
+                // inputs of the task's four trials, 16 bytes per access
+                const uint32_t al = static_cast<uint32_t>(a.alpha);
+                const uint32_t count = tau + 1 < al ? tau + 1 : al;
+                const size_t row = static_cast<size_t>(q) * n4 + i0;
+                u32x4 state[4] = {};
+                if constexpr (ALG == kAlgTapsa) {
+#pragma unroll
+                    for (int p = 0; p < 4; ++p)
+                        for (uint32_t s2 = 1; s2 < count; ++s2)
+                            state[p] += load_global_x4(a.ring + ((row + p) * al + (tau - s2) % al) * 4);
+                } else if constexpr (ALG == kAlgSpsa) {
+                    if (t > 0) {
+#pragma unroll
+                        for (int p = 0; p < 4; ++p) state[p] = load_global_x4(a.xs + (row + p) * 4);
+                    }
+                }
                 uint32_t up[4] = {0u, 0u, 0u, 0u}, fire[4] = {0u, 0u, 0u, 0u};
                 // trials two at a time: a byte pair of the new words each
 #pragma unroll
@@ -319,9 +340,17 @@ __device__ __forceinline__ void ell4_steps(const AnnealArgs &a, int32_t q, unsig
                             close = false;
 #pragma unroll
                             for (int p = 0; p < 4; ++p) {
-                                const int32_t L = static_cast<int32_t>(2.0f * (ell4_count(sum, p, kk) + hd[p]));
-                                x[p] = 0.0f;
-                                if (valid) x[p] = input_of<ALG>(ac[p], bc[p], L, st, i0 + p, k, tau, sw[p]);
+                                const float Lf = 2.0f * (ell4_count(sum, p, kk) + hd[p]);
+                                if constexpr (ALG == kAlgTapsa) {
+                                    const int32_t L = static_cast<int32_t>(Lf);
+                                    const int32_t total = static_cast<int32_t>(state[p][kk]) + L;
+                                    state[p][kk] = static_cast<uint32_t>(L);
+                                    x[p] = ac[p] * (static_cast<float>(total) / static_cast<float>(count) + bc[p]);
+                                } else {
+                                    x[p] = t > 0 && (sw[p] >> 8) < a.stall24 ? __uint_as_float(state[p][kk])
+                                                                             : ac[p] * (Lf + bc[p]);
+                                    state[p][kk] = __float_as_uint(x[p]);
+                                }
                                 d[h][p] = decision_distance(x[p] * kTwoLog2e, rw[p]);
                                 close = close || !(fabsf(d[h][p]) > kCloseD);  // not a number: tanh_f32 decides
                             }
@@ -340,6 +369,17 @@ __device__ __forceinline__ void ell4_steps(const AnnealArgs &a, int32_t q, unsig
                         const uint32_t d0 = __float_as_uint(d[0][p]), d1 = __float_as_uint(d[1][p]);
                         up[p] |= H == 0 ? sign_bytes<0>(d0, d1) : sign_bytes<1>(d0, d1);
                         if (need_gate) fire[p] |= H == 0 ? sign_bytes<0>(gs[0][p], gs[1][p]) : sign_bytes<1>(gs[0][p], gs[1][p]);
+                    }
+                }
+                if constexpr (ALG == kAlgTapsa || ALG == kAlgSpsa) {
+                    // this step's fields into their window slot; the inputs held
+                    if (valid) {
+#pragma unroll
+                        for (int p = 0; p < 4; ++p) {
+                            void *to4 = ALG == kAlgTapsa ? static_cast<void *>(a.ring + ((row + p) * al + tau % al) * 4)
+                                                         : static_cast<void *>(a.xs + (row + p) * 4);
+                            *reinterpret_cast<u32x4 *>(to4) = state[p];
+                        }
                     }
                 }
 #pragma unroll

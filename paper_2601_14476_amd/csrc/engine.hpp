@@ -571,7 +571,7 @@ void ctx_retain(psa_ctx *ctx);
 void ctx_release(psa_ctx *ctx);
 
 // XCD-aware work list of a batched launch (batch.cpp).
-void build_work_list(const std::vector<int32_t> &trials, const std::vector<double> &cost,
+void build_work_list(const std::vector<int32_t> &items, const std::vector<double> &cost, int32_t slots,
                      std::vector<int2> *work);
 
 }  // namespace psa
@@ -689,6 +689,8 @@ struct psa_job {
     // the device arrays above are carved from memory the job does not own
     // (psa_anneal_noalloc's static scratch): never freed or grown
     bool borrowed = false;
+    // trials per workgroup left to the library: a batch may take four
+    bool auto_tpw = false;
     // every p-bit has lambda = 1, delta = 0 and thr24 >= 2^24 (no timing gate)
     bool identity_factors = false;
     // a timing clone: schedule, factors, task order and period records are

@@ -209,7 +209,6 @@ psa_status admit_job(psa_server *s, ServerJob *j) {
         st = psa::tuned_desc(s->ctx, j->graph, &d, PSA_TUNE_BATCH);
         if (st != PSA_OK) return st;
     }
-    if (d.trials_per_group == 0) d.trials_per_group = 1;
     st = psa_job_create(s->ctx, j->graph, &d, &j->job);
     if (st != PSA_OK) return st;
     // the autotuner may have built the dense matrix for a run that reads the CSR

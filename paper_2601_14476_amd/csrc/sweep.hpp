@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "device_math.hpp"
+#include "ell_sweep.hpp"
 #include "engine.hpp"
 
 namespace psa {
@@ -249,16 +250,41 @@ __device__ __forceinline__ FastCache<P> load_fast_cache(const Views &v, const in
     return c;
 }
 
+// The first fast_early<P>() cached slots' bytes of the buffer at LDS offset
+// OFF, issued before the step's random rounds, which need nothing from LDS: all
+// wavefronts leave the barrier together, so loads behind the rounds leave the
+// LDS idle first and the vector units afterwards.  One-row lanes (800 p-bits of
+// degree 48: 1.88 -> 1.79 us per step); two-row lanes, of few slots, are
+// slower that way (2,000 of degree 6: 1.22 -> 1.25 us).
+template <int P>
+constexpr int fast_early() { return P == 1 ? 8 : 0; }
+template <int P>
+struct EarlyBytes {
+    uint32_t x[fast_early<P>() > 0 ? fast_early<P>() : 1];
+};
+template <int P, uint32_t OFF>
+__device__ __forceinline__ EarlyBytes<P> load_early(const FastCache<P> &c) {
+    EarlyBytes<P> e{};
+#pragma unroll
+    for (int j = 0; j < fast_early<P>(); ++j) e.x[j] = lds_byte<OFF>(c.a[j]);
+    return e;
+}
+
 // Fields of the lane's P rows from the buffer at LDS offset OFF (cur points
 // there): the cached slots in one sum, then the edges past them.
 template <int P, uint32_t OFF, bool BLK>
 __device__ __forceinline__ void field_fast(const Views &v, const int32_t *rp, const int32_t *h,
-                                           const FastCache<P> &c, const uint8_t *cur, int32_t L[P]) {
+                                           const FastCache<P> &c, const EarlyBytes<P> &early,
+                                           const uint8_t *cur, int32_t L[P]) {
     uint32_t acc = 0u;
     constexpr int K = fast_slots<P>();
     constexpr int C = fast_chunk<P>();
+    constexpr int E = fast_early<P>();
+    static_assert(E % C == 0, "early slots are whole chunks");
 #pragma unroll
-    for (int g = 0; g < K / C; ++g) {
+    for (int j = 0; j < E; ++j) acc += early.x[j];
+#pragma unroll
+    for (int g = E / C; g < K / C; ++g) {
         if (static_cast<uint32_t>(g) < c.chunks) {
 #pragma unroll
             for (int j = 0; j < C; ++j) acc += lds_byte<OFF>(c.a[C * g + j]);
@@ -306,64 +332,98 @@ __device__ __forceinline__ void field_words(const Views &v, int32_t i, const uin
 }
 
 // ---------------------------------------------------------------------------
+// Lanes of a task.  LPT 1 and 4: neighbours; LPT 2: lanes l and l + 32 of a
+// wavefront (sub 0 and 1 of slot 32 wave + l).
+template <int LPT>
+__device__ __forceinline__ int32_t lane_slot() {
+    const int32_t tid = static_cast<int32_t>(threadIdx.x);
+    return LPT == 2 ? (tid >> 6) * 32 + (tid & 31) : tid / LPT;
+}
+template <int LPT>
+__device__ __forceinline__ uint32_t lane_sub() {
+    return LPT == 2 ? (threadIdx.x >> 5) & 1u : threadIdx.x % LPT;
+}
+
 // Random words of a task for one trial.  With LPT lanes per task, lane `sub`
 // needs the words of its P = 4/LPT p-bits sub*P .. sub*P+P-1.  When the gate
-// is on and LPT >= 2, even lanes draw the r block and odd lanes the gate
-// block, and each pair swaps the words the other needs (DPP), so the two
-// Philox blocks run side by side.
+// is on and LPT >= 2, even subs draw the r block and odd ones the gate block
+// side by side, then exchange what the other needs: with LPT 2 one half-wave
+// swap of words 0 and 2 leaves the r words of both halves in one register and
+// the gate words in the other (words 1 and 3 likewise); with LPT 4 neighbours
+// swap by DPP.  B.own: the prefix of the lane's block; B.gate: LPT 1's second.
 // ---------------------------------------------------------------------------
+struct StepBlocks {
+    BlockPrefix own, gate;
+};
 template <int LPT>
-__device__ __forceinline__ void task_words(uint32_t t, uint32_t m, uint32_t k, uint32_t sub,
-                                           bool need_gate, uint32_t k0, uint32_t k1,
-                                           uint32_t rw[4 / LPT], uint32_t gw[4 / LPT]) {
+__device__ __forceinline__ StepBlocks step_blocks(uint32_t t, uint32_t k, uint32_t sub, bool gated, uint32_t k0,
+                                                  uint32_t k1) {
+    StepBlocks B;
+    B.own = block_prefix(t, k, kTagR, k0, k1);
+    B.gate = gated ? block_prefix(t, k, kTagGate, k0, k1) : B.own;
+    if constexpr (LPT > 1) {
+        if (gated) {
+            const bool odd = (sub & 1u) != 0u;
+            B.own.b = odd ? B.gate.b : B.own.b;
+            B.own.c = odd ? B.gate.c : B.own.c;
+            B.own.e = odd ? B.gate.e : B.own.e;
+        }
+    }
+    return B;
+}
+template <int LPT>
+__device__ __forceinline__ void task_words(uint32_t m, uint32_t sub, bool gated, const StepBlocks &B,
+                                           const RoundKeys &keys, uint32_t rw[4 / LPT], uint32_t gw[4 / LPT]) {
+    const Words4 b = block_of_task(m, B.own, keys);
     if constexpr (LPT == 1) {
-        const Words4 r = block_of(t, m, k, kTagR, k0, k1);
-        rw[0] = r.x;
-        rw[1] = r.y;
-        rw[2] = r.z;
-        rw[3] = r.w;
+        rw[0] = b.x;
+        rw[1] = b.y;
+        rw[2] = b.z;
+        rw[3] = b.w;
         gw[0] = gw[1] = gw[2] = gw[3] = 0u;
-        if (need_gate) {
-            const Words4 g = block_of(t, m, k, kTagGate, k0, k1);
+        if (gated) {
+            const Words4 g = block_of_task(m, B.gate, keys);
             gw[0] = g.x;
             gw[1] = g.y;
             gw[2] = g.z;
             gw[3] = g.w;
         }
-    } else {
-        const uint32_t tag = (need_gate && (sub & 1u)) ? kTagGate : kTagR;
-        const Words4 b = block_of(t, m, k, tag, k0, k1);
-        if constexpr (LPT == 2) {
-            if (need_gate) {  // lane 0 holds the r words, lane 1 the gate words
-                const uint32_t x0 = swap_pair(sub ? b.x : b.z);
-                const uint32_t x1 = swap_pair(sub ? b.y : b.w);
-                rw[0] = sub ? x0 : b.x;
-                rw[1] = sub ? x1 : b.y;
-                gw[0] = sub ? b.z : x0;
-                gw[1] = sub ? b.w : x1;
-            } else {
-                rw[0] = sub ? b.z : b.x;
-                rw[1] = sub ? b.w : b.y;
-                gw[0] = gw[1] = 0u;
-            }
-        } else {  // LPT == 4: even lanes r block, odd lanes gate block
-            const uint32_t own = word_of(b, sub);
-            if (need_gate) {
-                const uint32_t x = swap_pair(word_of(b, sub ^ 1u));
-                const bool even = (sub & 1u) == 0u;
-                rw[0] = even ? own : x;
-                gw[0] = even ? x : own;
-            } else {
-                rw[0] = own;
-                gw[0] = 0u;
-            }
+    } else if constexpr (LPT == 2) {
+        if (gated) {
+            const auto e = __builtin_amdgcn_permlane32_swap(b.x, b.z, false, false);
+            const auto o = __builtin_amdgcn_permlane32_swap(b.y, b.w, false, false);
+            rw[0] = e[0];
+            rw[1] = o[0];
+            gw[0] = e[1];
+            gw[1] = o[1];
+        } else {
+            rw[0] = sub ? b.z : b.x;
+            rw[1] = sub ? b.w : b.y;
+            gw[0] = gw[1] = 0u;
+        }
+    } else {  // LPT == 4: even lanes r block, odd lanes gate block
+        const uint32_t own = word_of(b, sub);
+        if (gated) {
+            const uint32_t x = swap_pair(word_of(b, sub ^ 1u));
+            const bool even = (sub & 1u) == 0u;
+            rw[0] = even ? own : x;
+            gw[0] = even ? x : own;
+        } else {
+            rw[0] = own;
+            gw[0] = 0u;
         }
     }
 }
 
-__device__ __forceinline__ bool any_gate(const uint32_t *thr, int32_t m) {
-    const uint4 th = *reinterpret_cast<const uint4 *>(thr + 4 * m);
-    return (th.x < kGateOne) | (th.y < kGateOne) | (th.z < kGateOne) | (th.w < kGateOne);
+// Masks of a lane's P values: byte j all ones where v[j] is negative.
+template <int P>
+__device__ __forceinline__ uint32_t sign_bytes_of(const uint32_t (&v)[P]) {
+    if constexpr (P == 4)
+        return sign_bytes<0>(v[0], v[1]) | sign_bytes<1>(v[2], v[3]);
+    else if constexpr (P == 2)
+        return sign_bytes<0>(v[0], v[1]);
+    else
+        return sign_mask(v[0]) & 0xFFu;
 }
 
 // ---------------------------------------------------------------------------
@@ -379,7 +439,7 @@ struct TaskConst {
     int32_t h[P];
     float lam[P], dlt[P];
     uint32_t thr[P];
-    bool need_gate;     // some p-bit of the task (all four) has a timing gate
+    float p1[P], p2[P];  // lambda and lambda delta times 2 log2 e (the decision's exponent)
 };
 
 template <int LPT>
@@ -396,8 +456,9 @@ __device__ __forceinline__ TaskConst<4 / LPT> load_task(const Views &v, int32_t 
         c.lam[j] = v.lam[c.base + j];
         c.dlt[j] = v.dlt[c.base + j];
         c.thr[j] = v.thr[c.base + j];
+        c.p1[j] = c.lam[j] * kTwoLog2e;
+        c.p2[j] = c.p1[j] * c.dlt[j];
     }
-    c.need_gate = any_gate(v.thr, m);
     return c;
 }
 
@@ -419,8 +480,10 @@ template <int CSR, int LPT, int ALG, bool BLK, int FIELD, bool LRING = false>
 __device__ __forceinline__ uint32_t task_one_trial(const Views &v, const TaskConst<4 / LPT> &c,
                                                    const EdgeCache *ec, const FastCache<4 / LPT> *fc,
                                                    LaneInput<4 / LPT> *li, int32_t *lring, uint32_t sub, uint32_t k,
-                                                   uint32_t t, float i0t, const unsigned char *cur,
-                                                   uint32_t k0, uint32_t k1, const InputState &st) {
+                                                   uint32_t t, float i0t, float close_d,
+                                                   const unsigned char *cur, uint32_t k0, uint32_t k1,
+                                                   bool gated, const StepBlocks &B, const RoundKeys &keys,
+                                                   const InputState &st) {
     constexpr int P = 4 / LPT;
     constexpr bool kU = Enc<1, CSR>::kU;
     // resident lanes carry the input stage in registers (li)
@@ -448,7 +511,7 @@ __device__ __forceinline__ uint32_t task_one_trial(const Views &v, const TaskCon
 #pragma unroll
         for (int j = 0; j < P; ++j) {
             if constexpr (LRING)
-                tap_w[j] = lring + static_cast<size_t>(base + j) * al + slot;
+                tap_w[j] = lring + slot * static_cast<uint32_t>(st.n4) + base + j;
             else
                 tap_w[j] = st.ring + ((static_cast<size_t>(k >> 2) * st.n4 + base + j) * al + slot) * 4 + (k & 3u);
             tap_old[j] = t >= al ? *tap_w[j] : 0;
@@ -456,9 +519,15 @@ __device__ __forceinline__ uint32_t task_one_trial(const Views &v, const TaskCon
     } else {
         (void)lring;
     }
-    const bool need_gate = ALG != kAlgPeriod && c.need_gate;
+    EarlyBytes<P> early{};
+    constexpr bool FAST = CSR == kCsrUnit && (FIELD == kFieldFast0 || FIELD == kFieldFast1) && P <= 2;
+    constexpr uint32_t FAST_OFF = FIELD == kFieldFast1 ? static_cast<uint32_t>(kFastStride) : 0u;
+    if constexpr (FAST) {
+        early = load_early<P, FAST_OFF>(*fc);
+        if constexpr (fast_early<P>() > 0) __builtin_amdgcn_sched_barrier(0);
+    }
     uint32_t rw[P], gw[P], sw[P];
-    task_words<LPT>(t, static_cast<uint32_t>(c.m), k, sub, need_gate, k0, k1, rw, gw);
+    task_words<LPT>(static_cast<uint32_t>(c.m), sub, gated, B, keys, rw, gw);
 #pragma unroll
     for (int j = 0; j < P; ++j) sw[j] = 0u;
     if (ALG == kAlgSpsa && t > 0) {
@@ -467,10 +536,9 @@ __device__ __forceinline__ uint32_t task_one_trial(const Views &v, const TaskCon
         for (int j = 0; j < P; ++j) sw[j] = word_of(b, sub * P + j);
     }
     int32_t L[P];
-    if constexpr (CSR == kCsrUnit && (FIELD == kFieldFast0 || FIELD == kFieldFast1) && P <= 2) {
+    if constexpr (FAST) {
         (void)ec;
-        field_fast<P, FIELD == kFieldFast0 ? 0u : static_cast<uint32_t>(kFastStride), BLK>(
-            v, c.rp, c.h, *fc, cur, L);
+        field_fast<P, FAST_OFF, BLK>(v, c.rp, c.h, *fc, early, cur, L);
     } else if constexpr (CSR == kCsrUnit && FIELD == kFieldEdgeCache) {
         (void)fc;
         if constexpr (P == 4) {
@@ -493,14 +561,22 @@ __device__ __forceinline__ uint32_t task_one_trial(const Views &v, const TaskCon
         for (int j = 0; j < P; ++j)
             L[j] = field_pm1<CSR>(v, c.rp[j], c.rp[j + 1], c.h[j], reinterpret_cast<const int8_t *>(cur));
     }
-    // pre-activations, then the P decisions from the tanh estimate; when
-    // some lane of the wave holds an estimate within 2^-16 of r, the P are
-    // retaken with the exact recipe -- one uniform branch per task, none per
-    // p-bit (pbit_up's decisions either way)
-    float xv[P];
+    // pre-activations, then the P decisions as signed distances; when some
+    // lane of the wave holds one within kCloseD of 0, the P are retaken with
+    // the exact recipe -- one uniform branch per task, none per p-bit.  A
+    // resident lane of plain pSA forms the decision's exponent straight from
+    // the field with its kept factors, as the streaming sweeps do.
+    constexpr bool DIRECT = RES && (ALG == kAlgPsa || ALG == kAlgPeriod);
+    float xv[P], d[P];
+    bool close = false;
 #pragma unroll
     for (int j = 0; j < P; ++j) {
         const int32_t i = base + j;
+        if constexpr (DIRECT) {
+            d[j] = decision_distance(i0t * fmaf(static_cast<float>(L[j]), c.p1[j], c.p2[j]), rw[j]);
+            close = close || !(fabsf(d[j]) > close_d);
+            continue;
+        }
         float x;
         if constexpr (ALG == kAlgTapsa && RES) {
             // the window sum advanced by the entering and the leaving field
@@ -519,29 +595,42 @@ __device__ __forceinline__ uint32_t task_one_trial(const Views &v, const TaskCon
             x = input_of<ALG>(i0t * c.lam[j], c.dlt[j], L[j], st, i, k, t, sw[j]);
         }
         xv[j] = x;
-    }
-    bool up[P];
-    bool close = false;
-#pragma unroll
-    for (int j = 0; j < P; ++j) {
-        const float diff = tanh_estimate_minus(xv[j], r_of(rw[j]));
-        close = close || !estimate_decides(diff);
-        up[j] = diff > 0.0f;
+        d[j] = decision_distance(x * kTwoLog2e, rw[j]);
+        close = close || !(fabsf(d[j]) > kCloseD);
     }
     if (__ballot(close) != 0u) {
 #pragma unroll
-        for (int j = 0; j < P; ++j) up[j] = tanh_f32(xv[j]) > r_of(rw[j]);
+        for (int j = 0; j < P; ++j) {
+            if constexpr (DIRECT) xv[j] = (i0t * c.lam[j]) * (static_cast<float>(L[j]) + c.dlt[j]);
+            d[j] = tanh_f32(xv[j]) > r_of(rw[j]) ? -1.0f : 1.0f;
+        }
     }
-    uint32_t out = 0u;
+    // new bytes of the lane's P p-bits, the old ones where a p-bit does not fire
+    constexpr uint32_t kOnes = P == 4 ? 0x01010101u : (P == 2 ? 0x0101u : 0x01u);
+    uint32_t db[P];
 #pragma unroll
-    for (int j = 0; j < P; ++j) {
-        const uint32_t old = cur[base + j];
-        const uint32_t th = c.thr[j];
-        const bool fire = ALG == kAlgPeriod ? period_fires(t, th) : (th >= kGateOne || fires(gw[j], th));
-        const uint32_t nb = kU ? (up[j] ? 1u : 0u) : (up[j] ? 0x01u : 0xFFu);
-        out |= (fire ? nb : old) << (8 * j);
+    for (int j = 0; j < P; ++j) db[j] = __float_as_uint(d[j]);
+    const uint32_t upm = sign_bytes_of<P>(db);
+    const uint32_t out = kU ? upm & kOnes : ((upm ^ (kOnes * 0xFFu)) | kOnes);  // +-1: 0x01 or 0xFF
+    if (ALG != kAlgPeriod && !gated) return out;
+    uint32_t old, fire;
+    if constexpr (P == 4)
+        old = *reinterpret_cast<const uint32_t *>(cur + base);
+    else if constexpr (P == 2)
+        old = *reinterpret_cast<const uint16_t *>(cur + base);
+    else
+        old = cur[base];
+    if constexpr (ALG == kAlgPeriod) {
+        fire = 0u;
+#pragma unroll
+        for (int j = 0; j < P; ++j) fire |= period_fires(t, c.thr[j]) ? 0xFFu << (8 * j) : 0u;
+    } else {
+        uint32_t gs[P];  // negative iff (gw >> 8) < thr, both below 2^25
+#pragma unroll
+        for (int j = 0; j < P; ++j) gs[j] = (gw[j] >> 8) - c.thr[j];
+        fire = sign_bytes_of<P>(gs);
     }
-    return out;
+    return __builtin_amdgcn_bitop3_b32(fire, out, old, 0xCA);  // fire ? out : old
 }
 
 // ---------------------------------------------------------------------------
@@ -772,15 +861,20 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
     // One trial per workgroup: update the P p-bits of one task and store them
     // (and the complemented copy) into the next buffer.
     constexpr int P = 4 / LPT;
-    const uint32_t sub = threadIdx.x % LPT;
+    const uint32_t sub = lane_sub<LPT>();
+    const bool gated = a.gated != 0;
+    // two rows or more per lane: round keys in vector registers (the one-row
+    // lanes' 64 edge slots leave no room for them)
+    const RoundKeys keys = round_keys<(P > 1)>(a.k0, a.k1);
     auto one_trial_step = [&](auto alg_tag, auto cached_tag, const TaskConst<P> &c,
-                              const EdgeCache *ec, LaneInput<P> *li, uint32_t tau, float i0t,
-                              uint32_t k0, uint32_t k1, const unsigned char *from, unsigned char *to)
-                              __attribute__((always_inline)) {
+                              const EdgeCache *ec, LaneInput<P> *li, uint32_t tau, float i0t, float close_d,
+                              uint32_t k0, uint32_t k1, const StepBlocks &B, const unsigned char *from,
+                              unsigned char *to) __attribute__((always_inline)) {
         constexpr int ALG = decltype(alg_tag)::value;
         constexpr bool CACHED = decltype(cached_tag)::value;
         const uint32_t b = task_one_trial<CSR, LPT, ALG, !CSR_LDS, CACHED ? kFieldEdgeCache : kFieldPlain>(
-            v, c, ec, nullptr, li, nullptr, sub, static_cast<uint32_t>(q), tau, i0t, from, k0, k1, st);
+            v, c, ec, nullptr, li, nullptr, sub, static_cast<uint32_t>(q), tau, i0t, close_d, from, k0, k1,
+            ALG != kAlgPeriod && gated, B, keys, st);
         const int32_t at = c.base;
         if constexpr (P == 4) {
             *reinterpret_cast<uint32_t *>(to + at) = b;
@@ -797,7 +891,7 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
     // When every task has a slot of its own (tasks x LPT <= BLOCK), a lane
     // keeps its task's constants in registers for the whole launch.
     const bool resident = TPW == 1 && tasks * LPT <= BLOCK;
-    const bool owns = resident && static_cast<int32_t>(threadIdx.x) / LPT < tasks;
+    const bool owns = resident && lane_slot<LPT>() < tasks;
     // resident lanes in the fast layout (LPT 2 or 4) sum cached slots; other
     // resident lanes (LPT 1) walk cached edge indices
     const bool fast = fast_lay && resident;
@@ -806,7 +900,7 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
     FastCache<P> own_fast = {};
     LaneInput<P> own_in = {};
     if (owns) {
-        own = load_task<LPT>(v, v.order[threadIdx.x / LPT], sub);
+        own = load_task<LPT>(v, v.order[lane_slot<LPT>()], sub);
         // input-stage state of the lane's p-bits: the TApSA window sums up to
         // step t_begin - 1 from the ring, the SpSA held inputs
         const size_t row0 = static_cast<size_t>(q >> 2) * n4 + own.base;
@@ -840,7 +934,8 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
     if (lds_ring) {
         const int32_t al = a.alpha;
         const size_t g0 = static_cast<size_t>(q >> 2) * n4 * al;
-        for (int32_t x = threadIdx.x; x < n4 * al; x += BLOCK) lring[x] = a.ring[(g0 + x) * 4 + (q & 3)];
+        for (int32_t x = threadIdx.x; x < n4 * al; x += BLOCK)  // [slot][p-bit]: lanes of a wavefront on different banks
+            lring[x % al * n4 + x / al] = a.ring[(g0 + x) * 4 + (q & 3)];
         __syncthreads();
     }
     if constexpr (kFastKind) {
@@ -856,16 +951,16 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
     }
     // Fast layout, one step: read the buffer at offset RO, write all four
     // copies into the other.
-    auto fast_step = [&](auto alg_tag, auto par_tag, auto lring_tag, uint32_t tau, float i0t, uint32_t k0,
-                         uint32_t k1) __attribute__((always_inline)) {
+    auto fast_step = [&](auto alg_tag, auto par_tag, auto lring_tag, uint32_t tau, float i0t, float close_d,
+                         uint32_t k0, uint32_t k1, const StepBlocks &B) __attribute__((always_inline)) {
         constexpr int ALG = decltype(alg_tag)::value;
         constexpr int PAR = decltype(par_tag)::value;
         constexpr bool LR = decltype(lring_tag)::value;
         constexpr uint32_t RO = PAR ? static_cast<uint32_t>(kFastStride) : 0u;
         constexpr uint32_t WO = PAR ? 0u : static_cast<uint32_t>(kFastStride);
         const uint32_t b = task_one_trial<CSR, LPT, ALG, !CSR_LDS, PAR ? kFieldFast1 : kFieldFast0, LR>(
-            v, own, nullptr, &own_fast, &own_in, lring, sub, static_cast<uint32_t>(q), tau, i0t, smem + RO,
-            k0, k1, st);
+            v, own, nullptr, &own_fast, &own_in, lring, sub, static_cast<uint32_t>(q), tau, i0t, close_d, smem + RO,
+            k0, k1, ALG != kAlgPeriod && gated, B, keys, st);
         unsigned char *to = smem + WO + own.base;
         if constexpr (P == 2) {
             const uint32_t m = b ^ 0x0101u;
@@ -894,12 +989,14 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
             auto run_fast = [&](auto lring_tag) __attribute__((always_inline)) {
                 int32_t t = a.t_begin, s = 0, left = (a.t_end - a.t_begin) * nsub;
                 auto half = [&](auto par_tag) __attribute__((always_inline)) {
-                    const float i0t = a.i0[t];
+                    const float i0t = load_uniform(a.i0 + t);
+                    const float close_d = fabsf(i0t) <= a.i0_lim ? kCloseD : __builtin_inff();
                     uint32_t k0 = a.k0, k1 = a.k1;
                     asm volatile("" : "+s"(k0), "+s"(k1));
                     const uint32_t tau = static_cast<uint32_t>(t) * static_cast<uint32_t>(nsub) +
                                          static_cast<uint32_t>(s);
-                    if (owns) fast_step(alg_tag, par_tag, lring_tag, tau, i0t, k0, k1);
+                    const StepBlocks B = step_blocks<LPT>(tau, static_cast<uint32_t>(q), sub, ALG != kAlgPeriod && gated, k0, k1);
+                    if (owns) fast_step(alg_tag, par_tag, lring_tag, tau, i0t, close_d, k0, k1, B);
                     __syncthreads();
                     if (++s == nsub) {
                         s = 0;
@@ -927,7 +1024,8 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
         }
     }
     for (int32_t t = a.t_begin; t < a.t_end; ++t) {
-        const float i0t = a.i0[t];
+        const float i0t = load_uniform(a.i0 + t);
+        const float close_d = fabsf(i0t) <= a.i0_lim ? kCloseD : __builtin_inff();
         // the key, opaque to the optimiser at every step: the Philox key
         // schedule is then formed on the scalar unit where it is used rather
         // than hoisted out of the loop into registers that spill
@@ -936,14 +1034,15 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
         for (int32_t s = 0; s < nsub; ++s) {
         const uint32_t tau = static_cast<uint32_t>(t) * static_cast<uint32_t>(nsub) + static_cast<uint32_t>(s);
         if constexpr (TPW == 1) {
+            const StepBlocks B = step_blocks<LPT>(tau, static_cast<uint32_t>(q), sub, ALG != kAlgPeriod && gated, k0, k1);
             if (resident) {
                 if (owns)
-                    one_trial_step(alg_tag, std::true_type{}, own, own_edges, &own_in, tau, i0t, k0, k1, cur, nxt);
+                    one_trial_step(alg_tag, std::true_type{}, own, own_edges, &own_in, tau, i0t, close_d, k0, k1, B, cur, nxt);
             } else {
                 // the LPT lanes of a task share its slot, so they enter and leave together
-                for (int32_t slot = threadIdx.x / LPT; slot < tasks; slot += BLOCK / LPT)
+                for (int32_t slot = lane_slot<LPT>(); slot < tasks; slot += BLOCK / LPT)
                     one_trial_step(alg_tag, std::false_type{}, load_task<LPT>(v, v.order[slot], sub),
-                                   nullptr, nullptr, tau, i0t, k0, k1, cur, nxt);
+                                   nullptr, nullptr, tau, i0t, close_d, k0, k1, B, cur, nxt);
             }
         } else {
             for (int32_t slot = threadIdx.x; slot < tasks; slot += BLOCK)
@@ -971,7 +1070,8 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
         if (lds_ring) {
             const int32_t al = a.alpha;
             const size_t g0 = static_cast<size_t>(q >> 2) * n4 * al;
-            for (int32_t x = threadIdx.x; x < n4 * al; x += BLOCK) a.ring[(g0 + x) * 4 + (q & 3)] = lring[x];
+            for (int32_t x = threadIdx.x; x < n4 * al; x += BLOCK)
+                a.ring[(g0 + x) * 4 + (q & 3)] = lring[x % al * n4 + x / al];
         }
         if (owns && a.xs != nullptr) {
             const size_t row0 = static_cast<size_t>(q >> 2) * n4 + own.base;
