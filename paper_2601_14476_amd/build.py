@@ -20,7 +20,7 @@ OBJDIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libpsa.so")
 
 SOURCES = [
-    "anneal_batch.hip", "anneal.hip", "ell.hip", "dense.hip", "kernels.hip", "abi.cpp", "graph.cpp", "batch.cpp", "server.cpp",
+    "anneal_batch.hip", "anneal.hip", "ell.hip", "ahead.hip", "dense.hip", "kernels.hip", "abi.cpp", "graph.cpp", "batch.cpp", "server.cpp",
     "host_params.cpp", "tune.cpp", "noalloc.hip", "period.hip",
 ]
 

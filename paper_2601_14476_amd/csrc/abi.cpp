@@ -369,6 +369,7 @@ void ctx_release(psa_ctx *ctx) {
     if (ctx->d_batch_table) (void)hipFree(ctx->d_batch_table);
     if (ctx->d_energy_table) (void)hipFree(ctx->d_energy_table);
     if (ctx->d_batch_work) (void)hipFree(ctx->d_batch_work);
+    if (ctx->d_ahead) (void)hipFree(ctx->d_ahead);
     if (ctx->d_dense_table) (void)hipFree(ctx->d_dense_table);
     if (ctx->d_dense_work) (void)hipFree(ctx->d_dense_work);
     for (const auto &dg : ctx->dense_graph_cache) (void)hipGraphExecDestroy(dg.exec);
@@ -518,6 +519,34 @@ namespace {
 // Body of psa_job_create: validate, upload the schedule and factors, plan
 // the launch, set the initial spins.  Device arrays come from `arena` when
 // given (then the job borrows them), else from fresh allocations.
+// Whether a run stepped alone draws its thresholds ahead of its steps: plain
+// pSA of few trials on a graph the bit rows were built for (at most 4,032
+// p-bits, sums of |J| at most 126).  Each further bound is where the drawing
+// stops being exact or free (us per step here and without, timing gate):
+//   I0 lambda in [2^-12, 2^60]: the decision is then monotone in the field;
+//   trials <= half the compute units, the others draw (250 p-bits of degree 6,
+//   128 trials 0.41 / 0.83; 1,000 of degree 6 0.91 / 1.17); with two p-bits
+//   per lane (1,025 to 2,048) 7 / 16 of them, since the sweep without is then
+//   at its best (2,000 of degree 6: 100 trials 1.00 / 1.23, 128 1.38 / 1.35);
+//   past 2,048 p-bits a mean degree of 16, since each lane's four rows then
+//   outgrow its registers (4,000 p-bits: 2.38 / 2.72 at 6, 7.1 / 6.3 at 24, 19
+//   / 13 at 60; 2,000 at 60 8.8 / 53).
+bool ahead_fits(const psa_ctx *ctx, const psa_graph *g, const psa_run_desc &d, const std::vector<float> &i0,
+                const std::vector<float> &lam, const std::vector<float> &dlt) {
+    if (d.algorithm != PSA_ALG_PSA || d.t_res != 0 || d.trials_per_group != 0 || d.steps < psa::kAheadMinSteps)
+        return false;
+    const int32_t n = g->info.n, units = ctx->num_cu;
+    if (!g->dev.be || 16 * static_cast<int64_t>(d.trials) > (n > 1024 && n <= 2048 ? 7 : 8) * static_cast<int64_t>(units) ||
+        (n > 2048 && g->dev.nnz > 16 * static_cast<int64_t>(n)))
+        return false;
+    const auto i0_mm = std::minmax_element(i0.begin(), i0.end());
+    const auto lam_mm = std::minmax_element(lam.begin(), lam.end());
+    if (!(*i0_mm.first > 0.0f && *lam_mm.first > 0.0f && *i0_mm.first * *lam_mm.first >= 0x1p-12f &&
+          *i0_mm.second <= 0x1p30f && *lam_mm.second <= 0x1p30f))
+        return false;
+    return std::all_of(dlt.begin(), dlt.end(), [](float x) { return std::fabs(x) <= 0x1p20f; });
+}
+
 psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
                       const psa_run_desc *desc, Arena *arena, psa_job **out) {
     if (!ctx || !g || !desc || !out) {
@@ -705,6 +734,8 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
     }
     j->run.i0_lim = static_cast<float>(std::min(max_prod > 0.0 ? psa::kEstimateLimit / max_prod : 1e30,
                                                 max_lam > 0.0 ? 1e30 / max_lam : 1e30));
+    j->plan.ahead = !j->plan.dense && !arena && desc->lanes_per_task == 0 && desc->block == 0 &&
+                    ahead_fits(ctx, g, *desc, i0, lam, dlt);
     // per-p-bit arrays padded to n4: padding p-bits never fire
     lam.resize(static_cast<size_t>(n4), 1.0f);
     dlt.resize(static_cast<size_t>(n4), 0.0f);
@@ -846,6 +877,22 @@ psa_status clone_job_for_timing(psa_job *src, psa_job **out) {
     return PSA_OK;
 }
 
+// Whether these steps of a job stepped alone draw their thresholds ahead: not
+// for few steps, nor in a capture (a replay could meet another job's launches
+// on the context's buffer).
+bool ahead_now(psa_job *job, int32_t steps) {
+    psa_ctx *ctx = job->ctx;
+    if (!job->plan.ahead || steps < psa::kAheadMinSteps) return false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+    if (!ctx->d_ahead && hipMalloc(reinterpret_cast<void **>(&ctx->d_ahead), psa::kAheadBytes) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->d_ahead = nullptr;
+        return false;
+    }
+    return true;
+}
+
 }  // namespace psa
 
 extern "C" {
@@ -896,6 +943,10 @@ psa_status psa_job_step(psa_job *job, int32_t k) {
             PSA_HIP(psa::launch_period(job->ctx->stream, job->g->dev, job->run, job->pplan, job->d_prec,
                                        job->d_pcls, job->d_pcache, job->t, t_end),
                     "period sweep launch");
+        else if (psa::ahead_now(job, t_end - job->t))
+            PSA_HIP(psa::launch_ahead(job->ctx->stream, job->g->dev, job->run, job->ctx->d_ahead, psa::kAheadBytes,
+                                      job->ctx->num_cu, job->t, t_end),
+                    "anneal launch");
         else
             PSA_HIP(psa::launch_anneal(job->ctx->stream, job->g->dev, job->run, job->plan, job->d_order,
                                        job->t, t_end),

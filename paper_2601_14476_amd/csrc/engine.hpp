@@ -106,6 +106,12 @@ struct DevGraph {
     const uint32_t *e4 = nullptr, *e1 = nullptr, *e1j = nullptr;
     int32_t e4_mode = -1;              // kEll*: four-trial sums, -1: none
     int32_t ell_groups = 0;            // wofs[waves]
+    // rows of the sweep over spin bits (ahead.hip), or null: p-bits in the
+    // order border (longest rows first), 64 to a wavefront, every row of a
+    // wavefront padded to the same even count; be [bofs[waves]][64]; with at
+    // most 1,024 p-bits and weights +-1 also as masks bm [4 waves][64 waves]
+    const int32_t *border = nullptr, *bofs = nullptr;
+    const uint32_t *be = nullptr, *bm = nullptr;
     const int32_t *h = nullptr;        // [n4]
     int64_t w2 = 0;                    // sum_i sum_j J_ij = 2 sum_{i<j} J_ij
 };
@@ -158,6 +164,7 @@ struct AnnealPlan {
     int32_t csr = kCsrPair;   // edge encoding read by the kernel
     int32_t csr_lds = 0;      // 1: CSR, biases and per-p-bit factors staged in LDS
     int32_t ell = 0;          // 1: streaming sweep over the graph's ELL rows
+    int32_t ahead = 0;        // 1: a job stepped alone draws its thresholds ahead (ahead.hip)
     int32_t block = 256;      // threads per workgroup
     int32_t grid = 0;         // workgroups
     size_t lds_bytes = 0;     // dynamic LDS per workgroup
@@ -365,6 +372,19 @@ hipError_t launch_anneal(hipStream_t stream, const DevGraph &g, const DevRun &ru
                          int32_t t_end);
 // Streaming sweep of one run (ell.hip): plan.ell set.
 hipError_t launch_ell(hipStream_t stream, const AnnealArgs &args, const AnnealPlan &plan, int32_t e4_mode);
+// Steps t_begin .. t_end-1 of a run planned `ahead`, its thresholds through
+// buf (two halves, a chunk of steps each).
+constexpr int32_t kAheadMaxN = 4032;      // p-bits: four per lane, rows of words in 16-bit addresses
+constexpr int32_t kAheadMaxRow = 126;     // sum_j |J_ij|: counts and thresholds in 7 bits
+constexpr int32_t kAheadChunk = 256;      // steps of a launch at most
+constexpr int32_t kAheadMinSteps = 64;    // fewer steps take the other sweeps
+constexpr size_t kAheadBytes = size_t{64} << 20;
+hipError_t launch_ahead(hipStream_t stream, const DevGraph &g, const DevRun &run, uint8_t *buf, size_t buf_bytes,
+                        int32_t num_cu, int32_t t_begin, int32_t t_end);
+// Fill a graph's bit rows (be, and bm where not null) from its CSR.
+hipError_t launch_build_bit_rows(hipStream_t stream, int32_t n, int32_t bw, const int32_t *row_ptr, const int32_t *col,
+                                 const int32_t *val, const int32_t *border, const int32_t *place, const int32_t *bofs,
+                                 uint32_t *be, uint32_t *bm);
 // Fill a graph's ELL rows (e4, e1, e1j where not null) from its CSR.
 hipError_t launch_build_ell(hipStream_t stream, int32_t waves, int32_t tasks, int32_t n4, const int32_t *row_ptr,
                             const int32_t *col, const int32_t *val, const int32_t *gorder, const int32_t *wofs,
@@ -494,16 +514,28 @@ struct HostGraph {
     std::vector<int32_t> gorder, wofs;
     int32_t e4_mode = -1;
     std::vector<int32_t> absrow;  // [n4] sum_j |J_ij|
+    // rows of the sweep over spin bits: p-bits by position and back, wavefront
+    // offsets; empty: none
+    std::vector<int32_t> border, place, bofs;
     void drop_ell() {
         gorder.clear();
         wofs.clear();
         e4_mode = -1;
+        border.clear();
+        place.clear();
+        bofs.clear();
+    }
+    // words of the bit rows' masks
+    size_t mask_words() const {
+        return info.unit_weights && n <= 1024 && !bofs.empty() ? 256 * (bofs.size() - 1) * (bofs.size() - 1) : 0;
     }
     // device bytes of the ELL rows and the arrays they are found through
     size_t ell_bytes() const {
         if (wofs.empty()) return 0;
+        const size_t bits = bofs.empty() ? 0 : border.size() + place.size() + bofs.size() +
+                                                static_cast<size_t>(bofs.back()) * 64 + mask_words();
         const size_t pairs = static_cast<size_t>(wofs.back()) * 64 * 16;
-        return (gorder.size() + wofs.size()) * 4 + pairs * (1 + (info.unit_weights ? 0 : 1) + (e4_mode >= 0 ? 2 : 0));
+        return (gorder.size() + wofs.size() + bits) * 4 + pairs * (1 + (info.unit_weights ? 0 : 1) + (e4_mode >= 0 ? 2 : 0));
     }
 };
 psa_status host_graph_from_edges(int32_t n, int64_t m, const int32_t *u, const int32_t *v,
@@ -595,6 +627,9 @@ struct psa_ctx {
     void *d_energy_table = nullptr;
     size_t energy_table_cap = 0;
     std::vector<psa::EnergyJob> h_energy_table;
+    // thresholds of the launches that draw them ahead, kAheadBytes, made at
+    // the first step that wants it (launches on `stream` only)
+    uint8_t *d_ahead = nullptr;
     // dense-path launches run on a second stream, joined with events
     hipStream_t stream2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -647,6 +682,7 @@ struct psa_graph {
     uint16_t *d_ux16 = nullptr;
     int32_t *d_gorder = nullptr, *d_wofs = nullptr;
     uint32_t *d_e4 = nullptr, *d_e1 = nullptr, *d_e1j = nullptr;
+    int32_t *d_bits = nullptr;  // border, place, bofs, be, bm
     std::vector<int32_t> row_ptr_host;  // [n4+4]
     std::vector<int32_t> h_host;        // [n4]
     std::vector<int32_t> gorder_host;   // task order of the ELL rows

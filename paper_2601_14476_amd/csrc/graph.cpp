@@ -99,6 +99,29 @@ void plan_ell_rows(HostGraph *g, const std::vector<int32_t> &val) {
         g->e4_mode = max_row <= 255 ? (g->info.unit_weights ? 0 : 1) : (max_row <= 65535 && max_mag <= 8191 ? 2 : -1);
 }
 
+// Rows of the sweep over spin bits (ahead.hip): the p-bits, longest rows
+// first, and the wavefronts' offsets.  Left empty for more p-bits or larger
+// sums of |J| than it takes.
+void plan_bit_rows(HostGraph *g) {
+    if (g->wofs.empty() || g->n > kAheadMaxN) return;
+    for (int32_t i = 0; i < g->n; ++i)
+        if (g->absrow[i] > kAheadMaxRow) return;
+    std::vector<int32_t> count(static_cast<size_t>(g->max_degree) + 2, 0);
+    auto degree = [&](int32_t i) { return g->rp32[i + 1] - g->rp32[i]; };
+    for (int32_t i = 0; i < g->n; ++i) ++count[static_cast<size_t>(g->max_degree - degree(i)) + 1];
+    for (size_t d = 1; d < count.size(); ++d) count[d] += count[d - 1];
+    g->border.resize(static_cast<size_t>(g->n));
+    g->place.resize(static_cast<size_t>(g->n));
+    for (int32_t i = 0; i < g->n; ++i) {
+        g->place[i] = count[static_cast<size_t>(g->max_degree - degree(i))]++;
+        g->border[g->place[i]] = i;
+    }
+    const int32_t waves = (g->n + 63) / 64;
+    g->bofs.assign(static_cast<size_t>(waves) + 1, 0);
+    for (int32_t w = 0; w < waves; ++w)
+        g->bofs[w + 1] = g->bofs[w] + (degree(g->border[64 * static_cast<size_t>(w)]) + 1) / 2 * 2;
+}
+
 // Statistics, bounds, padding and packed encodings of a canonical CSR.
 psa_status finish_host_graph(int32_t n, const std::vector<int64_t> &row_ptr,
                              std::vector<int32_t> &&col, std::vector<int32_t> &&val,
@@ -176,6 +199,7 @@ psa_status finish_host_graph(int32_t n, const std::vector<int64_t> &row_ptr,
             g.ux16[p] = static_cast<uint16_t>(col[p] + (val[p] < 0 ? g.n4 : 0));
     }
     plan_ell_rows(&g, val);
+    plan_bit_rows(&g);
     g.col = std::move(col);
     g.val = std::move(val);
     *out = std::move(g);
@@ -218,7 +242,8 @@ void graph_release(psa_graph *g) {
                     static_cast<void *>(g->d_pk32), static_cast<void *>(g->d_e4),
                     static_cast<void *>(g->d_ux16), static_cast<void *>(g->d_dense),
                     static_cast<void *>(g->d_e1), static_cast<void *>(g->d_e1j),
-                    static_cast<void *>(g->d_gorder), static_cast<void *>(g->d_wofs)})
+                    static_cast<void *>(g->d_gorder), static_cast<void *>(g->d_wofs),
+                    static_cast<void *>(g->d_bits)})
         if (p) (void)hipFree(p);
     psa_ctx *ctx = g->retained ? g->ctx : nullptr;
     delete g;
@@ -467,6 +492,24 @@ psa_status upload_graph(psa_ctx *ctx, HostGraph &&hg, psa_graph **out) {
         g->dev.ell_groups = hg.wofs.back();
         g->gorder_host = std::move(hg.gorder);
         g->absrow_host = std::move(hg.absrow);
+    }
+    if (g->dev.e1 && !hg.bofs.empty()) {
+        // one allocation: order, places, offsets (uploaded), then be and bm
+        std::vector<int32_t> head(hg.border);
+        head.insert(head.end(), hg.place.begin(), hg.place.end());
+        head.insert(head.end(), hg.bofs.begin(), hg.bofs.end());
+        const size_t entries = static_cast<size_t>(hg.bofs.back()) * 64, top = head.size();
+        if ((st = reserve(&g->d_bits, top + entries + hg.mask_words(), &g->dev_bytes)) != PSA_OK) return st;
+        PSA_HIP(hipMemcpy(g->d_bits, head.data(), top * sizeof(int32_t), hipMemcpyHostToDevice), "graph upload");
+        const size_t n = static_cast<size_t>(hg.n);
+        uint32_t *be = reinterpret_cast<uint32_t *>(g->d_bits) + top, *bm = hg.mask_words() > 0 ? be + entries : nullptr;
+        PSA_HIP(launch_build_bit_rows(ctx->stream, hg.n, static_cast<int32_t>(hg.bofs.size()) - 1, g->d_row_ptr, g->d_col,
+                                      g->d_val, g->d_bits, g->d_bits + n, g->d_bits + 2 * n, be, bm),
+                "bit rows");
+        g->dev.border = g->d_bits;
+        g->dev.bofs = g->d_bits + 2 * n;
+        g->dev.be = be;
+        g->dev.bm = bm;
     }
     g->dev.n = hg.n;
     g->dev.n4 = hg.n4;
