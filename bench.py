@@ -41,9 +41,13 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# Algorithmic 32-bit lane-operations per p-bit update: the fewest VALU
-# instructions the method's arithmetic takes on gfx950 (a lower bound on what
-# a kernel issues).  One Philox4x32-10 block = 10 rounds x (2 32x32->64
+# Algorithmic 32-bit lane-operations per p-bit update: the VALU instructions
+# the method's arithmetic takes on gfx950 with every random block drawn whole
+# on the vector unit and the decision in the tanh form.  The sweeps now issue
+# fewer (the blocks' uniform rounds on the scalar unit, 34 vector instructions
+# a block; a signed logistic decision of 6 operations instead of r map and
+# decision's 15), so the fraction may pass 1: it is a figure for comparing
+# runs, and the measured issue rate says how busy the chip is.  One Philox4x32-10 block = 10 rounds x (2 32x32->64
 # multiplies, one instruction each, + 2 three-input XOR) = 40, shared by the
 # 4 p-bits of a task; the timing gate needs a second block.
 PHILOX_BLOCK_OPS = 40
@@ -91,7 +95,7 @@ ISSUE_TABLE = os.path.join(ROOT, "profiles", "valu_issue_by_workload.md")
 # per-update arithmetic and the argument structures it reads (and, for the
 # dense step, the host file that cuts its launch into work items).
 KERNEL_SOURCES = {
-    "anneal_kernel": ["anneal.hip", "device_math.hpp", "engine.hpp"],
+    "anneal_kernel": ["anneal.hip", "sweep.hpp", "ell.hip", "ell_sweep.hpp", "ahead.hip", "device_math.hpp", "engine.hpp"],
     "dense_step_kernel": ["dense.hip", "device_math.hpp", "engine.hpp", "batch.cpp"],
     "period_kernel": ["period.hip", "device_math.hpp", "engine.hpp"],
 }

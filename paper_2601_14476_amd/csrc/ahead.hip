@@ -434,25 +434,24 @@ __global__ __launch_bounds__(1024) void ahead_kernel(AheadArgs a) {
         draw_thresholds(a, b - a.consumers, static_cast<int32_t>(gridDim.x) - a.consumers);
 }
 
-// Workgroup wv writes the entries of positions 64 wv .. 64 wv + 63: the
+// Workgroup (wv, c) writes kBuildEntries entries of positions 64 wv .. 64 wv +
+// 63 (longest rows first, so the first wavefront's are the most): the
 // neighbour's row of words (1 - u for J < 0) as a byte address << 16, |J| << 5
-// and its bit; 0 (the zero row) past a row's end.  bm (where not null): words
-// 2 j and 2 j + 1 of a position, 64 bw apart, hold its neighbours among
-// positions 32 j .. 32 j + 31 and those with J < 0.
+// and its bit; 0 (the zero row) past a row's end.
+constexpr int32_t kBuildEntries = 4;
 __global__ __launch_bounds__(64) void build_bit_rows_kernel(int32_t n, int32_t bw, const int32_t *__restrict__ row_ptr,
                                                             const int32_t *__restrict__ col,
                                                             const int32_t *__restrict__ val,
                                                             const int32_t *__restrict__ border,
                                                             const int32_t *__restrict__ place,
-                                                            const int32_t *__restrict__ bofs, uint32_t *__restrict__ be,
-                                                            uint32_t *__restrict__ bm) {
+                                                            const int32_t *__restrict__ bofs, uint32_t *__restrict__ be) {
     const int32_t wv = static_cast<int32_t>(blockIdx.x), lane = static_cast<int32_t>(threadIdx.x);
     const int32_t pos = 64 * wv + lane;
     const int32_t i = pos < n ? border[pos] : 0;
     const int32_t b = pos < n ? row_ptr[i] : 0, e = pos < n ? row_ptr[i + 1] : 0;
-    if (bm)
-        for (int32_t j = 0; j < 4 * bw; ++j) bm[j * 64 * bw + pos] = 0u;
-    for (int32_t g = bofs[wv]; g < bofs[wv + 1]; ++g) {
+    const int32_t g0 = bofs[wv] + static_cast<int32_t>(blockIdx.y) * kBuildEntries;
+    const int32_t g1 = min(g0 + kBuildEntries, bofs[wv + 1]);
+    for (int32_t g = g0; g < g1; ++g) {
         const int32_t x = b + (g - bofs[wv]);
         uint32_t word = 0u;
         if (x < e) {
@@ -460,23 +459,40 @@ __global__ __launch_bounds__(64) void build_bit_rows_kernel(int32_t n, int32_t b
             const int32_t row = 1 + (p >> 5) + (J < 0 ? 2 * bw : 0);
             word = static_cast<uint32_t>(row * kRowBytes) << 16 | static_cast<uint32_t>(J < 0 ? -J : J) << 5 |
                    static_cast<uint32_t>(p & 31);
-            if (bm) {  // this thread's own words
-                bm[(p >> 5) * 2 * 64 * bw + pos] |= 1u << (p & 31);
-                if (J < 0) bm[((p >> 5) * 2 + 1) * 64 * bw + pos] |= 1u << (p & 31);
-            }
         }
         be[static_cast<size_t>(g) * 64 + lane] = word;
     }
 }
 
+// Workgroup wv writes the masks of positions 64 wv .. 64 wv + 63 from their
+// entries, collected in LDS: words 2 j and 2 j + 1 of a position, 64 bw apart,
+// hold its neighbours among positions 32 j .. 32 j + 31 and those with J < 0.
+__global__ __launch_bounds__(64) void build_masks_kernel(int32_t bw, const int32_t *__restrict__ bofs,
+                                                         const uint32_t *__restrict__ be, uint32_t *__restrict__ bm) {
+    __shared__ uint32_t word[64][64];
+    const int32_t wv = static_cast<int32_t>(blockIdx.x), lane = static_cast<int32_t>(threadIdx.x);
+    for (int32_t j = 0; j < 4 * bw; ++j) word[j][lane] = 0u;  // each lane its own column
+    for (int32_t g = bofs[wv]; g < bofs[wv + 1]; ++g) {
+        const uint32_t e = be[static_cast<size_t>(g) * 64 + lane];
+        if (e == 0u) continue;  // past the row's end
+        const int32_t row = static_cast<int32_t>(e >> 16) / kRowBytes - 1;
+        const int32_t neg = row >= 2 * bw ? 1 : 0, j = row - 2 * bw * neg;
+        word[2 * j][lane] |= 1u << (e & 31u);
+        if (neg) word[2 * j + 1][lane] |= 1u << (e & 31u);
+    }
+    for (int32_t j = 0; j < 4 * bw; ++j) bm[j * 64 * bw + 64 * wv + lane] = word[j][lane];
+}
+
 }  // namespace
 
-hipError_t launch_build_bit_rows(hipStream_t stream, int32_t n, int32_t bw, const int32_t *row_ptr, const int32_t *col,
+hipError_t launch_build_bit_rows(hipStream_t stream, int32_t n, int32_t bw, int32_t most, const int32_t *row_ptr, const int32_t *col,
                                  const int32_t *val, const int32_t *border, const int32_t *place, const int32_t *bofs,
                                  uint32_t *be, uint32_t *bm) {
-    if (bw <= 0) return hipSuccess;
-    hipLaunchKernelGGL(build_bit_rows_kernel, dim3(bw), dim3(64), 0, stream, n, bw, row_ptr, col, val, border, place, bofs,
-                       be, bm);
+    if (bw <= 0 || most <= 0) return hipSuccess;
+    const int32_t parts = (most + kBuildEntries - 1) / kBuildEntries;
+    hipLaunchKernelGGL(build_bit_rows_kernel, dim3(bw, parts), dim3(64), 0, stream, n, bw, row_ptr, col, val, border,
+                       place, bofs, be);
+    if (bm) hipLaunchKernelGGL(build_masks_kernel, dim3(bw), dim3(64), 0, stream, bw, bofs, be, bm);
     return hipGetLastError();
 }
 

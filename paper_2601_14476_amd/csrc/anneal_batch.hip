@@ -15,7 +15,7 @@ namespace {
 // variants share one launch (dynamic LDS = the largest any item needs).
 // ---------------------------------------------------------------------------
 template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void anneal_batch_kernel(const BatchJob *__restrict__ jobs,
+__global__ __launch_bounds__(BLOCK, 4) void anneal_batch_kernel(const BatchJob *__restrict__ jobs,
                                                              const int2 *__restrict__ work) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int2 w = work[blockIdx.x];

@@ -112,15 +112,22 @@ constexpr double kDenseStepFloorSeconds = 4.2e-6;    // fp4 couplings
 constexpr double kDenseI8StepFloorSeconds = 8.0e-6;  // int8
 
 double csr_step_seconds(const DevGraph &g, const DevRun &run, const AnnealPlan &plan) {
-    if (plan.ell) {
+    if (plan.ell && !(run.t_res > 0 && plan.tpw == 1)) {  // (period classes have a sweep of their own)
         // streaming sweeps: lane-operations per update fitted to runs of
         // degree 4 to 50 (four trials 35 + 4 d, one trial 50 + 7 d), on the
-        // compute units its workgroups reach
+        // compute units its workgroups reach, in whole rounds of them; TApSA
+        // windows and SpSA inputs in device memory at about 4 TB/s, 16 bytes
+        // for the 4 a one-trial workgroup uses (15,013 p-bits of degree 26, 366
+        // trials, TApSA: 207 us per step, on the dense path 101)
         const double deg = g.nnz / static_cast<double>(std::max(g.n, 1));
         const double wgs = plan.tpw == 4 ? run.t4 / 4 : run.trials;
         const double ops = plan.tpw == 4 ? 35.0 + 4.0 * deg : 50.0 + 7.0 * deg;
-        return std::max(kCsrStepFloorSeconds, static_cast<double>(g.n) * run.trials * ops /
-                                                  (kValuOpsPerSecond * std::min(1.0, wgs / 256.0)));
+        const double rounds = wgs * plan.block / (256.0 * 1024.0);
+        const double words = run.ring ? run.alpha : (run.xs ? 2.0 : 0.0);
+        const double state = words * (plan.tpw == 4 ? 4.0 : 16.0) / 4.0e12;
+        const double share = rounds > 1.0 ? rounds / std::ceil(rounds) : std::min(1.0, wgs / 256.0);
+        return std::max(kCsrStepFloorSeconds,
+                        static_cast<double>(g.n) * run.trials * (ops / (kValuOpsPerSecond * share) + state));
     }
     // lane-ops per update: RNG, activation and decision (about 60), plus a
     // gather per edge: a few ops from LDS, tens when the rows stream from

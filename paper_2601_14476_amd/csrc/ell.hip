@@ -20,8 +20,11 @@ __global__ __launch_bounds__(1024) void ell4_kernel(AnnealArgs a) {
     ell4_body<MODE>(a, static_cast<int32_t>(blockIdx.x), smem);
 }
 
-// Workgroup w writes the rows of wavefront w's 64 tasks: thread (lane, row p
-// of the lane's task) walks its row and pads it to the wavefront's length.
+// Workgroup (w, c) writes kBuildGroups pairs of entries of wavefront w's 64
+// tasks: thread (lane, row p of the lane's task) walks its part of the row and
+// pads it to the wavefront's length.  Bound by the latency of its gathers, so
+// rows are cut into parts.
+constexpr int32_t kBuildGroups = 4;
 __global__ __launch_bounds__(256) void build_ell_kernel(int32_t tasks, int32_t n4, const int32_t *__restrict__ row_ptr,
                                                         const int32_t *__restrict__ col,
                                                         const int32_t *__restrict__ val,
@@ -33,7 +36,8 @@ __global__ __launch_bounds__(256) void build_ell_kernel(int32_t tasks, int32_t n
     const int32_t slot = 64 * w + lane;
     const int32_t i = slot < tasks ? 4 * gorder[slot] + p : 0;
     const int32_t b = slot < tasks ? row_ptr[i] : 0, e = slot < tasks ? row_ptr[i + 1] : 0;
-    for (int32_t g = wofs[w]; g < wofs[w + 1]; ++g) {
+    const int32_t g0 = wofs[w] + static_cast<int32_t>(blockIdx.y) * kBuildGroups, g1 = min(g0 + kBuildGroups, wofs[w + 1]);
+    for (int32_t g = g0; g < g1; ++g) {
         uint32_t idx[2], mag[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -69,11 +73,12 @@ hipError_t launch_ell(hipStream_t stream, const AnnealArgs &args, const AnnealPl
     return hipGetLastError();
 }
 
-hipError_t launch_build_ell(hipStream_t stream, int32_t waves, int32_t tasks, int32_t n4, const int32_t *row_ptr,
+hipError_t launch_build_ell(hipStream_t stream, int32_t waves, int32_t most, int32_t tasks, int32_t n4, const int32_t *row_ptr,
                             const int32_t *col, const int32_t *val, const int32_t *gorder, const int32_t *wofs,
                             uint32_t *e4, uint32_t *e1, uint32_t *e1j) {
-    if (waves <= 0) return hipSuccess;
-    hipLaunchKernelGGL(build_ell_kernel, dim3(waves), dim3(256), 0, stream, tasks, n4, row_ptr, col, val, gorder, wofs,
+    if (waves <= 0 || most <= 0) return hipSuccess;
+    hipLaunchKernelGGL(build_ell_kernel, dim3(waves, (most + kBuildGroups - 1) / kBuildGroups), dim3(256),
+                       0, stream, tasks, n4, row_ptr, col, val, gorder, wofs,
                        e4, e1, e1j);
     return hipGetLastError();
 }

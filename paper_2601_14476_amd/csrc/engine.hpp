@@ -381,12 +381,14 @@ constexpr int32_t kAheadMinSteps = 64;    // fewer steps take the other sweeps
 constexpr size_t kAheadBytes = size_t{64} << 20;
 hipError_t launch_ahead(hipStream_t stream, const DevGraph &g, const DevRun &run, uint8_t *buf, size_t buf_bytes,
                         int32_t num_cu, int32_t t_begin, int32_t t_end);
-// Fill a graph's bit rows (be, and bm where not null) from its CSR.
-hipError_t launch_build_bit_rows(hipStream_t stream, int32_t n, int32_t bw, const int32_t *row_ptr, const int32_t *col,
+// Fill a graph's bit rows (be, and bm where not null) from its CSR; most: entries
+// of the longest wavefront, the first.
+hipError_t launch_build_bit_rows(hipStream_t stream, int32_t n, int32_t bw, int32_t most, const int32_t *row_ptr, const int32_t *col,
                                  const int32_t *val, const int32_t *border, const int32_t *place, const int32_t *bofs,
                                  uint32_t *be, uint32_t *bm);
-// Fill a graph's ELL rows (e4, e1, e1j where not null) from its CSR.
-hipError_t launch_build_ell(hipStream_t stream, int32_t waves, int32_t tasks, int32_t n4, const int32_t *row_ptr,
+// Fill a graph's ELL rows (e4, e1, e1j where not null) from its CSR; most: pairs
+// of entries of the longest wavefront, the first.
+hipError_t launch_build_ell(hipStream_t stream, int32_t waves, int32_t most, int32_t tasks, int32_t n4, const int32_t *row_ptr,
                             const int32_t *col, const int32_t *val, const int32_t *gorder, const int32_t *wofs,
                             uint32_t *e4, uint32_t *e1, uint32_t *e1j);
 void fill_anneal_args(AnnealArgs *a, const DevGraph &g, const DevRun &run, const int32_t *order,

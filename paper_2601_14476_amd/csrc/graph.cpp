@@ -480,7 +480,7 @@ psa_status upload_graph(psa_ctx *ctx, HostGraph &&hg, psa_graph **out) {
         if ((st = reserve(&g->d_e1, words, &g->dev_bytes)) != PSA_OK) return st;
         if (!hg.info.unit_weights && (st = reserve(&g->d_e1j, words, &g->dev_bytes)) != PSA_OK) return st;
         if (hg.e4_mode >= 0 && (st = reserve(&g->d_e4, 2 * words, &g->dev_bytes)) != PSA_OK) return st;
-        PSA_HIP(launch_build_ell(ctx->stream, static_cast<int32_t>(hg.wofs.size()) - 1, hg.n4 / 4, hg.n4, g->d_row_ptr,
+        PSA_HIP(launch_build_ell(ctx->stream, static_cast<int32_t>(hg.wofs.size()) - 1, hg.wofs[1], hg.n4 / 4, hg.n4, g->d_row_ptr,
                                  g->d_col, g->d_val, g->d_gorder, g->d_wofs, g->d_e4, g->d_e1, g->d_e1j),
                 "ELL rows");
         g->dev.gorder = g->d_gorder;
@@ -503,7 +503,7 @@ psa_status upload_graph(psa_ctx *ctx, HostGraph &&hg, psa_graph **out) {
         PSA_HIP(hipMemcpy(g->d_bits, head.data(), top * sizeof(int32_t), hipMemcpyHostToDevice), "graph upload");
         const size_t n = static_cast<size_t>(hg.n);
         uint32_t *be = reinterpret_cast<uint32_t *>(g->d_bits) + top, *bm = hg.mask_words() > 0 ? be + entries : nullptr;
-        PSA_HIP(launch_build_bit_rows(ctx->stream, hg.n, static_cast<int32_t>(hg.bofs.size()) - 1, g->d_row_ptr, g->d_col,
+        PSA_HIP(launch_build_bit_rows(ctx->stream, hg.n, static_cast<int32_t>(hg.bofs.size()) - 1, hg.bofs[1], g->d_row_ptr, g->d_col,
                                       g->d_val, g->d_bits, g->d_bits + n, g->d_bits + 2 * n, be, bm),
                 "bit rows");
         g->dev.border = g->d_bits;
