@@ -710,7 +710,9 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
             j->plan.dense = 1;  // too large for the LDS-resident sweep
         }
     }
-    if (path == PSA_PATH_DENSE || (path == PSA_PATH_AUTO && psa::prefer_dense(g, j->run, j->plan)))
+    psa::DevRun asked = j->run;
+    asked.t_res = desc->t_res;
+    if (path == PSA_PATH_DENSE || (path == PSA_PATH_AUTO && psa::prefer_dense(g, asked, j->plan)))
         j->plan.dense = 1;
     if (j->plan.dense && arena) {
         set_error("the run needs the dense path, which the static scratch does not hold");
