@@ -86,7 +86,8 @@ bool plan_anneal(const DevGraph &g, const DevRun &run, int32_t tpw_req, int32_t 
         // degree 6, 512 trials 2.9 and 3.7, 600 4.1 and 3.7; 4,000, 512 5.8 and
         // 6.0, 600 8.1 and 5.9; 250, 1,024 1.7 and 2.6, 2,048 2.8 and 2.8).
         AnnealPlan one;
-        if (ell_ok && g.e4_mode >= 0 && plan_anneal(g, run, 1, lpt_req, block_req, max_lds, num_cu, &one, nullptr))
+        const int32_t spread = tasks * 4 <= 1024 ? 4 : (tasks * 2 <= 1024 ? 2 : 1);
+        if (ell_ok && g.e4_mode >= 0 && plan_anneal(g, run, 1, lpt_req ? lpt_req : spread, block_req, max_lds, num_cu, &one, nullptr))
             p.tpw = static_cast<int64_t>(run.trials) * one.block > 2 * static_cast<int64_t>(num_cu) * 1024 ? 4 : 1;
         else
             p.tpw = (run.t4 / 4 >= num_cu) ? 4 : 1;
@@ -102,6 +103,16 @@ bool plan_anneal(const DevGraph &g, const DevRun &run, int32_t tpw_req, int32_t 
             p.lpt = lpt_req;
         else  // spread tasks over more lanes while the workgroup has lanes to spare
             p.lpt = tasks * 4 <= 1024 ? 4 : (tasks * 2 <= 1024 ? 2 : 1);
+        // but with workgroups to share the compute units, two lanes per task
+        // issue less for short rows, whose random blocks outweigh their sums,
+        // as long as two rows fit a lane's 32 cached slots (us per step with
+        // four and two: 364 p-bits of degree 4, 843 trials, SpSA 2.93 and 1.39;
+        // 1,000 of degree 6, 300 trials 2.17 and 1.37; 250 of degree 6, 300
+        // trials 0.89 and 0.88; 404 of mean degree 11, 466 trials 1.14 and 1.50;
+        // 263 of 18, 438 trials 1.16 and 2.23)
+        if (lpt_req == 0 && p.lpt == 4 && p.csr == kCsrUnit && g.nnz <= 8 * static_cast<int64_t>(g.n) && g.max_degree <= 16 &&
+            4 * static_cast<int64_t>(run.trials) > 5 * static_cast<int64_t>(num_cu))
+            p.lpt = 2;
         // (a lane that keeps its task's input-stage state and edges in
         // registers steps SpSA and TApSA faster: 3,000 p-bits of degree 6, 30
         // trials, TApSA 3.5 against 4.5 us per step)
