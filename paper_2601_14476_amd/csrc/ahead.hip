@@ -193,7 +193,8 @@ __device__ __forceinline__ void run_steps(const AheadArgs &a, int32_t k, unsigne
         rows[s] = a.be + static_cast<size_t>(b) * 64;
         // every load at once (at a clamped index), then the rest made the zero row
 #pragma unroll
-        for (int e = 0; e < kCached; ++e) ent[s][e] = rows[s][max(min(e, len[s] - 1), 0) * 64 + static_cast<int32_t>(lane)];
+        for (int e = 0; e < kCached; ++e)
+            ent[s][e] = a.be[static_cast<size_t>(bit_row_entry(b, len[s], e)) * 64 + lane];
 #pragma unroll
         for (int e = 0; e < kCached; ++e) {
             asm volatile("" : "+v"(ent[s][e]));

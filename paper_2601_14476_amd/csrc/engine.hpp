@@ -379,6 +379,14 @@ constexpr int32_t kAheadMaxRow = 126;     // sum_j |J_ij|: counts and thresholds
 constexpr int32_t kAheadChunk = 256;      // steps of a launch at most
 constexpr int32_t kAheadMinSteps = 64;    // fewer steps take the other sweeps
 constexpr size_t kAheadBytes = size_t{64} << 20;
+// Entry e of a row of the bit rows, as an index in units of 64 words into be:
+// of the wavefront's rows of len entries from b on, at most the last (the sweep
+// loads a fixed count and drops those past len).  A wavefront of empty rows
+// (they sort last, so b may be the end of be) reads entry 0, which every graph
+// with bit rows has.
+__host__ __device__ constexpr int32_t bit_row_entry(int32_t b, int32_t len, int32_t e) {
+    return len > 0 ? b + (e < len ? e : len - 1) : 0;
+}
 hipError_t launch_ahead(hipStream_t stream, const DevGraph &g, const DevRun &run, uint8_t *buf, size_t buf_bytes,
                         int32_t num_cu, int32_t t_begin, int32_t t_end);
 // Fill a graph's bit rows (be, and bm where not null) from its CSR; most: entries
