@@ -128,6 +128,12 @@ __device__ __forceinline__ float decision_distance(float v, uint32_t rword) {
     const float f = __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, rword, 9u));  // 1.0 | top 23 bits
     return __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(v) + 1.0f) + (f - 2.0f);
 }
+// Least magnitude of four distances.  minnum passes over a not-a-number: with
+// four of them the result is one and no `> close_d` holds; with fewer, close_d
+// is infinite (a schedule within i0_lim overflows nothing) and none holds either.
+__device__ __forceinline__ float least_of(const float (&d)[4]) {
+    return fminf(fminf(fminf(fabsf(d[0]), fabsf(d[1])), fabsf(d[2])), fabsf(d[3]));
+}
 // Bytes 0 and 1 (HALF 0) or 2 and 3 (HALF 1) all ones where lo or hi is
 // negative; the other bytes 0.
 template <int HALF>
@@ -327,7 +333,7 @@ __device__ __forceinline__ void ell4_steps(const AnnealArgs &a, int32_t q, unsig
 #pragma unroll
                             for (int p = 0; p < 4; ++p)
                                 d[h][p] = decision_distance(fmaf(ell4_count(sum, p, kk) + hd[p], ac[p], bc[p]), rw[p]);
-                            close = fminf(fminf(fminf(fabsf(d[h][0]), fabsf(d[h][1])), fabsf(d[h][2])), fabsf(d[h][3])) <= close_d;
+                            close = !(least_of(d[h]) > close_d);
                         } else {
                             uint32_t sw[4] = {0u, 0u, 0u, 0u};
                             if (ALG == kAlgSpsa && t > 0) {
@@ -607,7 +613,7 @@ __device__ __forceinline__ void ell1_steps(const AnnealArgs &a, int32_t q, unsig
                 if constexpr (ALG == kAlgPsa || ALG == kAlgPeriod) {
 #pragma unroll
                     for (int p = 0; p < 4; ++p) d[p] = decision_distance(i0t * fmaf(lh[p], p1[p], p2[p]), rw[p]);
-                    close = fminf(fminf(fminf(fabsf(d[0]), fabsf(d[1])), fabsf(d[2])), fabsf(d[3])) <= close_d;
+                    close = !(least_of(d) > close_d);
                 } else {
                     uint32_t sw[4] = {0u, 0u, 0u, 0u};
                     if (ALG == kAlgSpsa && t > 0) {
