@@ -729,13 +729,22 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
     for (int32_t i = 0; i < n && j->identity_factors; ++i)
         j->identity_factors = lam[i] == 1.0f && dlt[i] == 0.0f && thr[i] >= psa::kGateOneHost;
     double max_lam = 0.0, max_prod = 0.0;
+    bool subnormal = false;
     for (int32_t i = 0; i < n; ++i) {
         if (thr[i] < psa::kGateOneHost) j->run.gated = 1;
         max_lam = std::max(max_lam, std::fabs(static_cast<double>(lam[i])));
         max_prod = std::max(max_prod, std::fabs(static_cast<double>(lam[i]) * dlt[i]));
+        subnormal = subnormal || std::fpclassify(lam[i]) == FP_SUBNORMAL;
     }
-    j->run.i0_lim = static_cast<float>(std::min(max_prod > 0.0 ? psa::kEstimateLimit / max_prod : 1e30,
-                                                max_lam > 0.0 ? 1e30 / max_lam : 1e30));
+    // The estimate's exponent is I0 times a sum formed in floats, lambda times
+    // the field plus lambda delta, each times 2 log2 e: no I0 is within its
+    // bound where that sum may overflow, or where lambda, as a subnormal, has
+    // too few bits for the product with delta
+    const bool fits = psa::kTwoLog2eHost * (max_lam * std::max(g->info.max_abs_field, 2) + max_prod) <= 0x1p126;
+    j->run.i0_lim = fits && !subnormal
+                        ? static_cast<float>(std::min({max_prod > 0.0 ? psa::kEstimateLimit / max_prod : 1e30,
+                                                       max_lam > 0.0 ? 1e30 / max_lam : 1e30, 1e38}))
+                        : -1.0f;
     j->plan.ahead = !j->plan.dense && !arena && desc->lanes_per_task == 0 && desc->block == 0 &&
                     ahead_fits(ctx, g, *desc, i0, lam, dlt);
     // per-p-bit arrays padded to n4: padding p-bits never fire

@@ -120,7 +120,8 @@ __device__ __forceinline__ Words4 block_of_task(uint32_t m, const BlockPrefix &P
 // log2 e rounded once, sum and product once: relative errors of v move q by
 // less than 2^-22 (v q^2 2^v <= 0.33), and the rounding of P2 by 0.18 * 2^-24
 // |2 I0 lambda delta log2 e|, which the bound on |I0 lambda delta|
-// (kEstimateLimit) keeps below 2^-19.  Past |D| = kCloseD the sign is therefore tanh_f32's decision; the
+// (kEstimateLimit) keeps below 2^-19; where the sum in v may overflow no I0
+// passes.  Past |D| = kCloseD the sign is therefore tanh_f32's decision; the
 // rest evaluates tanh_f32.
 constexpr float kCloseD = 0x1p-17f;
 constexpr float kTwoLog2e = 0x1.715476p+1f;

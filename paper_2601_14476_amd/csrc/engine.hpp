@@ -139,7 +139,7 @@ struct DevRun {
     // (SpSA and TApSA: lambda_i, delta_i; float bits), thr24_i
     const uint32_t *pps = nullptr;
     int32_t gated = 0;                    // some p-bit has thr24 < 2^24
-    float i0_lim = 0.0f;                  // |I0| up to which the decision estimate's bound holds
+    float i0_lim = 0.0f;                  // |I0| up to which the decision estimate's bound holds; < 0: none
 };
 
 // How the persistent anneal kernel is launched for one run.

@@ -1,9 +1,12 @@
-"""Factors and schedules at the ends of the float range (they need only be
-finite) against the oracle, bit for bit."""
+"""Factors at the ends of the float range (lambda and delta need only be
+finite) against the oracle, bit for bit: products of a factor, the field bound
+and the decision's constants that overflow, subnormal factors, and schedules
+that overflow beside fields that are all zero."""
 import numpy as np
 import pytest
 
 import oracle
+from paper_2601_14476_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -49,6 +52,38 @@ def _check(psa, ctx, n, u, v, j, lam, delta, i0, h=None, gate=False, batch=False
     np.testing.assert_array_equal(job.read_spins(), ref)
     job.close()
     g.close()
+
+
+# (lambda, delta, I0): the exponent's factor 2 lambda log2 e past the float
+# range; in it, but not times the field; lambda delta past it, with I0 = 0 too;
+# subnormal lambda beside a huge delta
+FACTORS = {"lambda past the range": (6.5e37, 0.0, [2e-38, 1.5e-38, 3e-38]),
+           "lambda at the end": (3.4e38, 0.0, [1.2e-38, 2e-38, 5e-39]),
+           "lambda times the field": (1e37, 0.0, [3e-38, 1e-38, 6e-38]),
+           "lambda times half the field": (-2.5e37, 0.25, [2e-38, 1.3e-38]),
+           "lambda delta past the range": (1.0, 1.3e38, [0.0, 1e-38, 0.0, 5e-39]),
+           "lambda delta in double only": (1e30, 1e30, [0.0, 1e-45, 0.0]),
+           "subnormal lambda": (2.8e-45, 3e38, [1e6, 3e6, 2e6])}
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("name", FACTORS)
+@pytest.mark.parametrize("top", [1, 5])
+def test_factors_past_the_range(psa, ctx, shape, name, top):
+    lam, delta, i0 = FACTORS[name]
+    n, u, v, w = inputs.gnm(1501, 5000, 8)
+    j = (w * np.random.default_rng(2).integers(1, top + 1, w.size)).astype(np.int32)
+    _check(psa, ctx, n, u, v, j, lam, delta, i0, **SHAPES[shape])
+    _check(psa, ctx, n, u, v, j, lam, delta, i0, gate=True, batch=True, **SHAPES[shape])
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("rule", ["psa", "spsa", "tapsa"])
+def test_one_extreme_p_bit_in_each_task(psa, ctx, shape, rule):
+    n, u, v, w = inputs.gnm(1203, 4000, 4)
+    lam = np.ones(n, np.float32)
+    lam[::4] = 1e38
+    _check(psa, ctx, n, u, v, w, lam, 0.0, np.geomspace(1e-38, 1e-36, 5), rule=rule, **SHAPES[shape])
 
 
 @pytest.mark.parametrize("shape", SHAPES)
