@@ -488,6 +488,15 @@ inline void energy_split(EnergyJob *e, int64_t waves, int64_t wgs) {
         }
     }
 }
+// Grid of at least `count` workgroups of at most 1,024 threads, its number b =
+// y * gridDim.x + x.  A launch holds fewer than 2^32 threads along x and at most
+// 65,535 workgroups along y, and a read-out of many trials needs more workgroups
+// than that (2^28 trials: 2^26 wavefronts of the final pass).
+constexpr int32_t kMostGridY = 65535;
+inline dim3 wide_grid(int64_t count) {
+    const int64_t x = std::min<int64_t>(count, int64_t{1} << 20);
+    return dim3(static_cast<unsigned>(x), static_cast<unsigned>((count + x - 1) / x));
+}
 hipError_t launch_spins_to_tn(hipStream_t stream, int32_t n, const DevRun &run,
                               int8_t *out_tn);
 hipError_t launch_spins_from_tn(hipStream_t stream, int32_t n, const DevRun &run,

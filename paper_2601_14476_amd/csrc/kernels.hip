@@ -64,6 +64,13 @@ constexpr int kEnergyRows = 256;   // rows of a partial sum
 constexpr int kEnergyBlock = 1024;  // most threads of a partial pass
 constexpr int kFieldBlock = 256;
 
+// Number of a workgroup of a wide_grid; those past the last one that a launch
+// asked for have one, too (at most 2^31 - 1).
+__device__ __forceinline__ int32_t wide_index() {
+    const uint32_t b = blockIdx.y * gridDim.x + blockIdx.x;
+    return static_cast<int32_t>(min(b, 0x7FFFFFFFu));
+}
+
 // Final pass: a wavefront sums the row blocks' terms of one trial group, eight
 // lanes (the group's S and h terms) to a block, then reduces over the blocks:
 //   E_k   = -sum_i h_i m_i - S_k / 2
@@ -73,6 +80,7 @@ constexpr int kFieldBlock = 256;
 __device__ __forceinline__ void energy_finish(const EnergyJob &e, int32_t q) {
     const int lane = threadIdx.x & 63, c = lane & 7;
     const int32_t groups = e.t4 / 4;
+    if (q >= groups) return;  // past the last wavefront of the grid (wide_grid)
     int64_t v = 0;
     for (int32_t b = lane >> 3; b < e.blocks; b += 8) v += e.part[(static_cast<size_t>(b) * groups + q) * 8 + c];
 #pragma unroll
@@ -87,7 +95,7 @@ __device__ __forceinline__ void energy_finish(const EnergyJob &e, int32_t q) {
 
 // One run (its table entry as the argument).
 __global__ __launch_bounds__(64) void energy_finish_kernel(EnergyJob e) {
-    energy_finish(e, static_cast<int32_t>(blockIdx.x));
+    energy_finish(e, wide_index());
 }
 
 // The run of a batched read-out that index x (a workgroup of the partial
@@ -170,6 +178,7 @@ __device__ __forceinline__ void energy_partial_run(const EnergyJob &e, int32_t l
     const int32_t groups = e.t4 / 4;
     const int32_t ys = (groups + Q * e.cpl - 1) / (Q * e.cpl);
     const int32_t blk = local / ys;
+    if (blk >= e.blocks) return;  // past the last workgroup of the grid (wide_grid)
     const ReadLane l = read_lane<Q>(e, local % ys);
     const bool has_h = e.h != nullptr;
     int32_t s32[Q][4] = {}, hm32[Q][4] = {};
@@ -238,21 +247,21 @@ __device__ __forceinline__ void energy_partial_run(const EnergyJob &e, int32_t l
 // and four trials, which the one-run read-out used before: 224 us).
 template <typename SUM, int Q>
 __global__ __launch_bounds__(kEnergyBlock) void energy_partial_kernel(EnergyJob e) {
-    energy_partial_run<SUM, Q>(e, static_cast<int32_t>(blockIdx.x));
+    energy_partial_run<SUM, Q>(e, wide_index());
 }
 
 // Many runs: workgroup b is workgroup b - wg0 of its run.
 template <typename SUM, int Q>
 __global__ __launch_bounds__(kEnergyBlock) void energy_partial_batch_kernel(const EnergyJob *__restrict__ jobs,
                                                                             int32_t count) {
-    const int32_t b = blockIdx.x;
+    const int32_t b = wide_index();
     const EnergyJob &e = jobs[energy_run_of<true>(jobs, count, b)];
     energy_partial_run<SUM, Q>(e, b - e.wg0);
 }
 
 // Many runs' final pass: wavefront x is trial group x - q0 of its run.
 __global__ __launch_bounds__(64) void energy_finish_batch_kernel(const EnergyJob *__restrict__ jobs, int32_t count) {
-    const int32_t x = blockIdx.x;
+    const int32_t x = wide_index();
     const EnergyJob &e = jobs[energy_run_of<false>(jobs, count, x)];
     energy_finish(e, x - e.q0);
 }
@@ -264,7 +273,7 @@ __global__ __launch_bounds__(64) void energy_finish_batch_kernel(const EnergyJob
 // 60 us with a chunk's rows on neighbouring lanes (16-byte gathers).
 __global__ __launch_bounds__(kFieldBlock) void local_field_kernel(EnergyJob e, int32_t *__restrict__ out) {
     constexpr int Q = 4;
-    const ReadLane l = read_lane<Q>(e, static_cast<int32_t>(blockIdx.y));
+    const ReadLane l = read_lane<Q>(e, static_cast<int32_t>(blockIdx.z * gridDim.y + blockIdx.y));
     const int32_t i = static_cast<int32_t>(blockIdx.x) * l.rows + l.row;
     int32_t L[Q][4] = {};
     if (i < e.n && l.nq > 0) row_sums<Q>(e, i, l, L);
@@ -284,11 +293,24 @@ __global__ __launch_bounds__(kFieldBlock) void local_field_kernel(EnergyJob e, i
 // byte of a row each, took 24.6 us at 20,000 p-bits x 256 trials; this 5.6 us).
 constexpr int kTile = 64;
 
+// Workgroup b's tile: the p-bits' tiles next to each other.
+struct TileAt {
+    int32_t i0, k0;
+};
+__device__ __forceinline__ TileAt tile_at(int32_t n) {
+    const uint32_t across = static_cast<uint32_t>((n + kTile - 1) / kTile);
+    return TileAt{static_cast<int32_t>(blockIdx.x % across) * kTile, static_cast<int32_t>(blockIdx.x / across) * kTile};
+}
+inline unsigned tile_grid(int32_t n, int32_t trials) {
+    return static_cast<unsigned>((static_cast<int64_t>(n) + kTile - 1) / kTile * ((static_cast<int64_t>(trials) + kTile - 1) / kTile));
+}
+
 // spins -> out
 __global__ __launch_bounds__(256) void spins_to_tn_kernel(int32_t n, int32_t t4, int32_t trials,
                                                           const int8_t *__restrict__ spins, int8_t *__restrict__ out) {
     __shared__ int8_t tile[kTile][kTile + 4];
-    const int32_t i0 = static_cast<int32_t>(blockIdx.x) * kTile, k0 = static_cast<int32_t>(blockIdx.y) * kTile;
+    const TileAt at = tile_at(n);
+    const int32_t i0 = at.i0, k0 = at.k0;
     // 16 words of four trials per row
     for (int32_t x = threadIdx.x; x < kTile * 16; x += 256) {
         const int32_t r = x / 16, w = x % 16;
@@ -306,7 +328,8 @@ __global__ __launch_bounds__(256) void spins_to_tn_kernel(int32_t n, int32_t t4,
 __global__ __launch_bounds__(256) void spins_from_tn_kernel(int32_t n, int32_t t4, int32_t trials,
                                                             const int8_t *__restrict__ in, int8_t *__restrict__ spins) {
     __shared__ int8_t tile[kTile][kTile + 4];
-    const int32_t i0 = static_cast<int32_t>(blockIdx.x) * kTile, k0 = static_cast<int32_t>(blockIdx.y) * kTile;
+    const TileAt at = tile_at(n);
+    const int32_t i0 = at.i0, k0 = at.k0;
     const int32_t c = threadIdx.x & 63;
     if (i0 + c < n)
         for (int32_t r = threadIdx.x >> 6; r < kTile && k0 + r < trials; r += 4)
@@ -376,9 +399,10 @@ EnergyJob energy_job(const DevGraph &g, const DevRun &run) {
 hipError_t launch_local_field(hipStream_t stream, const DevGraph &g, const DevRun &run,
                               int32_t *out_tn) {
     const EnergyJob e = energy_job(g, run);
-    const int32_t chunks = (run.t4 + 15) / 16;
+    const int32_t chunks = (run.t4 + 15) / 16, ys = (chunks + e.cpl - 1) / e.cpl;
+    const int32_t y = std::min(ys, kMostGridY);
     hipLaunchKernelGGL(local_field_kernel,
-                       dim3(grid_for(static_cast<int64_t>(g.n) * e.cpl * e.lpr, kFieldBlock), (chunks + e.cpl - 1) / e.cpl),
+                       dim3(grid_for(static_cast<int64_t>(g.n) * e.cpl * e.lpr, kFieldBlock), y, (ys + y - 1) / y),
                        dim3(kFieldBlock), 0, stream, e, out_tn);
     return hipGetLastError();
 }
@@ -403,11 +427,11 @@ hipError_t launch_energy_cut(hipStream_t stream, const DevGraph &g, const DevRun
     auto kern = e.quads == 1 ? (e.narrow ? energy_partial_kernel<int32_t, 1> : energy_partial_kernel<int64_t, 1>)
                              : (e.narrow ? energy_partial_kernel<int32_t, 4> : energy_partial_kernel<int64_t, 4>);
     const int32_t block = energy_block(e);
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(energy_batch_wgs(e))), dim3(block),
+    hipLaunchKernelGGL(kern, wide_grid(energy_batch_wgs(e)), dim3(block),
                        energy_lds_bytes(e, block, e.narrow), stream, e);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(energy_finish_kernel, dim3(run.t4 / 4), dim3(64), 0, stream, e);
+    hipLaunchKernelGGL(energy_finish_kernel, wide_grid(run.t4 / 4), dim3(64), 0, stream, e);
     return hipGetLastError();
 }
 
@@ -426,22 +450,22 @@ hipError_t launch_energy_cut_batch(hipStream_t stream, const EnergyJob *jobs, co
     auto kern = host[0].quads == 1
                     ? (narrow ? energy_partial_batch_kernel<int32_t, 1> : energy_partial_batch_kernel<int64_t, 1>)
                     : (narrow ? energy_partial_batch_kernel<int32_t, 4> : energy_partial_batch_kernel<int64_t, 4>);
-    hipLaunchKernelGGL(kern, dim3(wgs), dim3(block), lds, stream, jobs, count);
+    hipLaunchKernelGGL(kern, wide_grid(wgs), dim3(block), lds, stream, jobs, count);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(energy_finish_batch_kernel, dim3(groups), dim3(64), 0, stream, jobs, count);
+    hipLaunchKernelGGL(energy_finish_batch_kernel, wide_grid(groups), dim3(64), 0, stream, jobs, count);
     return hipGetLastError();
 }
 
 hipError_t launch_spins_to_tn(hipStream_t stream, int32_t n, const DevRun &run, int8_t *out_tn) {
-    hipLaunchKernelGGL(spins_to_tn_kernel, dim3(grid_for(n, kTile), grid_for(run.trials, kTile)), dim3(256), 0, stream, n,
+    hipLaunchKernelGGL(spins_to_tn_kernel, dim3(tile_grid(n, run.trials)), dim3(256), 0, stream, n,
                        run.t4, run.trials, run.spins, out_tn);
     return hipGetLastError();
 }
 
 hipError_t launch_spins_from_tn(hipStream_t stream, int32_t n, const DevRun &run,
                                 const int8_t *in_tn) {
-    hipLaunchKernelGGL(spins_from_tn_kernel, dim3(grid_for(n, kTile), grid_for(run.trials, kTile)), dim3(256), 0, stream, n,
+    hipLaunchKernelGGL(spins_from_tn_kernel, dim3(tile_grid(n, run.trials)), dim3(256), 0, stream, n,
                        run.t4, run.trials, in_tn, run.spins);
     return hipGetLastError();
 }
