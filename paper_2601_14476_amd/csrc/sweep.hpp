@@ -350,31 +350,40 @@ __device__ __forceinline__ uint32_t lane_sub() {
 // side by side, then exchange what the other needs: with LPT 2 one half-wave
 // swap of words 0 and 2 leaves the r words of both halves in one register and
 // the gate words in the other (words 1 and 3 likewise); with LPT 4 neighbours
-// swap by DPP.  B.own: the prefix of the lane's block; B.gate: LPT 1's second.
+// swap by DPP.
+//
+// LPT 1: both blocks under their scalar prefixes.  LPT >= 2: each lane draws its
+// one block whole.  A prefix for two purposes takes about 50 scalar instructions
+// a wavefront and step and saves a lane's one block 6 vector ones less 3
+// selects, and the scalar unit is shared by all wavefronts of a compute unit (us
+// per step, drawn whole and under prefixes: 250 p-bits of degree 27, 700 trials
+// 1.22 and 1.33, 500 of degree 6, 360 trials 1.07 and 1.17; one workgroup per
+// compute unit, 500 of degree 6, 130 trials 0.80 and 0.78).
 // ---------------------------------------------------------------------------
 struct StepBlocks {
-    BlockPrefix own, gate;
+    BlockPrefix r, gate;      // LPT 1
+    uint32_t t, k, tag, k0, k1;  // LPT >= 2: the lane's block
 };
 template <int LPT>
 __device__ __forceinline__ StepBlocks step_blocks(uint32_t t, uint32_t k, uint32_t sub, bool gated, uint32_t k0,
                                                   uint32_t k1) {
-    StepBlocks B;
-    B.own = block_prefix(t, k, kTagR, k0, k1);
-    B.gate = gated ? block_prefix(t, k, kTagGate, k0, k1) : B.own;
-    if constexpr (LPT > 1) {
-        if (gated) {
-            const bool odd = (sub & 1u) != 0u;
-            B.own.b = odd ? B.gate.b : B.own.b;
-            B.own.c = odd ? B.gate.c : B.own.c;
-            B.own.e = odd ? B.gate.e : B.own.e;
-        }
+    StepBlocks B{};
+    if constexpr (LPT == 1) {
+        B.r = block_prefix(t, k, kTagR, k0, k1);
+        B.gate = gated ? block_prefix(t, k, kTagGate, k0, k1) : B.r;
+    } else {
+        B.t = t;
+        B.k = k;
+        B.tag = gated && (sub & 1u) != 0u ? kTagGate : kTagR;
+        B.k0 = k0;
+        B.k1 = k1;
     }
     return B;
 }
 template <int LPT>
 __device__ __forceinline__ void task_words(uint32_t m, uint32_t sub, bool gated, const StepBlocks &B,
                                            const RoundKeys &keys, uint32_t rw[4 / LPT], uint32_t gw[4 / LPT]) {
-    const Words4 b = block_of_task(m, B.own, keys);
+    const Words4 b = LPT == 1 ? block_of_task(m, B.r, keys) : philox4x32_10(B.t, m, B.k, B.tag, B.k0, B.k1);
     if constexpr (LPT == 1) {
         rw[0] = b.x;
         rw[1] = b.y;
@@ -601,7 +610,8 @@ __device__ __forceinline__ uint32_t task_one_trial(const Views &v, const TaskCon
     if (__ballot(close) != 0u) {
 #pragma unroll
         for (int j = 0; j < P; ++j) {
-            if constexpr (DIRECT) xv[j] = (i0t * c.lam[j]) * (static_cast<float>(L[j]) + c.dlt[j]);
+            // (read again: kept, the two would spill edge slots of one-row lanes)
+            if constexpr (DIRECT) xv[j] = (i0t * v.lam[base + j]) * (static_cast<float>(L[j]) + v.dlt[base + j]);
             d[j] = tanh_f32(xv[j]) > r_of(rw[j]) ? -1.0f : 1.0f;
         }
     }
@@ -863,9 +873,7 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
     constexpr int P = 4 / LPT;
     const uint32_t sub = lane_sub<LPT>();
     const bool gated = a.gated != 0;
-    // two rows or more per lane: round keys in vector registers (the one-row
-    // lanes' 64 edge slots leave no room for them)
-    const RoundKeys keys = round_keys<(P > 1)>(a.k0, a.k1);
+    const RoundKeys keys = round_keys(a.k0, a.k1);  // LPT 1
     auto one_trial_step = [&](auto alg_tag, auto cached_tag, const TaskConst<P> &c,
                               const EdgeCache *ec, LaneInput<P> *li, uint32_t tau, float i0t, float close_d,
                               uint32_t k0, uint32_t k1, const StepBlocks &B, const unsigned char *from,
