@@ -366,7 +366,8 @@ psa_status dense_step_jobs(psa_ctx *ctx, psa_job *const *jobs, int32_t count, in
             // 64 rows read the trial tile's spins again)
             int64_t items = 0;
             for (int32_t j : by_enc[e]) items += static_cast<int64_t>((table[j].np + 255) / 256) * (table[j].tp / (16 * nb[e]));
-            split[e] = items < kDenseSplitItems;
+            dense_work_list(table, by_enc[e], nb[e], 256, &part);
+            split[e] = dense_splits(items, static_cast<int64_t>(part.size()), dense_fp4(e));
             if (split[e]) {
                 const int32_t most = nb[e];
                 auto fine = [&](int32_t b) {
@@ -376,8 +377,8 @@ psa_status dense_step_jobs(psa_ctx *ctx, psa_job *const *jobs, int32_t count, in
                 };
                 nb[e] = 1;
                 while (nb[e] < most && fine(nb[e]) > 2 * kDenseSplitItems) nb[e] *= 2;
+                dense_work_list(table, by_enc[e], nb[e], 64, &part);
             }
-            dense_work_list(table, by_enc[e], nb[e], split[e] ? 64 : 256, &part);
         }
         off[e] = work.size();
         len[e] = part.size();

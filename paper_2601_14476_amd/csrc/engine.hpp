@@ -339,7 +339,18 @@ constexpr int32_t kDenseGraphMinSteps = 2;
 hipError_t launch_dense_steps(hipStream_t stream, const DenseJob *jobs, const int4 *work,
                               int32_t nwork, int32_t nb, bool split, const DenseJob *one, int32_t enc, int32_t mode,
                               int32_t steps);
-constexpr int64_t kDenseSplitItems = 256;  // 256-row items below which a list is split
+// Whether a list of so many 256-row items is split: fewer than the compute units.
+// int8 couplings are four times the bytes, so past half the units the 64-row
+// items' repeated spin and coupling reads cost more than the idle units, as long
+// as the 256-row items fit one round (`slots`: 8 times the fullest XCD's; us per
+// step without factors, 256-row and 64-row items: 3,000 p-bits x 500 trials, 96
+// items, 34.6 and 28.3; 2,000 x 1,000, 128, 27.5 and 21.9; 3,000 x 700, 132, 34.8 and
+// 38.4; 4,500 x 500, 144, 46.5 and 53.5; 3,000 x 1,000, 192, 35.0 and 38.7; 4,500 x
+// 700, 198 in 264 slots, 78.4 and 69.4).
+constexpr int64_t kDenseSplitItems = 256;
+constexpr bool dense_splits(int64_t items, int64_t slots, bool fp4) {
+    return items < kDenseSplitItems && (fp4 || items <= kDenseSplitItems / 2 || slots > kDenseSplitItems);
+}
 // The same `steps` steps in one launch (dense_steps_kernel): the work list
 // split into kDenseQueues queues of whole runs (queue x: items off[x] ..
 // off[x+1]-1), tasks taken in step order from each queue's ticket counter,
