@@ -676,6 +676,7 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
     j->run.trials = desc->trials;
     j->run.t4 = (desc->trials + 3) / 4 * 4;
     j->run.steps = S;
+    j->run.t_res = desc->t_res;
     psa_status st;
     const int32_t n4 = g->dev.n4;
     // input-stage state first: the launch plan depends on it (LDS windows)
@@ -710,9 +711,7 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
             j->plan.dense = 1;  // too large for the LDS-resident sweep
         }
     }
-    psa::DevRun asked = j->run;
-    asked.t_res = desc->t_res;
-    if (path == PSA_PATH_DENSE || (path == PSA_PATH_AUTO && psa::prefer_dense(g, asked, j->plan)))
+    if (path == PSA_PATH_DENSE || (path == PSA_PATH_AUTO && psa::prefer_dense(g, j->run, j->plan)))
         j->plan.dense = 1;
     if (j->plan.dense && arena) {
         set_error("the run needs the dense path, which the static scratch does not hold");
@@ -786,7 +785,6 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
         std::vector<psa::PeriodRec> recs;
         std::vector<psa::PeriodClass> classes;
         std::vector<uint32_t> ecache;
-        j->run.t_res = desc->t_res;
         if (psa::plan_period(g->dev, j->run, g->row_ptr_host, g->col_host, g->val_host, g->h_host, lam,
                              dlt, thr, ctx->max_lds,
                              desc->block, &j->pplan, &recs, &classes, &ecache)) {
@@ -806,7 +804,6 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
         const size_t mb = 2 * static_cast<size_t>(j->tp) * static_cast<size_t>(g->np);
         if ((st = dev_upload<int8_t>(&j->d_m, nullptr, mb, "job dense spins", &j->dev_bytes, arena)) != PSA_OK) return st;
     }
-    j->run.t_res = desc->t_res;
     j->run.i0 = j->d_i0;
     j->run.lambda = j->d_lambda;
     j->run.delta = j->d_delta;

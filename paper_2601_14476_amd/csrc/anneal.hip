@@ -68,6 +68,34 @@ hipError_t launch_four_trials(hipStream_t stream, const AnnealArgs &args, const 
 
 }  // namespace
 
+// Rounds of one-trial workgroups up to which a run on a graph with ELL rows
+// keeps them: about the ratio of a four-trial step to one round (us per step, one
+// and four trials per workgroup).
+//   streaming sweep: 2 (4,000 p-bits of degree 6, 512 trials 5.8 and 6.0, 600 8.1
+//     and 5.9), and so resident lanes whose rows are weighted or outgrow their
+//     cached slots (64 for one row, 32 for two) (1,000 of degree 6, weights, 1,000 trials 5.9 and 3.7; 2,000 of
+//     24, 520 trials 14.3 and 6.3);
+//   resident lanes with cached rows: 3 (600 of degree 6, 760 trials 3.1 and 3.4,
+//     780 4.1 and 3.4; SpSA 1,500 of degree 6, 760 trials 4.1 and 4.7), but 2 where
+//     two rows fill more than 800 lanes (2,000 of degree 6, 760 trials 4.1 and 3.7;
+//     1,200 of degree 6 3.3 and 3.5); TApSA 4, the
+//     window in LDS against 16 bytes per p-bit from memory (1,500 of degree 6, 1,000
+//     trials 5.6 and 8.1; 600 of degree 6, 1,000 4.7 and 6.0);
+//   period classes, which visit only the p-bits that fire: 4 with one row per
+//     lane (800 of degree 12, sub-steps of 10, 760 trials 15.7 and 21.3, 1,000 20.6 and
+//     21.3), 3 up to mean degree 32, and with two short rows (2,000 of degree 6, 760
+//     trials 18.7 and 20.9), else 2 (2,000 of degree 24, 500 trials 37 and 36).
+static int64_t one_trial_rounds(const DevGraph &g, const DevRun &run, const AnnealPlan &one) {
+    const int64_t n = g.n;
+    if (run.t_res > 0) {
+        if (one.lpt == 4) return g.nnz <= 16 * n ? 4 : (g.nnz <= 32 * n ? 3 : 2);
+        return one.lpt == 2 && g.nnz <= 8 * n ? 3 : 2;
+    }
+    if (one.ell || one.csr != kCsrUnit || !one.csr_lds || one.lpt == 1) return 2;
+    if (one.lpt == 4 ? g.max_degree > 64 : (g.nnz > 8 * n || g.max_degree > 32)) return 2;
+    return run.ring ? 4 : (run.xs || one.lpt == 4 || n <= 1600 ? 3 : 2);
+}
+
 bool plan_anneal(const DevGraph &g, const DevRun &run, int32_t tpw_req, int32_t lpt_req,
                  int32_t block_req, size_t max_lds, int32_t num_cu, AnnealPlan *plan,
                  std::string *why) {
@@ -79,18 +107,18 @@ bool plan_anneal(const DevGraph &g, const DevRun &run, int32_t tpw_req, int32_t 
         p.tpw = tpw_req;
     } else {
         // One trial per workgroup exposes four times the workgroups; four
-        // share each walk of the rows and issue fewer instructions.  On the
-        // streaming sweep four pay once the one-trial workgroups would take
-        // three rounds or more of the compute units (a unit runs 1,024 of
-        // their threads at once; us per step, one and four trials: 2,000 p-bits of
-        // degree 6, 512 trials 2.9 and 3.7, 600 4.1 and 3.7; 4,000, 512 5.8 and
-        // 6.0, 600 8.1 and 5.9; 250, 1,024 1.7 and 2.6, 2,048 2.8 and 2.8).
+        // share each walk of the rows and issue fewer instructions.  Four pay
+        // once the one-trial workgroups take too many rounds of the compute
+        // units (one_trial_rounds; a unit runs 1,024 of their threads at once,
+        // and one workgroup of the period-class sweep).
         AnnealPlan one;
         const int32_t spread = tasks * 4 <= 1024 ? 4 : (tasks * 2 <= 1024 ? 2 : 1);
-        if (ell_ok && g.e4_mode >= 0 && plan_anneal(g, run, 1, lpt_req ? lpt_req : spread, block_req, max_lds, num_cu, &one, nullptr))
-            p.tpw = static_cast<int64_t>(run.trials) * one.block > 2 * static_cast<int64_t>(num_cu) * 1024 ? 4 : 1;
-        else
+        if (ell_ok && g.e4_mode >= 0 && plan_anneal(g, run, 1, lpt_req ? lpt_req : spread, block_req, max_lds, num_cu, &one, nullptr)) {
+            const int64_t threads = run.t_res > 0 ? 1024 : one.block;
+            p.tpw = run.trials * threads > one_trial_rounds(g, run, one) * static_cast<int64_t>(num_cu) * 1024 ? 4 : 1;
+        } else {
             p.tpw = (run.t4 / 4 >= num_cu) ? 4 : 1;
+        }
     }
     p.grid = p.tpw == 4 ? run.t4 / 4 : run.trials;
     if (p.tpw == 4) {
