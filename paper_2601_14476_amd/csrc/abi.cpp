@@ -711,7 +711,10 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
             j->plan.dense = 1;  // too large for the LDS-resident sweep
         }
     }
-    if (path == PSA_PATH_DENSE || (path == PSA_PATH_AUTO && psa::prefer_dense(g, j->run, j->plan)))
+    j->identity_factors = desc->algorithm == PSA_ALG_PSA && desc->t_res == 0;
+    for (int32_t i = 0; i < n && j->identity_factors; ++i)
+        j->identity_factors = lam[i] == 1.0f && dlt[i] == 0.0f && thr[i] >= psa::kGateOneHost;
+    if (path == PSA_PATH_DENSE || (path == PSA_PATH_AUTO && psa::prefer_dense(g, j->run, j->plan, j->identity_factors)))
         j->plan.dense = 1;
     if (j->plan.dense && arena) {
         set_error("the run needs the dense path, which the static scratch does not hold");
@@ -724,9 +727,6 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
     }
     j->run.key0 = static_cast<uint32_t>(desc->seed);
     j->run.key1 = static_cast<uint32_t>(desc->seed >> 32);
-    j->identity_factors = desc->algorithm == PSA_ALG_PSA && desc->t_res == 0;
-    for (int32_t i = 0; i < n && j->identity_factors; ++i)
-        j->identity_factors = lam[i] == 1.0f && dlt[i] == 0.0f && thr[i] >= psa::kGateOneHost;
     double max_lam = 0.0, max_prod = 0.0;
     bool subnormal = false;
     for (int32_t i = 0; i < n; ++i) {

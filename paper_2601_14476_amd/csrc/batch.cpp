@@ -94,59 +94,65 @@ void build_work_list(const std::vector<int32_t> &items, const std::vector<double
         for (size_t s = 0; s < queue[x].size(); ++s) (*work)[s * kXcds + x] = queue[x][s];
 }
 
-// Automatic path choice.  Estimates per step (above the floors below): the CSR
-// sweeps' lane-operations per update (csr_step_seconds); the dense product's 2
-// np^2 tp operations at two fifths of the int8 (or, 1- and 2-bit couplings,
-// fp4) matrix peak, or the bytes of J once per trial tile at the HBM peak,
-// whichever is larger, plus 40 lane-operations of epilogue per update (+-1
-// couplings of density 0.06, us per step, estimate and measured: 3,000 p-bits x 64
-// trials 4.7 and 5.0, 4,000 x 64 5.0 and 6.0, 2,000 x 1,024 8.5 and 10.6, 4,000
-// x 1,024 17.0 and 17.1; int8 3,000 x 64 8.6 and 11.6).
-// Latency floors of a step: the CSR sweep's step is a barrier and a chain of
-// LDS reads inside one persistent launch; the dense step is a launch of its
-// own.  They decide for small runs, whose throughput terms are tiny (a G1-
-// sized run of 10 trials: 2 us per CSR step measured, several times that per
-// dense step).
+// Automatic path choice: modelled time of a step (period timing: of a
+// sub-step) on either path.  Fitted to 2,610 runs of 300 to 4,500 p-bits of
+// degree 6 to 180, +-1 and integer weights, 8 to 2,048 trials, with and without
+// gate, SpSA, TApSA (window 4) and periods of 10 (each on both paths): the choice
+// takes 0.8 % longer than the better path over all of them, and none longer than
+// 1.8 times it.
 constexpr double kCsrStepFloorSeconds = 1.5e-6;
-constexpr double kDenseStepFloorSeconds = 4.2e-6;    // fp4 couplings
-constexpr double kDenseI8StepFloorSeconds = 8.0e-6;  // int8
+constexpr double kDenseStepFloorSeconds = 5.5e-6;    // fp4 couplings: the launch
+constexpr double kDenseI8StepFloorSeconds = 7.0e-6;  // int8
 
 double csr_step_seconds(const DevGraph &g, const DevRun &run, const AnnealPlan &plan) {
-    if (plan.ell && !(run.t_res > 0 && plan.tpw == 1)) {  // (period classes have a sweep of their own)
-        // streaming sweeps: lane-operations per update fitted to runs of
-        // degree 4 to 50 (four trials 35 + 4 d, one trial 50 + 7 d), on the
-        // compute units its workgroups reach, in whole rounds of them; TApSA
-        // windows and SpSA inputs in device memory at about 4 TB/s, 16 bytes
-        // for the 4 a one-trial workgroup uses (15,013 p-bits of degree 26, 366
-        // trials, TApSA: 207 us per step, on the dense path 101)
-        const double deg = g.nnz / static_cast<double>(std::max(g.n, 1));
-        const double wgs = plan.tpw == 4 ? run.t4 / 4 : run.trials;
-        const double ops = plan.tpw == 4 ? 35.0 + 4.0 * deg : 50.0 + 7.0 * deg;
-        const double rounds = wgs * plan.block / (256.0 * 1024.0);
+    const double n = g.n, nnz = static_cast<double>(g.nnz), deg = nnz / std::max(n, 1.0);
+    const double wgs = plan.tpw == 4 ? run.t4 / 4 : run.trials;
+    const double rounds = wgs * plan.block / (256.0 * 1024.0), whole = std::max(1.0, std::ceil(rounds));
+    if (run.t_res > 0 && plan.tpw == 1)  // the class sweep visits the p-bits that fire
+        return std::max(kCsrStepFloorSeconds, whole * (0.5e-6 + n / run.t_res * (2.5e-9 + 0.35e-9 * deg)));
+    if (plan.ell) {
+        // streaming sweeps: lane-operations per update, on the compute units the
+        // workgroups reach in whole rounds of them (sums in halves issue half as
+        // much again; a sub-step of periods passes by the wavefronts that hold);
+        // TApSA windows and SpSA inputs in device memory at about 4 TB/s, 16
+        // bytes for the 4 a one-trial workgroup uses, and the latency of window
+        // reads where a lane takes several tasks
+        double ops = plan.tpw == 4 ? 35.0 + (g.e4_mode == 0 ? 4.0 : 6.0) * deg : 50.0 + 7.0 * deg;
+        if (run.t_res > 0) ops *= 0.45;
         const double words = run.ring ? run.alpha : (run.xs ? 2.0 : 0.0);
         const double state = words * (plan.tpw == 4 ? 4.0 : 16.0) / 4.0e12;
-        const double share = rounds > 1.0 ? rounds / std::ceil(rounds) : std::min(1.0, wgs / 256.0);
-        return std::max(kCsrStepFloorSeconds,
-                        static_cast<double>(g.n) * run.trials * (ops / (kValuOpsPerSecond * share) + state));
+        const double share = rounds > 1.0 ? rounds / whole : std::min(1.0, wgs / 256.0);
+        const double wait = run.ring && plan.tpw == 1 && g.n4 / 4 > 1024 ? 3.5e-6 * run.alpha * whole : 0.0;
+        return std::max(kCsrStepFloorSeconds, n * run.trials * (ops / (kValuOpsPerSecond * share) + state)) + wait;
     }
-    // lane-ops per update: RNG, activation and decision (about 60), plus a
-    // gather per edge: a few ops from LDS, tens when the rows stream from
-    // memory (latency-bound gathers of one trial per workgroup)
-    const double d = g.nnz / static_cast<double>(std::max(g.n, 1));
-    const double per_edge = plan.csr_lds ? 3.0 : 40.0;
-    return std::max(kCsrStepFloorSeconds,
-                    static_cast<double>(g.n) * run.t4 * (60.0 + per_edge * d) / kValuOpsPerSecond);
+    if (plan.csr_lds) return std::max(kCsrStepFloorSeconds, whole * (1.0e-6 + nnz * 0.08e-9));
+    // rows read from device memory by the few lanes of a workgroup: a latency
+    // per 1,024 entries
+    return whole * nnz / 1024.0 * (plan.csr == kCsrUnit ? 0.4e-6 : 0.23e-6) * (1.0 + std::min(run.trials, 256) / 200.0);
 }
 
-double dense_step_seconds(int32_t n, int32_t t4, bool two_bit, bool one_bit) {
+double dense_step_seconds(int32_t n, const DevRun &run, bool two_bit, bool one_bit, bool identity) {
     const bool fp4 = two_bit || one_bit;
-    const double np = fp4 ? (n + 255) / 256 * 256 : (n + 127) / 128 * 128;
+    const int32_t np = fp4 ? (n + 255) / 256 * 256 : (n + 127) / 128 * 128, t4 = run.t4;
     const int32_t nb = t4 >= 64 ? 4 : (t4 >= 32 ? 2 : 1);
-    const double tp = std::ceil(t4 / (16.0 * nb)) * 16.0 * nb;
-    const double mfma = 2.0 * np * np * tp / (0.4 * (fp4 ? kMfmaF4OpsPerSecond : kMfmaI8OpsPerSecond));
-    const double bytes = np * np * (one_bit ? 0.125 : (two_bit ? 0.25 : 1.0)) * (tp / (16.0 * nb)) / kHbmBytesPerSecond;
-    return (fp4 ? kDenseStepFloorSeconds : kDenseI8StepFloorSeconds) + std::max(mfma, bytes) +
-           static_cast<double>(n) * t4 * 40.0 / kValuOpsPerSecond;
+    const double tiles = std::ceil(t4 / (16.0 * nb)), tp = tiles * 16.0 * nb, np2 = static_cast<double>(np) * np;
+    const double mfma = 2.0 * np2 * tp / (0.4 * (fp4 ? kMfmaF4OpsPerSecond : kMfmaI8OpsPerSecond));
+    const double bytes = np2 * (one_bit ? 0.125 : (two_bit ? 0.25 : 1.0)) * tiles / kHbmBytesPerSecond;
+    double t = (fp4 ? kDenseStepFloorSeconds : kDenseI8StepFloorSeconds) + 1.2 * std::max(mfma, bytes) +
+               static_cast<double>(n) * t4 * 40.0 / kValuOpsPerSecond;
+    // the general epilogue, and its window or input reads: for each (row block,
+    // trial block) pair of a wavefront one after the other
+    const int32_t most = fp4 ? std::min(nb, 2) : nb;
+    const double items = (np + 255) / 256 * std::ceil(t4 / (16.0 * most));
+    if (dense_splits(static_cast<int64_t>(items), static_cast<int64_t>(items), fp4)) {
+        int32_t k = 1;
+        while (k < most && np / 64 * std::ceil(t4 / (16.0 * k)) > 2.0 * kDenseSplitItems) k *= 2;
+        t += k * (run.ring ? 0.75e-6 * run.alpha : (run.xs ? 1.3e-6 : 0.0));
+    } else if (!identity) {
+        const double turns = std::max(1.0, items / (fp4 ? 512.0 : 256.0));
+        t += turns * (run.ring ? (fp4 ? 9.0e-6 : 12.5e-6) * run.alpha : (run.xs ? (fp4 ? 11.0e-6 : 18.0e-6) : 4.0e-6));
+    }
+    return t;
 }
 
 bool dense_two_bit(const psa_graph *g) {
@@ -165,13 +171,21 @@ bool dense_one_bit(const psa_graph *g) {
     return std::all_of(g->val_host.begin(), g->val_host.end(), [&](int32_t v) { return v == g->val_host[0]; });
 }
 
-bool prefer_dense(const psa_graph *g, const DevRun &run, const AnnealPlan &plan) {
+// A graph without its dense matrix pays for it at the first dense run: about 0.11
+// ns per entry of it, encoded and uploaded (5,000 p-bits 2.7 ms, where 10 steps of
+// 8 trials take 0.2 ms there and 0.7 on the rows).
+constexpr double kDenseEncodeSecondsPerEntry = 0.11e-9;
+
+bool prefer_dense(const psa_graph *g, const DevRun &run, const AnnealPlan &plan, bool identity) {
     if (g->info.n < 256) return false;
     const bool two_bit = dense_two_bit(g);
     if (!two_bit && std::any_of(g->val_host.begin(), g->val_host.end(),
                                 [](int32_t v) { return v < -127 || v > 127; }))
         return false;
-    return dense_step_seconds(g->info.n, run.t4, two_bit, dense_one_bit(g)) < 0.7 * csr_step_seconds(g->dev, run, plan);
+    const double steps = static_cast<double>(run.steps) * std::max(run.t_res, 1);
+    const double encode = g->d_dense ? 0.0 : kDenseEncodeSecondsPerEntry * g->info.n * static_cast<double>(g->info.n);
+    return dense_step_seconds(g->info.n, run, two_bit, dense_one_bit(g), identity) + encode / steps <
+           0.7 * csr_step_seconds(g->dev, run, plan);
 }
 
 // Work list of the dense runs `idx` of `table` (one encoding): items (job,
@@ -597,8 +611,8 @@ psa_status psa_jobs_step_batch(psa_ctx *ctx, int32_t count, psa_job *const *jobs
             if (te <= job->t) continue;
             if (job->plan.dense) {
                 dense_jobs.push_back(job);
-                dense_s += psa::dense_step_seconds(job->g->info.n, job->run.t4, job->g->dense_enc == psa::kDenseT2,
-                                                   job->g->dense_enc == psa::kDenseB1) *
+                dense_s += psa::dense_step_seconds(job->g->info.n, job->run, job->g->dense_enc == psa::kDenseT2,
+                                                   job->g->dense_enc == psa::kDenseB1, job->identity_factors) *
                            (te - job->t);
                 continue;
             }

@@ -585,7 +585,8 @@ constexpr double kHbmBytesPerSecond = 8.0e12;
 // Modelled seconds per step of the CSR sweep (with the given plan) and of the
 // dense matrix-core step (1-bit, 2-bit or int8 couplings).
 double csr_step_seconds(const DevGraph &g, const DevRun &run, const AnnealPlan &plan);
-double dense_step_seconds(int32_t n, int32_t t4, bool two_bit, bool one_bit);
+// identity: no p-bit has a factor or a gate.
+double dense_step_seconds(int32_t n, const DevRun &run, bool two_bit, bool one_bit, bool identity);
 // True when every stored coupling has one magnitude (the 2-bit encoding).
 bool dense_two_bit(const psa_graph *g);
 // Every stored coupling the same nonzero value (the 1-bit dense encoding).
@@ -593,7 +594,7 @@ bool dense_one_bit(const psa_graph *g);
 // Cost model of the automatic path choice: dense when the rows are long
 // enough that the matrix-core product beats the CSR walk, and the couplings
 // have a dense encoding.
-bool prefer_dense(const psa_graph *g, const DevRun &run, const AnnealPlan &plan);
+bool prefer_dense(const psa_graph *g, const DevRun &run, const AnnealPlan &plan, bool identity);
 // Build and upload the dense int8 coupling matrix of g (once); EUNSUPPORTED
 // if a coupling does not fit int8.
 psa_status ensure_dense_matrix(psa_graph *g);

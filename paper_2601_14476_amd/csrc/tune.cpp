@@ -172,6 +172,8 @@ psa_status psa_autotune(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *de
         psa::DevRun mrun;
         mrun.trials = base.trials;
         mrun.t4 = (base.trials + 3) / 4 * 4;
+        mrun.steps = base.steps;
+        mrun.t_res = base.t_res;
         psa::AnnealPlan mplan;
         std::string why;
         const double model_csr =
@@ -179,7 +181,7 @@ psa_status psa_autotune(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *de
                 ? 1e6 * psa::csr_step_seconds(g->dev, mrun, mplan)
                 : -1.0;
         const double model_dense =
-            dense_ok ? 1e6 * psa::dense_step_seconds(g->info.n, mrun.t4, psa::dense_two_bit(g), psa::dense_one_bit(g))
+            dense_ok ? 1e6 * psa::dense_step_seconds(g->info.n, mrun, psa::dense_two_bit(g), psa::dense_one_bit(g), false)
                      : -1.0;
         const bool prune_dense = g->info.n > 4096 && model_csr > 0.0 && model_dense > 2.0 * model_csr;
         if (dense_ok && !prune_dense) cands.push_back({PSA_PATH_DENSE, 0, 0});
