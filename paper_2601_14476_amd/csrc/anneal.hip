@@ -15,15 +15,18 @@ namespace {
 // with a few more, a compute unit holds three workgroups of 256 or one of 512
 // fewer, and runs of more trials than units take another round (289 p-bits of
 // degree 27, 837 trials 4.1 us per step with 131 registers).
-template <int TPW, int LPT, int CSR, bool CSR_LDS, int BLOCK>
+template <int TPW, int LPT, int CSR, bool CSR_LDS, int BLOCK, bool ALONE>
 __global__ __launch_bounds__(BLOCK, 4) void anneal_kernel(AnnealArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    anneal_body<TPW, LPT, CSR, CSR_LDS, BLOCK>(a, static_cast<int32_t>(blockIdx.x), smem);
+    anneal_body<TPW, LPT, CSR, CSR_LDS, BLOCK, ALONE>(a, static_cast<int32_t>(blockIdx.x), smem);
 }
 
 template <int TPW, int LPT, int CSR, bool LDS, int BLOCK>
 hipError_t launch_variant(hipStream_t stream, const AnnealArgs &args, const AnnealPlan &plan) {
-    auto kern = anneal_kernel<TPW, LPT, CSR, LDS, BLOCK>;
+    auto kern = anneal_kernel<TPW, LPT, CSR, LDS, BLOCK, false>;
+    if constexpr (LPT == 4) {
+        if (plan.alone) kern = anneal_kernel<TPW, LPT, CSR, LDS, BLOCK, true>;
+    }
     hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                          hipFuncAttributeMaxDynamicSharedMemorySize,
                                          static_cast<int>(plan.lds_bytes));
@@ -121,6 +124,7 @@ bool plan_anneal(const DevGraph &g, const DevRun &run, int32_t tpw_req, int32_t 
         }
     }
     p.grid = p.tpw == 4 ? run.t4 / 4 : run.trials;
+    p.alone = p.grid <= num_cu ? 1 : 0;
     if (p.tpw == 4) {
         p.csr = g.pk32 ? kCsrPack32 : kCsrPair;
         p.lpt = 1;

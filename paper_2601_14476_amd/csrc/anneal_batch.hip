@@ -23,16 +23,16 @@ __global__ __launch_bounds__(BLOCK, 4) void anneal_batch_kernel(const BatchJob *
     const BatchJob &job = jobs[w.x];
     const AnnealArgs a = job.a;
     switch (job.variant) {
-        case kBatchUnitLds2: anneal_body<1, 2, kCsrUnit, true, BLOCK>(a, w.y, smem); break;
-        case kBatchUnitGlb2: anneal_body<1, 2, kCsrUnit, false, BLOCK>(a, w.y, smem); break;
-        case kBatchUnitLds4: anneal_body<1, 4, kCsrUnit, true, BLOCK>(a, w.y, smem); break;
-        case kBatchUnitGlb4: anneal_body<1, 4, kCsrUnit, false, BLOCK>(a, w.y, smem); break;
-        case kBatchP32Lds2: anneal_body<1, 2, kCsrPack32, true, BLOCK>(a, w.y, smem); break;
-        case kBatchP32Glb2: anneal_body<1, 2, kCsrPack32, false, BLOCK>(a, w.y, smem); break;
-        case kBatchPairGlb2: anneal_body<1, 2, kCsrPair, false, BLOCK>(a, w.y, smem); break;
-        case kBatchP32Lds4T: anneal_body<4, 1, kCsrPack32, true, BLOCK>(a, w.y, smem); break;
-        case kBatchP32Glb4T: anneal_body<4, 1, kCsrPack32, false, BLOCK>(a, w.y, smem); break;
-        case kBatchPairGlb4T: anneal_body<4, 1, kCsrPair, false, BLOCK>(a, w.y, smem); break;
+        case kBatchUnitLds2: anneal_body<1, 2, kCsrUnit, true, BLOCK, false>(a, w.y, smem); break;
+        case kBatchUnitGlb2: anneal_body<1, 2, kCsrUnit, false, BLOCK, false>(a, w.y, smem); break;
+        case kBatchUnitLds4: anneal_body<1, 4, kCsrUnit, true, BLOCK, false>(a, w.y, smem); break;
+        case kBatchUnitGlb4: anneal_body<1, 4, kCsrUnit, false, BLOCK, false>(a, w.y, smem); break;
+        case kBatchP32Lds2: anneal_body<1, 2, kCsrPack32, true, BLOCK, false>(a, w.y, smem); break;
+        case kBatchP32Glb2: anneal_body<1, 2, kCsrPack32, false, BLOCK, false>(a, w.y, smem); break;
+        case kBatchPairGlb2: anneal_body<1, 2, kCsrPair, false, BLOCK, false>(a, w.y, smem); break;
+        case kBatchP32Lds4T: anneal_body<4, 1, kCsrPack32, true, BLOCK, false>(a, w.y, smem); break;
+        case kBatchP32Glb4T: anneal_body<4, 1, kCsrPack32, false, BLOCK, false>(a, w.y, smem); break;
+        case kBatchPairGlb4T: anneal_body<4, 1, kCsrPair, false, BLOCK, false>(a, w.y, smem); break;
         case kBatchEll1Unit: ell1_body<false>(a, w.y, smem); break;
         case kBatchEll1: ell1_body<true>(a, w.y, smem); break;
         case kBatchEll4 + kEllUnit: ell4_body<kEllUnit>(a, w.y, smem); break;

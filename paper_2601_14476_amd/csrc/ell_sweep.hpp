@@ -49,12 +49,17 @@ __device__ __forceinline__ uint32_t in_vgpr(uint32_t x) {
 struct RoundKeys {
     uint32_t k0[7], k1[7];
 };
+template <bool VGPR = true>
 __device__ __forceinline__ RoundKeys round_keys(uint32_t k0, uint32_t k1) {
     RoundKeys K;
 #pragma unroll
     for (int i = 0; i < 7; ++i) {
-        K.k0[i] = in_vgpr(k0 + static_cast<uint32_t>(i + 3) * 0x9E3779B9u);
-        K.k1[i] = in_vgpr(k1 + static_cast<uint32_t>(i + 3) * 0xBB67AE85u);
+        K.k0[i] = k0 + static_cast<uint32_t>(i + 3) * 0x9E3779B9u;
+        K.k1[i] = k1 + static_cast<uint32_t>(i + 3) * 0xBB67AE85u;
+        if constexpr (VGPR) {
+            K.k0[i] = in_vgpr(K.k0[i]);
+            K.k1[i] = in_vgpr(K.k1[i]);
+        }
     }
     return K;
 }

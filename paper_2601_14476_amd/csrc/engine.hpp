@@ -164,6 +164,7 @@ struct AnnealPlan {
     int32_t csr = kCsrPair;   // edge encoding read by the kernel
     int32_t csr_lds = 0;      // 1: CSR, biases and per-p-bit factors staged in LDS
     int32_t ell = 0;          // 1: streaming sweep over the graph's ELL rows
+    int32_t alone = 0;        // 1: at most one workgroup per compute unit
     int32_t ahead = 0;        // 1: a job stepped alone draws its thresholds ahead (ahead.hip)
     int32_t block = 256;      // threads per workgroup
     int32_t grid = 0;         // workgroups

@@ -250,36 +250,37 @@ __device__ __forceinline__ FastCache<P> load_fast_cache(const Views &v, const in
     return c;
 }
 
-// The first fast_early<P>() cached slots' bytes of the buffer at LDS offset
+// The first E = fast_early<P, ALG>() cached slots' bytes of the buffer at LDS offset
 // OFF, issued before the step's random rounds, which need nothing from LDS: all
 // wavefronts leave the barrier together, so loads behind the rounds leave the
 // LDS idle first and the vector units afterwards.  One-row lanes (800 p-bits of
 // degree 48: 1.88 -> 1.79 us per step); two-row lanes, of few slots, are
-// slower that way (2,000 of degree 6: 1.22 -> 1.25 us).
-template <int P>
-constexpr int fast_early() { return P == 1 ? 8 : 0; }
-template <int P>
+// slower that way (2,000 of degree 6: 1.22 -> 1.25 us), and SpSA and TApSA, whose
+// state leaves no registers for the bytes (SpSA, 800 of degree 12, 100 trials: 1.69
+// -> 1.59).
+template <int P, int ALG>
+constexpr int fast_early() { return P == 1 && (ALG == kAlgPsa || ALG == kAlgPeriod) ? 8 : 0; }
+template <int E>
 struct EarlyBytes {
-    uint32_t x[fast_early<P>() > 0 ? fast_early<P>() : 1];
+    uint32_t x[E > 0 ? E : 1];
 };
-template <int P, uint32_t OFF>
-__device__ __forceinline__ EarlyBytes<P> load_early(const FastCache<P> &c) {
-    EarlyBytes<P> e{};
+template <int P, int E, uint32_t OFF>
+__device__ __forceinline__ EarlyBytes<E> load_early(const FastCache<P> &c) {
+    EarlyBytes<E> e{};
 #pragma unroll
-    for (int j = 0; j < fast_early<P>(); ++j) e.x[j] = lds_byte<OFF>(c.a[j]);
+    for (int j = 0; j < E; ++j) e.x[j] = lds_byte<OFF>(c.a[j]);
     return e;
 }
 
 // Fields of the lane's P rows from the buffer at LDS offset OFF (cur points
 // there): the cached slots in one sum, then the edges past them.
-template <int P, uint32_t OFF, bool BLK>
+template <int P, int E, uint32_t OFF, bool BLK>
 __device__ __forceinline__ void field_fast(const Views &v, const int32_t *rp, const int32_t *h,
-                                           const FastCache<P> &c, const EarlyBytes<P> &early,
+                                           const FastCache<P> &c, const EarlyBytes<E> &early,
                                            const uint8_t *cur, int32_t L[P]) {
     uint32_t acc = 0u;
     constexpr int K = fast_slots<P>();
     constexpr int C = fast_chunk<P>();
-    constexpr int E = fast_early<P>();
     static_assert(E % C == 0, "early slots are whole chunks");
 #pragma unroll
     for (int j = 0; j < E; ++j) acc += early.x[j];
@@ -357,20 +358,28 @@ __device__ __forceinline__ uint32_t lane_sub() {
 // a wavefront and step and saves a lane's one block 6 vector ones less 3
 // selects, and the scalar unit is shared by all wavefronts of a compute unit (us
 // per step, drawn whole and under prefixes: 250 p-bits of degree 27, 700 trials
-// 1.22 and 1.33, 500 of degree 6, 360 trials 1.07 and 1.17; one workgroup per
-// compute unit, 500 of degree 6, 130 trials 0.80 and 0.78).
+// 1.22 and 1.33, 500 of degree 6, 360 trials 1.07 and 1.17).  Only four lanes per
+// task in a workgroup that has its compute unit to itself (ALONE) take the
+// prefix: the shorter chain of the step then counts (1,000 of degree 4, 200 trials
+// 1.17 and 1.06; two lanes 1 % either way).
 // ---------------------------------------------------------------------------
 struct StepBlocks {
-    BlockPrefix r, gate;      // LPT 1
-    uint32_t t, k, tag, k0, k1;  // LPT >= 2: the lane's block
+    BlockPrefix r, gate;         // LPT 1; r: the lane's own with LPT 4, ALONE
+    uint32_t t, k, tag, k0, k1;  // else: the lane's block
 };
-template <int LPT>
+template <int LPT, bool ALONE>
 __device__ __forceinline__ StepBlocks step_blocks(uint32_t t, uint32_t k, uint32_t sub, bool gated, uint32_t k0,
                                                   uint32_t k1) {
     StepBlocks B{};
-    if constexpr (LPT == 1) {
+    if constexpr (LPT == 1 || ALONE) {
         B.r = block_prefix(t, k, kTagR, k0, k1);
         B.gate = gated ? block_prefix(t, k, kTagGate, k0, k1) : B.r;
+        if constexpr (LPT > 1) {
+            const bool odd = gated && (sub & 1u) != 0u;
+            B.r.b = odd ? B.gate.b : B.r.b;
+            B.r.c = odd ? B.gate.c : B.r.c;
+            B.r.e = odd ? B.gate.e : B.r.e;
+        }
     } else {
         B.t = t;
         B.k = k;
@@ -380,10 +389,10 @@ __device__ __forceinline__ StepBlocks step_blocks(uint32_t t, uint32_t k, uint32
     }
     return B;
 }
-template <int LPT>
+template <int LPT, bool ALONE>
 __device__ __forceinline__ void task_words(uint32_t m, uint32_t sub, bool gated, const StepBlocks &B,
                                            const RoundKeys &keys, uint32_t rw[4 / LPT], uint32_t gw[4 / LPT]) {
-    const Words4 b = LPT == 1 ? block_of_task(m, B.r, keys) : philox4x32_10(B.t, m, B.k, B.tag, B.k0, B.k1);
+    const Words4 b = LPT == 1 || ALONE ? block_of_task(m, B.r, keys) : philox4x32_10(B.t, m, B.k, B.tag, B.k0, B.k1);
     if constexpr (LPT == 1) {
         rw[0] = b.x;
         rw[1] = b.y;
@@ -485,7 +494,7 @@ struct LaneInput {
 // Field sources of the one-trial update.
 enum : int { kFieldPlain = 0, kFieldEdgeCache = 1, kFieldFast0 = 2, kFieldFast1 = 3 };
 
-template <int CSR, int LPT, int ALG, bool BLK, int FIELD, bool LRING = false>
+template <int CSR, int LPT, int ALG, bool BLK, int FIELD, bool ALONE, bool LRING = false>
 __device__ __forceinline__ uint32_t task_one_trial(const Views &v, const TaskConst<4 / LPT> &c,
                                                    const EdgeCache *ec, const FastCache<4 / LPT> *fc,
                                                    LaneInput<4 / LPT> *li, int32_t *lring, uint32_t sub, uint32_t k,
@@ -528,15 +537,16 @@ __device__ __forceinline__ uint32_t task_one_trial(const Views &v, const TaskCon
     } else {
         (void)lring;
     }
-    EarlyBytes<P> early{};
+    constexpr int E = fast_early<P, ALG>();
+    EarlyBytes<E> early{};
     constexpr bool FAST = CSR == kCsrUnit && (FIELD == kFieldFast0 || FIELD == kFieldFast1) && P <= 2;
     constexpr uint32_t FAST_OFF = FIELD == kFieldFast1 ? static_cast<uint32_t>(kFastStride) : 0u;
     if constexpr (FAST) {
-        early = load_early<P, FAST_OFF>(*fc);
-        if constexpr (fast_early<P>() > 0) __builtin_amdgcn_sched_barrier(0);
+        early = load_early<P, E, FAST_OFF>(*fc);
+        if constexpr (E > 0) __builtin_amdgcn_sched_barrier(0);
     }
     uint32_t rw[P], gw[P], sw[P];
-    task_words<LPT>(static_cast<uint32_t>(c.m), sub, gated, B, keys, rw, gw);
+    task_words<LPT, ALONE>(static_cast<uint32_t>(c.m), sub, gated, B, keys, rw, gw);
 #pragma unroll
     for (int j = 0; j < P; ++j) sw[j] = 0u;
     if (ALG == kAlgSpsa && t > 0) {
@@ -547,7 +557,7 @@ __device__ __forceinline__ uint32_t task_one_trial(const Views &v, const TaskCon
     int32_t L[P];
     if constexpr (FAST) {
         (void)ec;
-        field_fast<P, FAST_OFF, BLK>(v, c.rp, c.h, *fc, early, cur, L);
+        field_fast<P, E, FAST_OFF, BLK>(v, c.rp, c.h, *fc, early, cur, L);
     } else if constexpr (CSR == kCsrUnit && FIELD == kFieldEdgeCache) {
         (void)fc;
         if constexpr (P == 4) {
@@ -768,7 +778,7 @@ __host__ __device__ constexpr size_t edge_bytes(int32_t csr) {
 
 // Whole run of one workgroup: trial group q of the run described by `a`,
 // steps a.t_begin .. a.t_end-1.  `smem` is the dynamic LDS of the launch.
-template <int TPW, int LPT, int CSR, bool CSR_LDS, int BLOCK>
+template <int TPW, int LPT, int CSR, bool CSR_LDS, int BLOCK, bool ALONE>
 __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsigned char *smem) {
     using E = Enc<TPW, CSR>;
     const int32_t n = a.n, n4 = a.n4, tasks = a.tasks;
@@ -873,14 +883,15 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
     constexpr int P = 4 / LPT;
     const uint32_t sub = lane_sub<LPT>();
     const bool gated = a.gated != 0;
-    const RoundKeys keys = round_keys(a.k0, a.k1);  // LPT 1
+    // (one-row lanes have no vector registers left for the keys)
+    const RoundKeys keys = round_keys<(P > 1)>(a.k0, a.k1);
     auto one_trial_step = [&](auto alg_tag, auto cached_tag, const TaskConst<P> &c,
                               const EdgeCache *ec, LaneInput<P> *li, uint32_t tau, float i0t, float close_d,
                               uint32_t k0, uint32_t k1, const StepBlocks &B, const unsigned char *from,
                               unsigned char *to) __attribute__((always_inline)) {
         constexpr int ALG = decltype(alg_tag)::value;
         constexpr bool CACHED = decltype(cached_tag)::value;
-        const uint32_t b = task_one_trial<CSR, LPT, ALG, !CSR_LDS, CACHED ? kFieldEdgeCache : kFieldPlain>(
+        const uint32_t b = task_one_trial<CSR, LPT, ALG, !CSR_LDS, CACHED ? kFieldEdgeCache : kFieldPlain, ALONE>(
             v, c, ec, nullptr, li, nullptr, sub, static_cast<uint32_t>(q), tau, i0t, close_d, from, k0, k1,
             ALG != kAlgPeriod && gated, B, keys, st);
         const int32_t at = c.base;
@@ -966,7 +977,7 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
         constexpr bool LR = decltype(lring_tag)::value;
         constexpr uint32_t RO = PAR ? static_cast<uint32_t>(kFastStride) : 0u;
         constexpr uint32_t WO = PAR ? 0u : static_cast<uint32_t>(kFastStride);
-        const uint32_t b = task_one_trial<CSR, LPT, ALG, !CSR_LDS, PAR ? kFieldFast1 : kFieldFast0, LR>(
+        const uint32_t b = task_one_trial<CSR, LPT, ALG, !CSR_LDS, PAR ? kFieldFast1 : kFieldFast0, ALONE, LR>(
             v, own, nullptr, &own_fast, &own_in, lring, sub, static_cast<uint32_t>(q), tau, i0t, close_d, smem + RO,
             k0, k1, ALG != kAlgPeriod && gated, B, keys, st);
         unsigned char *to = smem + WO + own.base;
@@ -1003,7 +1014,7 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
                     asm volatile("" : "+s"(k0), "+s"(k1));
                     const uint32_t tau = static_cast<uint32_t>(t) * static_cast<uint32_t>(nsub) +
                                          static_cast<uint32_t>(s);
-                    const StepBlocks B = step_blocks<LPT>(tau, static_cast<uint32_t>(q), sub, ALG != kAlgPeriod && gated, k0, k1);
+                    const StepBlocks B = step_blocks<LPT, ALONE>(tau, static_cast<uint32_t>(q), sub, ALG != kAlgPeriod && gated, k0, k1);
                     if (owns) fast_step(alg_tag, par_tag, lring_tag, tau, i0t, close_d, k0, k1, B);
                     __syncthreads();
                     if (++s == nsub) {
@@ -1042,7 +1053,7 @@ __device__ __forceinline__ void anneal_body(const AnnealArgs &a, int32_t q, unsi
         for (int32_t s = 0; s < nsub; ++s) {
         const uint32_t tau = static_cast<uint32_t>(t) * static_cast<uint32_t>(nsub) + static_cast<uint32_t>(s);
         if constexpr (TPW == 1) {
-            const StepBlocks B = step_blocks<LPT>(tau, static_cast<uint32_t>(q), sub, ALG != kAlgPeriod && gated, k0, k1);
+            const StepBlocks B = step_blocks<LPT, ALONE>(tau, static_cast<uint32_t>(q), sub, ALG != kAlgPeriod && gated, k0, k1);
             if (resident) {
                 if (owns)
                     one_trial_step(alg_tag, std::true_type{}, own, own_edges, &own_in, tau, i0t, close_d, k0, k1, B, cur, nxt);
