@@ -86,12 +86,13 @@ hipError_t launch_four_trials(hipStream_t stream, const AnnealArgs &args, const 
 //     trials 5.6 and 8.1; 600 of degree 6, 1,000 4.7 and 6.0);
 //   period classes, which visit only the p-bits that fire: 4 with one row per
 //     lane (800 of degree 12, sub-steps of 10, 760 trials 15.7 and 21.3, 1,000 20.6 and
-//     21.3), 3 up to mean degree 32, and with two short rows (2,000 of degree 6, 760
-//     trials 18.7 and 20.9), else 2 (2,000 of degree 24, 500 trials 37 and 36).
+//     21.3), 3 from 10,000 to 20,000 entries (300 of degree 60, 700 trials 42 and 47) and
+//     with two short rows (2,000 of degree 6, 760 trials 18.7 and 20.9), else 2 (2,000
+//     of degree 24, 500 trials 37 and 36).
 static int64_t one_trial_rounds(const DevGraph &g, const DevRun &run, const AnnealPlan &one) {
     const int64_t n = g.n;
     if (run.t_res > 0) {
-        if (one.lpt == 4) return g.nnz <= 16 * n ? 4 : (g.nnz <= 32 * n ? 3 : 2);
+        if (one.lpt == 4) return g.nnz <= 10000 ? 4 : (g.nnz <= 20000 ? 3 : 2);
         return one.lpt == 2 && g.nnz <= 8 * n ? 3 : 2;
     }
     if (one.ell || one.csr != kCsrUnit || !one.csr_lds || one.lpt == 1) return 2;

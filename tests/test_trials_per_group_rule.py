@@ -15,7 +15,8 @@ CASES = [
     # period classes
     (600, 6, 1, "period", 1000, 1), (800, 12, 1, "period", 760, 1), (1000, 6, 0, "period", 760, 1), (1500, 6, 1, "period", 760, 1),
     (2000, 6, 1, "period", 760, 1), (2000, 6, 1, "period", 780, 4), (2000, 24, 1, "period", 520, 4), (800, 24, 1, "period", 700, 1),
-    (4000, 6, 1, "period", 500, 1), (4000, 6, 1, "period", 1000, 4), (250, 6, 1, "period", 1030, 4), (300, 6, 1, "period", 1000, 1)]
+    (4000, 6, 1, "period", 500, 1), (4000, 6, 1, "period", 1000, 4), (250, 6, 1, "period", 1030, 4), (300, 6, 1, "period", 1000, 1),
+    (300, 60, 1, "period", 700, 1), (800, 60, 1, "period", 700, 4)]
 
 
 def test_measured_runs(tmp_path):
