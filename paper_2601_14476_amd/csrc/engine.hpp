@@ -439,6 +439,7 @@ struct EnergyJob {
     int32_t wg0 = 0, q0 = 0, cpl = 1, lpr = 1;
     int32_t quads = 4;           // trial groups per lane of the partial pass: 4 or 1
     int32_t narrow = 0;          // sums over 256 rows fit int32
+    int32_t long_rows = 0;       // mean degree 12 or more: 1, 48 or more: 2
     int64_t w2 = 0;
     const int32_t *row_ptr = nullptr, *col = nullptr, *val = nullptr, *h = nullptr;  // h: null when all 0
     const int8_t *spins = nullptr;
@@ -481,24 +482,41 @@ inline int64_t energy_waves(const EnergyJob &e) {
 }
 // Split of a partial pass whose read-out (all its runs at their widest chunks)
 // has `waves` wavefronts in `wgs` workgroups.  Below kEnergyWaves the chip is
-// short of loads in flight: four trials per lane instead of sixteen (2,000
-// p-bits of degree 6, 100 trials: 8.2 against 15.8 us; 20,000 of degree 4, 100
-// trials: 14.2 against 30.6).  Above, a read-out of fewer workgroups than
-// compute units takes narrower groups of chunks (20,000 p-bits of degree 20,
-// 256 trials: 316 workgroups of 64-byte gathers instead of 79 of 256-byte ones,
-// 48 against 243 us).
-constexpr int64_t kEnergyWaves = 4096, kEnergyWgs = 256;
+// short of loads in flight: four trials per lane instead of sixteen, and the lanes
+// that this frees on a row's edges; from kEnergyWide spins on, four lanes side by
+// side on 16 trials and fewer on the edges, since 4-byte gathers then take longer
+// than the rows (us, energy and cut, a lane per row / as chosen: 800 p-bits of degree
+// 48, 256 trials 35.0 / 15.6; 5,000 of degree 40, 256 trials 152 / 30.5; 2,000 of degree
+// 6, 100 trials 9.1 / 7.8; 4,000 of degree 6, 1,000 trials 46.9 / 22.6).  Above, a
+// read-out of fewer workgroups than compute units takes narrower groups of chunks
+// (20,000 p-bits of degree 20, 256 trials: 316 workgroups of 64-byte gathers instead
+// of 79 of 256-byte ones, 48 against 243 us).
+constexpr int64_t kEnergyWaves = 4096, kEnergyWgs = 256, kEnergyWide = 350000;
 inline void energy_split(EnergyJob *e, int64_t waves, int64_t wgs) {
     if (waves < kEnergyWaves) {
+        const int64_t spins = static_cast<int64_t>(e->n) * e->t4;
+        const bool wide = spins >= kEnergyWide;
+        // (rows of 12 to 47 entries: 4 lanes to 150,000 spins, 1,000 p-bits of
+        // degree 20, 4 trials 7.6 against 8.4 with 16, 2,000 of 24, 100 trials 12.5 and 11.8)
         e->quads = 1;
-        e->lpr = e->lpr == 1 ? 1 : (e->lpr * e->cpl >= 16 ? 16 : 4);
-        e->cpl = 1;
+        e->cpl = wide ? 4 : 1;
+        e->lpr = wide ? (e->long_rows ? 4 : 1) : (e->long_rows == 2 || (e->long_rows == 1 && spins >= 150000) ? 16 : 4);
     } else if (wgs < kEnergyWgs) {
         while (e->cpl > 1 && energy_batch_wgs(*e) < kEnergyWgs) {
             e->cpl /= 2;
             if (e->lpr > 1) e->lpr *= 2;
         }
     }
+}
+// Split of the local fields: below kFieldWide spins four trials per lane, four
+// lanes side by side and four on a row's edges (us: 60 p-bits of degree 4, 100
+// trials 6.4 -> 4.0, 800 of degree 48, 256 trials 24.9 -> 8.2, 4,000 of degree 6, 256
+// trials 9.5 -> 8.9; past it 4,000 of degree 6, 1,000 trials 17.7 -> 31.7).
+constexpr int64_t kFieldWide = 1200000;
+inline void field_split(EnergyJob *e) {
+    if (static_cast<int64_t>(e->n) * e->t4 >= kFieldWide) return;
+    e->quads = 1;
+    e->cpl = e->lpr = 4;
 }
 // Grid of at least `count` workgroups of at most 1,024 threads, its number b =
 // y * gridDim.x + x.  A launch holds fewer than 2^32 threads along x and at most

@@ -271,8 +271,8 @@ __global__ __launch_bounds__(64) void energy_finish_batch_kernel(const EnergyJob
 // gathers from L2 (20,000 p-bits of degree 20, 256 trials: 103 MB): 35 us,
 // against 375 us with a thread per p-bit and four trials (4-byte gathers) and
 // 60 us with a chunk's rows on neighbouring lanes (16-byte gathers).
+template <int Q>
 __global__ __launch_bounds__(kFieldBlock) void local_field_kernel(EnergyJob e, int32_t *__restrict__ out) {
-    constexpr int Q = 4;
     const ReadLane l = read_lane<Q>(e, static_cast<int32_t>(blockIdx.z * gridDim.y + blockIdx.y));
     const int32_t i = static_cast<int32_t>(blockIdx.x) * l.rows + l.row;
     int32_t L[Q][4] = {};
@@ -392,16 +392,18 @@ EnergyJob energy_job(const DevGraph &g, const DevRun &run) {
     e.val = g.val;
     e.h = g.any_h ? g.h : nullptr;
     e.narrow = g.max_field < (1 << 23) ? 1 : 0;
+    e.long_rows = g.nnz >= 48 * static_cast<int64_t>(g.n) ? 2 : (g.nnz >= 12 * static_cast<int64_t>(g.n) ? 1 : 0);
     e.spins = run.spins;
     return e;
 }
 
 hipError_t launch_local_field(hipStream_t stream, const DevGraph &g, const DevRun &run,
                               int32_t *out_tn) {
-    const EnergyJob e = energy_job(g, run);
-    const int32_t chunks = (run.t4 + 15) / 16, ys = (chunks + e.cpl - 1) / e.cpl;
+    EnergyJob e = energy_job(g, run);
+    field_split(&e);
+    const int32_t chunks = (run.t4 + 4 * e.quads - 1) / (4 * e.quads), ys = (chunks + e.cpl - 1) / e.cpl;
     const int32_t y = std::min(ys, kMostGridY);
-    hipLaunchKernelGGL(local_field_kernel,
+    hipLaunchKernelGGL(e.quads == 1 ? local_field_kernel<1> : local_field_kernel<4>,
                        dim3(grid_for(static_cast<int64_t>(g.n) * e.cpl * e.lpr, kFieldBlock), y, (ys + y - 1) / y),
                        dim3(kFieldBlock), 0, stream, e, out_tn);
     return hipGetLastError();
