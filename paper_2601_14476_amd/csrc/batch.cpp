@@ -506,75 +506,133 @@ psa_status dense_step_jobs(psa_ctx *ctx, psa_job *const *jobs, int32_t count, in
 
 }  // namespace psa
 
-namespace {
+namespace psa {
 
-// Time of one workgroup's step, in lane-operations at a compute unit's rate,
-// fitted to runs of degree 4 to 50 on the streaming sweeps.
-double item_ops(const psa_job *job, int32_t tpw) {
-    const psa::DevGraph &g = job->g->dev;
-    const double d = g.nnz / static_cast<double>(std::max(g.n, 1));
-    return g.n * (tpw == 4 ? 4.0 * (25.0 + 2.6 * d) : 50.0 + 7.0 * d) * std::max(job->run.t_res, 1);
+// Modelled step (all its sub-steps) of one workgroup of a batch, fitted to runs
+// alone: its time with the compute unit to itself (a chain of latencies for small
+// runs), and the compute unit's time it takes in issue and in about 4 TB/s of
+// TApSA windows and SpSA inputs.  us, modelled and measured alone: 2,000 p-bits of
+// degree 6, four trials 4.1 and 4.2, of 60 11.8 and 11.7; 4,500 of 6, one trial 3.9
+// and 4.0; TApSA 800 of 24, four trials 8.8 and 8.8.
+BatchItemTime batch_item_time(const DevGraph &g, const DevRun &run, const AnnealPlan &plan) {
+    const double n = g.n, nnz = static_cast<double>(g.nnz), deg = nnz / std::max(n, 1.0);
+    constexpr double kUnitOps = kValuOpsPerSecond / 256.0, kUnitBytes = 4.0e12 / 256.0;
+    const double words = run.ring ? run.alpha : (run.xs ? (plan.tpw == 4 ? 0.5 : 1.3) : 0.0);
+    double alone, unit;
+    if (plan.tpw == 4) {
+        unit = 3.6 * n * (38.0 + 3.2 * deg) / kUnitOps;
+        alone = std::max(2.4e-6 + 0.1e-6 * deg + n * (0.4e-9 + 0.022e-9 * deg), unit) + (run.xs ? 1.2e-6 : 0.0);
+    } else if (plan.ell) {
+        unit = n * (50.0 + 7.0 * deg) / kUnitOps;
+        alone = 1.2e-6 + unit;
+    } else {
+        unit = n * (130.0 + 5.0 * deg) / kUnitOps;
+        alone = (plan.csr_lds ? 1.0e-6 + nnz * 0.08e-9 : nnz / 1024.0 * (plan.csr == kCsrUnit ? 0.8e-6 : 0.46e-6)) *
+                (run.ring ? 1.15 : (run.xs ? 1.1 : 1.0));
+    }
+    if (plan.tpw == 4 || plan.ell) {  // (resident lanes keep their state)
+        unit += 16.0 * words * n / kUnitBytes;
+        alone += 16.0 * words * n / kUnitBytes;
+    }
+    // wavefronts none of whose p-bits fire pass a sub-step by
+    const double subs = run.t_res > 0 ? run.t_res * (plan.tpw == 4 ? 0.5 : 0.65) : 1.0;
+    return BatchItemTime{alone * subs, unit * subs};
 }
 
 // Which runs of a batch take four trials per workgroup (those whose trials per
 // workgroup are the library's choice and whose rows the four-trial streaming
 // sweep reads).  A four-trial workgroup walks its rows once for the four and
-// issues 1.6 to 2.5 times fewer instructions per update, but takes about twice
-// as long per step.  The batch ends with its longest workgroup or with the
-// work spread over the compute units, whichever is later: every run starts
-// with four, and the run with the longest workgroup goes back to one as long as
-// that end comes earlier.  Measured (12 graphs of degree 4-8 and 2,069 to 4,044 p-bits,
-// 500 steps, one and four trials): 64 trials 4.55 and 3.17 ms, 32 3.15 and
-// 3.14, 16 1.73 and 3.15; 16 requests of 4,951 to 19,606 p-bits, degree 4 to 50,
-// 250 steps, 32.7 and 18.7 ms.
+// issues fewer instructions per update, but takes two to five times as long per
+// step.  The batch ends with its longest workgroup, its workgroups' times over
+// the slots they have, or the compute units' time over the units, whichever is
+// latest (where workgroups share a unit, plus the longest one's, which may meet
+// another); a slot is a launch's share of a unit, by the largest workgroup and LDS
+// of all its runs, so a single one-trial run of wide lanes may halve the slots of
+// every other.  Starting with four for every run, the run with the longest
+// workgroup goes back to one again and again; the earliest end of these, and of one
+// for every run, wins.
+// Measured, all one and all four, us per step: 12 graphs of degree 4-8 and 2,069 to
+// 4,044 p-bits, 64 trials 9.1 and 6.3, 32 6.3 and 6.3, 16 3.5 and 6.3; 16 requests
+// of 4,951 to 19,606 p-bits, degree 4 to 50, 131 and 75; 20 graphs of 60 to 500 p-bits,
+// degree 4-8, 100 to 500 trials 15.1 and 8.7 (19 of them four: 13.0); 40 such, TApSA, 8
+// to 64 trials 4.5 and 8.8; six of 3,000 of degree 6, 8 trials 3.0 and 5.6.
 std::vector<char> choose_four_trials(const psa_ctx *ctx, psa_job *const *jobs, const std::vector<int32_t> &idx,
                                      const std::vector<int32_t> &t_end) {
+    struct Form {
+        BatchItemTime t{0.0, 0.0};
+        int64_t items = 0;
+        int32_t lanes = 0;
+        size_t lds = 0;
+    };
     const size_t count = idx.size();
     std::vector<char> four(count, 0), fixed(count, 1);
-    std::vector<double> one_t(count, 0.0), four_t(count, 0.0);
-    double load = 0.0;  // of the chosen forms, over the compute units
+    std::vector<std::array<Form, 2>> forms(count);  // one and four trials
     for (size_t x = 0; x < count; ++x) {
         const psa_job *job = jobs[idx[x]];
-        const psa::DevGraph &g = job->g->dev;
+        const DevGraph &g = job->g->dev;
         const double steps = t_end[static_cast<size_t>(idx[x])] - job->t;
-        one_t[x] = steps * item_ops(job, 1);
-        four_t[x] = steps * item_ops(job, 4);
-        psa::AnnealPlan plan;
-        int32_t variant = 0;
-        fixed[x] = !(job->auto_tpw && job->plan.tpw == 1 && job->run.pps &&
-                     psa::plan_batch_item(g, job->run, 4, 0, ctx->max_lds, &plan, &variant, nullptr) && plan.ell);
+        bool have[2], ell4 = false;
+        for (int f = 0; f < 2; ++f) {
+            AnnealPlan p;
+            int32_t variant = 0;
+            have[f] = plan_batch_item(g, job->run, f ? 4 : 1, !f && job->plan.tpw == 1 ? job->plan.lpt : 0, ctx->max_lds, &p, &variant, nullptr);
+            if (!have[f]) continue;
+            const BatchItemTime t = batch_item_time(g, job->run, p);
+            forms[x][f] = Form{{t.alone * steps, t.unit * steps}, f ? job->run.t4 / 4 : job->run.trials, g.n4 / 4 * p.lpt, p.lds_bytes};
+            if (f) ell4 = p.ell != 0;
+        }
+        fixed[x] = !(job->auto_tpw && job->plan.tpw == 1 && job->run.pps && have[0] && have[1] && ell4);
         four[x] = fixed[x] ? job->plan.tpw == 4 : 1;
-        load += (four[x] ? four_t[x] * (job->run.t4 / 4) : one_t[x] * job->run.trials) / ctx->num_cu;
     }
-    auto longest = [&](size_t *at) {
-        double most = 0.0;
+    // modelled end, and the run with the longest workgroup
+    auto end_of = [&](const std::vector<char> &form, size_t *at) {
+        size_t lds = 1;
+        double longest = 0.0, shortest = 1e30, alone = 0.0, unit = 0.0, most_unit = 0.0;
+        int64_t items = 0;
+        int32_t lanes = 0;
+        *at = count;
         for (size_t x = 0; x < count; ++x) {
-            const double t = four[x] ? four_t[x] : one_t[x];
-            if (t > most) {
-                most = t;
+            const Form &f = forms[x][form[x] ? 1 : 0];
+            if (f.t.alone > longest) {
+                longest = f.t.alone;
                 *at = x;
             }
+            shortest = std::min(shortest, f.t.alone);
+            most_unit = std::max(most_unit, f.t.unit);
+            alone += f.t.alone * f.items;
+            unit += f.t.unit * f.items;
+            items += f.items;
+            lanes = std::max(lanes, f.lanes);
+            lds = std::max(lds, f.lds);
         }
-        return most;
+        const int64_t per_unit = std::min<int64_t>(1024 / batch_block(lanes), std::max<int64_t>(1, ctx->max_lds / lds));
+        const double slots = static_cast<double>(ctx->num_cu * per_unit);
+        return std::max({longest, alone / slots, unit / ctx->num_cu}) + (items > slots ? 0.5 * shortest : 0.0) +
+               (per_unit > 1 && items > ctx->num_cu ? most_unit : 0.0);
     };
-    for (;;) {
-        size_t x = count;
-        const double end = std::max(longest(&x), load);
-        if (x == count || !four[x] || fixed[x]) break;
-        const psa_job *job = jobs[idx[x]];
-        const double change = (one_t[x] * job->run.trials - four_t[x] * (job->run.t4 / 4)) / ctx->num_cu;
-        four[x] = 0;
-        size_t y = count;
-        if (std::max(longest(&y), load + change) >= end) {
-            four[x] = 1;
-            break;
-        }
-        load += change;
+    constexpr double kMixed = 1.15;  // a mixture has to be clearly earlier: its lanes and LDS are the larger of both forms'
+    size_t at = count;
+    std::vector<char> best = four, ones = four;
+    double best_end = end_of(four, &at);
+    for (size_t x = 0; x < count; ++x) ones[x] = fixed[x] ? four[x] : 0;
+    size_t unused = 0;
+    const double ones_end = end_of(ones, &unused);
+    if (ones_end < best_end) {
+        best = ones;
+        best_end = ones_end;
     }
-    return four;
+    while (at < count && four[at] && !fixed[at]) {
+        four[at] = 0;
+        const double end = kMixed * end_of(four, &at);
+        if (end < best_end) {
+            best = four;
+            best_end = end;
+        }
+    }
+    return best;
 }
 
-}  // namespace
+}  // namespace psa
 
 extern "C" {
 
@@ -618,7 +676,7 @@ psa_status psa_jobs_step_batch(psa_ctx *ctx, int32_t count, psa_job *const *jobs
             }
             sweep_jobs.push_back(j);
         }
-        std::vector<char> four = choose_four_trials(ctx, jobs, sweep_jobs, t_end);
+        std::vector<char> four = psa::choose_four_trials(ctx, jobs, sweep_jobs, t_end);
         for (size_t x = 0; x < sweep_jobs.size(); ++x) {
             const int32_t j = sweep_jobs[x];
             psa_job *job = jobs[j];
@@ -638,7 +696,7 @@ psa_status psa_jobs_step_batch(psa_ctx *ctx, int32_t count, psa_job *const *jobs
             bj.variant = variant;
             table.push_back(bj);
             trials.push_back(plan.tpw == 4 ? job->run.t4 / 4 : job->run.trials);  // work items
-            cost.push_back(item_ops(job, plan.tpw) * (te - job->t));
+            cost.push_back(psa::batch_item_time(job->g->dev, job->run, plan).alone * (te - job->t));
             lds = std::max(lds, plan.lds_bytes);
             max_lanes = std::max(max_lanes, job->g->dev.n4 / 4 * plan.lpt);
         }
@@ -660,10 +718,7 @@ psa_status psa_jobs_step_batch(psa_ctx *ctx, int32_t count, psa_job *const *jobs
                 PSA_HIP(hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0), "hipStreamWaitEvent");
             return PSA_OK;
         }
-        // a lane for every task of the longest run that keeps its tasks in lanes
-        // (2,000 p-bits of degree 6, 256 trials: 4.4 us per step with 512
-        // threads, 1.75 with 1,024)
-        const int32_t block = max_lanes > 512 ? 1024 : (max_lanes > 256 ? 512 : 256);
+        const int32_t block = psa::batch_block(max_lanes);
         std::vector<int2> work;
         psa::build_work_list(trials, cost, ctx->num_cu / kXcds * (1024 / block), &work);
         // the staging buffers are reused: the previous batched launch must be done

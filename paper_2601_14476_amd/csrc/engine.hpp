@@ -652,6 +652,19 @@ psa_status clone_job_for_timing(psa_job *src, psa_job **out);
 void ctx_retain(psa_ctx *ctx);
 void ctx_release(psa_ctx *ctx);
 
+// Threads of a batched launch: a lane for every task of the longest run that keeps
+// its tasks in lanes (2,000 p-bits of degree 6, 256 trials: 4.4 us per step with 512
+// threads, 1.75 with 1,024).
+constexpr int32_t batch_block(int32_t max_lanes) { return max_lanes > 512 ? 1024 : (max_lanes > 256 ? 512 : 256); }
+// Modelled time of one workgroup's step in a batch, and which of the runs jobs[idx]
+// take four trials per workgroup there (batch.cpp).
+struct BatchItemTime {
+    double alone, unit;  // seconds: with its compute unit to itself, of the unit's issue and bandwidth
+};
+BatchItemTime batch_item_time(const DevGraph &g, const DevRun &run, const AnnealPlan &plan);
+std::vector<char> choose_four_trials(const psa_ctx *ctx, psa_job *const *jobs, const std::vector<int32_t> &idx,
+                                     const std::vector<int32_t> &t_end);
+
 // XCD-aware work list of a batched launch (batch.cpp).
 void build_work_list(const std::vector<int32_t> &items, const std::vector<double> &cost, int32_t slots,
                      std::vector<int2> *work);
