@@ -344,6 +344,10 @@ void psa_run_desc_default(psa_run_desc *d);
  * device spin state (int8, [n][trials rounded up to 4], trials innermost)
  * and set the initial spins (m_i = +1 iff bit 31 of the Philox word of
  * counter (0, i/4, k, 0), word i mod 4).  The job is at step 0.
+ * With the first job whose steps may draw their random thresholds ahead (plain
+ * pSA of few trials on a graph of at most 4,032 p-bits) the context takes 64 MiB of
+ * device memory, shared by all its jobs and kept until it is released; without
+ * that memory such jobs run the other sweeps.  Stepping a job allocates nothing.
  * EUNSUPPORTED if the spin state of one workgroup's trials does not fit in
  * LDS (n above about 20,000 with 4 trials per workgroup, 80,000 with 1). */
 psa_status psa_job_create(psa_ctx *ctx, const psa_graph *g,

@@ -887,18 +887,26 @@ psa_status clone_job_for_timing(psa_job *src, psa_job **out) {
 
 // Whether these steps of a job stepped alone draw their thresholds ahead: not
 // for few steps, nor in a capture (a replay could meet another job's launches
-// on the context's buffer).
+// on the context's buffer), nor without the buffer.
 bool ahead_now(psa_job *job, int32_t steps) {
     psa_ctx *ctx = job->ctx;
-    if (!job->plan.ahead || steps < psa::kAheadMinSteps) return false;
+    if (!job->plan.ahead || !ctx->d_ahead || steps < psa::kAheadMinSteps) return false;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
-    if (!ctx->d_ahead && hipMalloc(reinterpret_cast<void **>(&ctx->d_ahead), psa::kAheadBytes) != hipSuccess) {
+    return hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+}
+
+// The context's buffer of thresholds, made with the first job that may be stepped
+// alone and planned `ahead` (without it, jobs take the other sweeps).
+static void reserve_ahead(psa_ctx *ctx) {
+    if (ctx->d_ahead) return;
+    if (hipMalloc(reinterpret_cast<void **>(&ctx->d_ahead), kAheadBytes) != hipSuccess) {
         (void)hipGetLastError();
         ctx->d_ahead = nullptr;
-        return false;
     }
-    return true;
+}
+
+psa_status create_batch_job(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *desc, psa_job **out) {
+    return guarded("psa_job_create", [&]() -> psa_status { return create_job("psa_job_create", ctx, g, desc, nullptr, out); });
 }
 
 }  // namespace psa
@@ -908,7 +916,9 @@ extern "C" {
 psa_status psa_job_create(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *desc,
                           psa_job **out) {
     return psa::guarded("psa_job_create", [&]() -> psa_status {
-        return create_job("psa_job_create", ctx, g, desc, nullptr, out);
+        const psa_status st = create_job("psa_job_create", ctx, g, desc, nullptr, out);
+        if (st == PSA_OK && (*out)->plan.ahead) psa::reserve_ahead(ctx);
+        return st;
     });
 }
 

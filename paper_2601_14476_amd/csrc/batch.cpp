@@ -780,7 +780,8 @@ psa_status psa_anneal_batch(psa_ctx *ctx, int32_t count, const psa_batch_item *i
                 }
             }
             psa_job *job = nullptr;
-            psa_status st = psa_job_create(ctx, items[j].graph, &d, &job);
+            psa_status st = (flags & PSA_BATCH_SEQUENTIAL) ? psa_job_create(ctx, items[j].graph, &d, &job)
+                                                           : psa::create_batch_job(ctx, items[j].graph, &d, &job);
             if (st != PSA_OK) {
                 set_error("psa_anneal_batch: item " + std::to_string(j) + ": " + psa_last_error());
                 return st;

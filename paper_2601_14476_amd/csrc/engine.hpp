@@ -633,6 +633,10 @@ psa_status tuned_desc(psa_ctx *ctx, const psa_graph *g, psa_run_desc *d, uint32_
 // Per-family timing (abi.cpp): begin/end a span on `stream` when the
 // context records timing (no-ops otherwise).
 enum : int { kTimeAnneal = 0, kTimeBatch = 1, kTimeDense = 2 };
+// psa_job_create for a job that is stepped in batches only: without the buffer that
+// stepping it alone may use.
+psa_status create_batch_job(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *desc, psa_job **out);
+
 psa_status time_begin(psa_ctx *ctx, hipStream_t stream, hipEvent_t *ev);
 psa_status time_end(psa_ctx *ctx, hipStream_t stream, int family, hipEvent_t begin,
                     int64_t launches);
@@ -690,8 +694,8 @@ struct psa_ctx {
     void *d_energy_table = nullptr;
     size_t energy_table_cap = 0;
     std::vector<psa::EnergyJob> h_energy_table;
-    // thresholds of the launches that draw them ahead, kAheadBytes, made at
-    // the first step that wants it (launches on `stream` only)
+    // thresholds of the launches that draw them ahead, kAheadBytes, made with the
+    // first job that wants it (launches on `stream` only)
     uint8_t *d_ahead = nullptr;
     // dense-path launches run on a second stream, joined with events
     hipStream_t stream2 = nullptr;

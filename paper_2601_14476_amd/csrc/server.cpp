@@ -209,7 +209,7 @@ psa_status admit_job(psa_server *s, ServerJob *j) {
         st = psa::tuned_desc(s->ctx, j->graph, &d, PSA_TUNE_BATCH);
         if (st != PSA_OK) return st;
     }
-    st = psa_job_create(s->ctx, j->graph, &d, &j->job);
+    st = psa::create_batch_job(s->ctx, j->graph, &d, &j->job);
     if (st != PSA_OK) return st;
     // the autotuner may have built the dense matrix for a run that reads the CSR
     psa_job_info ji{};
