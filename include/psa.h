@@ -100,7 +100,8 @@ typedef struct psa_timing {
     double anneal_ms;        /* CSR sweep launches (one job stepped alone) */
     double batch_ms;         /* CSR batch kernel launches                  */
     double dense_ms;         /* dense step sequences (launch gaps included) */
-    int64_t anneal_launches;
+    int64_t anneal_launches; /* one per psa_job_step, or one per chunk of 16 to
+                                256 steps where thresholds are drawn ahead */
     int64_t batch_launches;
     int64_t dense_launches;  /* per dense work list: one per step, or one
                                 for a persistent quantum                    */
@@ -361,7 +362,9 @@ psa_status psa_job_reset(psa_job *job);
  * context's stream; returns once they are queued. */
 psa_status psa_job_step(psa_job *job, int32_t k);
 
-/* How a job runs (chosen at creation). */
+/* How a job runs (chosen at creation).  Calls of 64 steps and more whose
+ * thresholds are drawn ahead run on launches of their own shape instead (one
+ * trial per workgroup, up to four p-bits per lane, up to 1,024 threads). */
 typedef struct psa_job_info {
     uint32_t path;             /* PSA_PATH_CSR or PSA_PATH_DENSE              */
     int32_t trials_per_group;  /* CSR: trials per workgroup (1 or 4)          */

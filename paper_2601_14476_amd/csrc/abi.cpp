@@ -955,6 +955,7 @@ psa_status psa_job_step(psa_job *job, int32_t k) {
             return st;
         }
         hipEvent_t ev = nullptr;
+        int64_t launches = 1;
         psa_status st = psa::time_begin(job->ctx, job->ctx->stream, &ev);
         if (st != PSA_OK) return st;
         if (job->pplan.nclass > 0)
@@ -963,13 +964,13 @@ psa_status psa_job_step(psa_job *job, int32_t k) {
                     "period sweep launch");
         else if (psa::ahead_now(job, t_end - job->t))
             PSA_HIP(psa::launch_ahead(job->ctx->stream, job->g->dev, job->run, job->ctx->d_ahead, psa::kAheadBytes,
-                                      job->ctx->num_cu, job->t, t_end),
+                                      job->ctx->num_cu, job->t, t_end, &launches),
                     "anneal launch");
         else
             PSA_HIP(psa::launch_anneal(job->ctx->stream, job->g->dev, job->run, job->plan, job->d_order,
                                        job->t, t_end),
                     "anneal launch");
-        if ((st = psa::time_end(job->ctx, job->ctx->stream, psa::kTimeAnneal, ev, 1)) != PSA_OK) return st;
+        if ((st = psa::time_end(job->ctx, job->ctx->stream, psa::kTimeAnneal, ev, launches)) != PSA_OK) return st;
         job->t = t_end;
         return PSA_OK;
     });

@@ -498,7 +498,8 @@ hipError_t launch_build_bit_rows(hipStream_t stream, int32_t n, int32_t bw, int3
 }
 
 hipError_t launch_ahead(hipStream_t stream, const DevGraph &g, const DevRun &run, uint8_t *buf, size_t buf_bytes,
-                        int32_t num_cu, int32_t t_begin, int32_t t_end) {
+                        int32_t num_cu, int32_t t_begin, int32_t t_end, int64_t *launches) {
+    *launches = 0;
     AheadArgs a{};
     a.n = g.n;
     a.n4 = g.n4;
@@ -563,6 +564,7 @@ hipError_t launch_ahead(hipStream_t stream, const DevGraph &g, const DevRun &run
         hipLaunchKernelGGL(kern, dim3(a.consumers + draw), dim3(block), lds, stream, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
+        ++*launches;
         a.c_begin = a.p_begin;
         a.c_end = a.p_end;
         next = a.p_end;

@@ -385,7 +385,7 @@ hipError_t launch_anneal(hipStream_t stream, const DevGraph &g, const DevRun &ru
 // Streaming sweep of one run (ell.hip): plan.ell set.
 hipError_t launch_ell(hipStream_t stream, const AnnealArgs &args, const AnnealPlan &plan, int32_t e4_mode);
 // Steps t_begin .. t_end-1 of a run planned `ahead`, its thresholds through
-// buf (two halves, a chunk of steps each).
+// buf (two halves, a chunk of steps each); *launches: how many it took.
 constexpr int32_t kAheadMaxN = 4032;      // p-bits: four per lane, rows of words in 16-bit addresses
 constexpr int32_t kAheadMaxRow = 126;     // sum_j |J_ij|: counts and thresholds in 7 bits
 constexpr int32_t kAheadChunk = 256;      // steps of a launch at most
@@ -400,7 +400,7 @@ __host__ __device__ constexpr int32_t bit_row_entry(int32_t b, int32_t len, int3
     return len > 0 ? b + (e < len ? e : len - 1) : 0;
 }
 hipError_t launch_ahead(hipStream_t stream, const DevGraph &g, const DevRun &run, uint8_t *buf, size_t buf_bytes,
-                        int32_t num_cu, int32_t t_begin, int32_t t_end);
+                        int32_t num_cu, int32_t t_begin, int32_t t_end, int64_t *launches);
 // Fill a graph's bit rows (be, and bm where not null) from its CSR; most: entries
 // of the longest wavefront, the first.
 hipError_t launch_build_bit_rows(hipStream_t stream, int32_t n, int32_t bw, int32_t most, const int32_t *row_ptr, const int32_t *col,
