@@ -72,7 +72,7 @@ inline psa_status hip_fail(hipError_t err, const char *what) {
     } while (0)
 
 // Shape class of a tuning problem (tune.cpp).
-using TuneKey = std::array<int64_t, 7>;
+using TuneKey = std::array<int64_t, 9>;
 
 // Device copy of a graph in CSR form.  Row i holds its neighbours j in
 // increasing order with their couplings J_ij.  Per-p-bit arrays are padded to

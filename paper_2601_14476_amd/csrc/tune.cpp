@@ -37,11 +37,13 @@ bool dense_encodable(const psa_graph *g) {
 }
 
 // Shape class of a tuning problem: mode, trials, n within 1/8 octave, mean
-// degree within 1/4 octave, dense encoding, rows short enough for 16-bit
-// packing, update rule.
-TuneKey tune_key(const psa_graph *g, int32_t trials, uint32_t mode, uint32_t algorithm) {
+// degree within 1/4 octave, dense encoding, the row layouts that the sweeps can
+// read (streaming rows, the four-trial sums' form, spin-bit rows), update rule,
+// window and timing mode.
+TuneKey tune_key(const psa_graph *g, const psa_run_desc &d, uint32_t mode) {
+    const int32_t trials = d.trials;
     const double n = std::max(g->info.n, 1);
-    const double d = static_cast<double>(g->info.nnz) / n;
+    const double deg = static_cast<double>(g->info.nnz) / n;
     const int64_t enc = dense_one_bit(g) ? 3 : (dense_two_bit(g) ? 2 : (dense_encodable(g) ? 1 : 0));
     // batched mode times copies of the run that fill the chip, so the trial
     // count matters by its magnitude: half-octave classes; alone, exactly
@@ -49,8 +51,9 @@ TuneKey tune_key(const psa_graph *g, int32_t trials, uint32_t mode, uint32_t alg
                              ? static_cast<int64_t>(std::ceil(std::log2(std::max(trials, 1)) * 2.0))
                              : trials;
     return TuneKey{static_cast<int64_t>(mode), tkey, static_cast<int64_t>(std::ceil(std::log2(n) * 8.0)),
-                   static_cast<int64_t>(std::floor(std::log2(1.0 + d) * 4.0)), enc,
-                   g->dev.max_degree <= 255 ? 1 : 0, static_cast<int64_t>(algorithm)};
+                   static_cast<int64_t>(std::floor(std::log2(1.0 + deg) * 4.0)), enc,
+                   (g->dev.e1 ? 1 : 0) + (g->dev.be ? 2 : 0) + 4 * (g->dev.e4_mode + 1), static_cast<int64_t>(d.algorithm),
+                   d.algorithm == PSA_ALG_TAPSA ? d.window : 0, d.t_res};
 }
 
 // Time one candidate: `copies` scratch runs of desc with the candidate's
@@ -213,7 +216,7 @@ psa_status psa_autotune(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *de
         r.model_dense_us = model_dense;
         {
             std::lock_guard<std::mutex> lock(ctx->tune_mu);
-            ctx->tune_cache[psa::tune_key(g, base.trials, mode, base.algorithm)] = r;
+            ctx->tune_cache[psa::tune_key(g, base, mode)] = r;
         }
         *out = r;
         return PSA_OK;
@@ -230,7 +233,7 @@ psa_status psa_tune_get(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *de
         }
         {
             std::lock_guard<std::mutex> lock(ctx->tune_mu);
-            auto it = ctx->tune_cache.find(psa::tune_key(g, desc->trials, mode, desc->algorithm));
+            auto it = ctx->tune_cache.find(psa::tune_key(g, *desc, mode));
             if (it != ctx->tune_cache.end()) {
                 *out = it->second;
                 return PSA_OK;
