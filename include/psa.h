@@ -518,13 +518,14 @@ typedef struct psa_tune_result {
     double model_dense_us;     /* (< 0: not applicable)                     */
 } psa_tune_result;
 
-/* Time every applicable configuration -- CSR with one trial per workgroup
- * at 1, 2 or 4 lanes per task (2 or 4 when batched), CSR with four trials
- * per workgroup, and the dense path when the couplings have a dense
- * encoding -- on
- * scratch runs of `desc` (same graph, trials, schedule and factors) over
- * `probe_steps` steps (>= 1, clipped to the schedule) after one warm-up
- * step, and return the fastest.  The result is also stored in the
+/* Time every applicable configuration -- CSR as an untuned run takes it, with
+ * one trial per workgroup at 1, 2 or 4 lanes per task (1 when batched only on the
+ * streaming sweep) and with four, and the dense path when the couplings have a
+ * dense encoding -- on scratch runs of `desc` (same graph, trials, schedule and
+ * factors) over `probe_steps` steps (>= 1, clipped to the schedule; 64 where an
+ * untuned run would draw its thresholds ahead) after one warm-up step, and
+ * return the fastest; of the CSR configurations the untuned one
+ * (trials_per_group = lanes_per_task = 0) if none is more than 5 % faster.  The result is also stored in the
  * context's tuning cache, keyed by mode, trials (in batched mode, trials
  * within a half octave), update rule and its window, timing mode (t_res) and the
  * graph's shape class (n and mean degree within about 9 % and 19 %, coupling

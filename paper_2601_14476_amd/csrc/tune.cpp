@@ -23,10 +23,15 @@
 namespace psa {
 namespace {
 
+// tpw and lpt 0 on the CSR path: left to the library, as in an untuned run.
 struct Candidate {
     uint32_t path;
     int32_t tpw, lpt;
+    bool automatic() const { return path == PSA_PATH_CSR && tpw == 0; }
 };
+// An automatic run is preferred to a fixed shape that times up to so much less: it
+// keeps the library free to draw thresholds ahead and to shape a real batch.
+constexpr double kPreferAutomatic = 0.05;
 
 using JobPtr = std::unique_ptr<psa_job, void (*)(psa_job *)>;
 
@@ -65,7 +70,8 @@ TuneKey tune_key(const psa_graph *g, const psa_run_desc &d, uint32_t mode) {
 // cost b decides: it is taken from calls of `probe` and 2 `probe` steps, b =
 // (T2 - T1) / probe, when the run has the steps for both (else T1 / probe).
 // Timing short calls alone put the dense path's per-run conversions into
-// every step (about 5x its per-step cost in a batch of 1,000 steps).
+// every step (about 5x its per-step cost in a batch of 1,000 steps).  A run that
+// draws its thresholds ahead does so only in calls of kAheadMinSteps and more.
 psa_status time_candidate(psa_ctx *ctx, const psa_graph *g, const psa_run_desc &base,
                           const Candidate &c, int32_t probe, uint32_t mode, double *us) {
     psa_run_desc d = base;
@@ -92,12 +98,14 @@ psa_status time_candidate(psa_ctx *ctx, const psa_graph *g, const psa_run_desc &
     // the stream before it is freed, and none is launched after that)
     for (int32_t i = 0; i < copies; ++i) {
         psa_job *job = nullptr;
-        const psa_status st = i == 0 ? psa_job_create(ctx, g, &d, &job)
-                                     : clone_job_for_timing(jobs[0], &job);
+        const psa_status st = i > 0 ? clone_job_for_timing(jobs[0], &job)
+                              : mode == PSA_TUNE_BATCH ? create_batch_job(ctx, g, &d, &job)
+                                                       : psa_job_create(ctx, g, &d, &job);
         if (st != PSA_OK) return st;
         owned.emplace_back(job, psa_job_destroy);
         jobs.push_back(job);
     }
+    if (mode == PSA_TUNE_ALONE && jobs[0]->plan.ahead) probe = std::max(probe, std::min(kAheadMinSteps, base.steps));
     const int32_t warm = base.steps > probe ? 1 : 0;
     auto advance = [&](int32_t k) -> psa_status {
         if (mode == PSA_TUNE_BATCH) return psa_jobs_step_batch(ctx, copies, jobs.data(), k);
@@ -162,10 +170,11 @@ psa_status psa_autotune(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *de
         base.flags = PSA_PATH_AUTO;
         const int32_t probe = std::min(probe_steps, base.steps);
         std::vector<psa::Candidate> cands;
+        cands.push_back({PSA_PATH_CSR, 0, 0});
         cands.push_back({PSA_PATH_CSR, 4, 0});
         for (int32_t lpt : {1, 2, 4}) {
-            // inside a batch a one-trial run uses 2 or 4 lanes per task
-            if (mode == PSA_TUNE_BATCH && lpt == 1) continue;
+            // inside a batch only the streaming sweep has one lane per task
+            if (mode == PSA_TUNE_BATCH && lpt == 1 && !g->dev.e1) continue;
             cands.push_back({PSA_PATH_CSR, 1, lpt});
         }
         const bool dense_ok = psa::dense_encodable(g) && g->info.n <= 32768;
@@ -177,6 +186,14 @@ psa_status psa_autotune(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *de
         mrun.t4 = (base.trials + 3) / 4 * 4;
         mrun.steps = base.steps;
         mrun.t_res = base.t_res;
+        // (the models look only whether there is input-stage state)
+        static float some_input;
+        static int32_t some_window;
+        if (base.algorithm == PSA_ALG_SPSA) mrun.xs = &some_input;
+        if (base.algorithm == PSA_ALG_TAPSA) {
+            mrun.ring = &some_window;
+            mrun.alpha = std::max(base.window, 1);
+        }
         psa::AnnealPlan mplan;
         std::string why;
         const double model_csr =
@@ -193,6 +210,7 @@ psa_status psa_autotune(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *de
         r.csr_us_per_step = -1.0;
         r.dense_us_per_step = -1.0;
         r.us_per_step = -1.0;
+        double automatic_us = -1.0;
         for (const psa::Candidate &c : cands) {
             double us = 0.0;
             const psa_status st = psa::time_candidate(ctx, g, base, c, probe, mode, &us);
@@ -201,6 +219,7 @@ psa_status psa_autotune(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *de
             ++r.candidates;
             double &best_of_path = c.path == PSA_PATH_DENSE ? r.dense_us_per_step : r.csr_us_per_step;
             if (best_of_path < 0.0 || us < best_of_path) best_of_path = us;
+            if (c.automatic()) automatic_us = us;
             if (r.us_per_step < 0.0 || us < r.us_per_step) {
                 r.us_per_step = us;
                 r.path = c.path;
@@ -208,6 +227,8 @@ psa_status psa_autotune(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *de
                 r.lanes_per_task = c.lpt;
             }
         }
+        if (r.path == PSA_PATH_CSR && automatic_us >= 0.0 && automatic_us <= (1.0 + psa::kPreferAutomatic) * r.us_per_step)
+            r.trials_per_group = r.lanes_per_task = 0;
         if (r.candidates == 0) {
             psa::set_error("psa_autotune: no configuration applies to this graph");
             return PSA_EUNSUPPORTED;
