@@ -19,10 +19,12 @@ Besides the contract fields the JSON line carries:
   roofline     -- the anneal kernel's algorithmic VALU lane-operations per
                   launch over its average duration (HIP events on the
                   library's stream) against the chip's VALU issue rate, with
-                  three operation counts side by side: the gfx950 lower bound
-                  (the headline fraction), the workload table's estimate, and
-                  the lane-instructions the kernel issued (rocprofv3 counters
-                  under profiles/, while the sources are unchanged);
+                  four operation counts side by side: the fewest that the
+                  method's arithmetic needs on gfx950 (the headline
+                  fraction), the count of its earlier form, the workload
+                  table's estimate, and the lane-instructions the kernel
+                  issued (rocprofv3 counters under profiles/, while the
+                  sources are unchanged);
   cpu_baseline -- the oracle timed on this host's cores on a bounded sample
                   of the same workload (trials spread over threads).
 """
@@ -41,15 +43,21 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# Algorithmic 32-bit lane-operations per p-bit update: the VALU instructions
-# the method's arithmetic takes on gfx950 with every random block drawn whole
-# on the vector unit and the decision in the tanh form.  The sweeps now issue
-# fewer (the blocks' uniform rounds on the scalar unit, 34 vector instructions
-# a block; a signed logistic decision of 6 operations instead of r map and
-# decision's 15), so the fraction may pass 1: it is a figure for comparing
-# runs, and the measured issue rate says how busy the chip is.  One Philox4x32-10 block = 10 rounds x (2 32x32->64
-# multiplies, one instruction each, + 2 three-input XOR) = 40, shared by the
-# 4 p-bits of a task; the timing gate needs a second block.
+# Algorithmic 32-bit lane-operations per p-bit update.  The headline count
+# (needed_ops_per_update) takes the fewest VALU instructions that any of the
+# sweeps' forms needs, so no kernel issues fewer.  A Philox4x32-10 block is 10
+# rounds x (2 32x32->64 multiplies, one instruction each, + 2 three-input
+# XOR), shared by the 4 p-bits of a task; the timing gate needs a second
+# block.  A block whose counter differs between lanes in one word only leaves
+# 34 of these 40 to the vector unit: the first three rounds' other parts are
+# uniform and run on the scalar one.  The decision is the sign of 1 / (2^v + 1)
+# + (f - 2): shift the r word into f, 2^v, + 1, reciprocal, - 2, add.
+#
+# The earlier form, kept beside it for comparison with older figures, drew
+# every block whole on the vector unit, mapped the r word to a float and took
+# tanh's estimate with its sign, distance, two compares and a select.
+PHILOX_UNIFORM_BLOCK_OPS = 34
+OPS_DECIDE_SIGNED = 6
 PHILOX_BLOCK_OPS = 40
 OPS_R_MAP = 4          # shift-or, subtract, convert, scale
 OPS_GATE_MAP = 2       # shift, compare
@@ -78,8 +86,8 @@ HBM_PEAK_GBS = 8000.0
 # Philox4x32-10 block, of which an update takes a quarter (r) or a half (r and
 # the timing gate), about 20 FP32 operations for the pre-activation and tanh,
 # and one add per neighbour.  gfx950 forms each 32x32->64 product in one
-# instruction and each three-way XOR in another, so a block takes 40, which is
-# why the lower bound above is the headline count.
+# instruction and each three-way XOR in another, so a block takes 40 or 34,
+# and the count above is the headline.
 PLAN_PHILOX_BLOCK_OPS = 100
 PLAN_FP32_OPS = 20
 
@@ -170,15 +178,29 @@ def host_cpu():
 
 
 def ops_per_update(field_ops: float, timing: bool, algorithm: str = "psa") -> float:
-    """Algorithmic 32-bit lane-operations of one p-bit update; field_ops is
-    the neighbour term (mean degree x the per-edge cost of the sweep).  SpSA
-    adds a quarter Philox block for the stall word and its compare and
-    select; TApSA the window-sum update and the mean (convert, divide)."""
+    """32-bit lane-operations of one p-bit update in the earlier form (whole
+    blocks, tanh estimate); field_ops is the neighbour term (mean degree x the
+    per-edge cost of the sweep).  SpSA adds a quarter Philox block for the
+    stall word and its compare and select; TApSA the window-sum update and the
+    mean (convert, divide)."""
     spsa = algorithm == "spsa"
     philox = PHILOX_BLOCK_OPS / 4 * ((2 if timing else 1) + (1 if spsa else 0))
     extra = OPS_STALL if spsa else (OPS_WINDOW + OPS_MEAN if algorithm == "tapsa" else 0)
     return (philox + OPS_R_MAP + (OPS_GATE_MAP if timing else 0) + field_ops
             + OPS_PREACT + OPS_DECIDE + extra)
+
+
+def needed_ops_per_update(field_ops: float, timing: bool, algorithm: str = "psa",
+                          whole_blocks: bool = False) -> float:
+    """Fewest 32-bit lane-operations of one p-bit update; arguments as in
+    ops_per_update.  whole_blocks: the words' counters differ between lanes in
+    more than the task, so no round is uniform."""
+    spsa = algorithm == "spsa"
+    block = PHILOX_BLOCK_OPS if whole_blocks else PHILOX_UNIFORM_BLOCK_OPS
+    philox = block / 4 * ((2 if timing else 1) + (1 if spsa else 0))
+    extra = OPS_STALL if spsa else (OPS_WINDOW + OPS_MEAN if algorithm == "tapsa" else 0)
+    return (philox + (OPS_GATE_MAP if timing else 0) + field_ops
+            + OPS_PREACT + OPS_DECIDE_SIGNED + extra)
 
 
 def edge_ops(job_info) -> float:
@@ -425,7 +447,7 @@ def main():
     timing = spec["sigma_nu"] > 0 or spec["p_mean"] < 1.0
     jinfo = job.info()
     field_ops = 0.0 if jinfo["path"] == psa.PSA_PATH_DENSE else info["nnz"] / n * edge_ops(jinfo)
-    opu = ops_per_update(field_ops, timing, args.algorithm)
+    opu = needed_ops_per_update(field_ops, timing, args.algorithm)
     if args.t_res > 0:
         # period mode: per cycle and p-bit, the expected number of firings
         # (t_res / period), each an ungated update that draws a whole Philox
@@ -434,7 +456,8 @@ def main():
         # periods per class, not per p-bit
         per = psa.periods_draw(n, spec["seed"], spec["sigma_nu"], args.t_res)
         fires = float(np.mean(args.t_res / per.astype(np.float64)))
-        opu = fires * (ops_per_update(field_ops, False) + PHILOX_BLOCK_OPS * 3 / 4)
+        opu = fires * (needed_ops_per_update(field_ops, False, whole_blocks=True)
+                       + PHILOX_BLOCK_OPS * 3 / 4)
         if jinfo["period_classes"] == 0:
             opu += args.t_res * OPS_PERIOD
     achieved = opu * updates / (kernel_ms * 1e-3) / 1e12
@@ -442,9 +465,10 @@ def main():
              "period_kernel" if args.t_res > 0 and jinfo["period_classes"] > 0 else "anneal_kernel")
     default_launch = (args.algorithm == "psa" and not args.t_res and args.path == "auto"
                       and not (args.block or args.tpw or args.lpt))
-    # the three operation counts side by side (plain pSA in probability mode)
+    # the operation counts side by side (plain pSA in probability mode)
     op_counts = {"gfx950_lower_bound": opu}
     if args.algorithm == "psa" and not args.t_res and not job.dense:
+        op_counts["earlier_form"] = ops_per_update(field_ops, timing)
         op_counts["workload_table_estimate"] = plan_ops_per_update(info["nnz"] / n, timing)
     issue = measured_issue(args.workload, kname) if default_launch else None
     if issue is not None:
@@ -547,7 +571,7 @@ def bench_batch(args):
         updates += upd
         if rb["path"] == psa.PSA_PATH_DENSE:
             dense_jobs += 1
-            dense_valu += ops_per_update(0.0, False) * upd
+            dense_valu += needed_ops_per_update(0.0, False) * upd
             enc = jobs[-1].info()["dense_encoding"]   # 1 int8, 2 two-bit, 3 one-bit
             fp4 = enc in (2, 3)
             # matrix work in int8-peak equivalents: 1- and 2-bit couplings run
@@ -560,7 +584,7 @@ def bench_batch(args):
             dense_bytes += (np_ * np_ * {1: 1.0, 2: 0.25, 3: 0.125}[enc] * tiles
                             + 2 * n * sp["trials"] * (0.5 if fp4 else 1.0)) * sp["steps"]
         else:
-            valu_ops += ops_per_update(info["nnz"] / n * edge_ops(jobs[-1].info()), False) * upd
+            valu_ops += needed_ops_per_update(info["nnz"] / n * edge_ops(jobs[-1].info()), False) * upd
     S = max(sp["steps"] for sp in specs)
 
     def batched(ev=None):
@@ -702,7 +726,7 @@ def bench_dense(args):
     one_bit = args.dense_weights == "one"
     mfma = (2 * n_arr ** 2 * 64).sum() / (per_us * 1e-6) / 1e12
     hbm = (npad ** 2 / (8 if one_bit else 4) + n_arr * 64).sum() / (per_us * 1e-6) / 1e9
-    valu = ops_per_update(0.0, False) * upd / (per_us * 1e-6) / 1e12
+    valu = needed_ops_per_update(0.0, False) * upd / (per_us * 1e-6) / 1e12
     fr = {"mfma": mfma / MFMA_F4_PEAK_TOPS, "alu": valu / VALU_PEAK_TOPS, "hbm": hbm / HBM_PEAK_GBS}
     bound = max(fr, key=fr.get)
     line = {

@@ -467,9 +467,11 @@ psa_status psa_anneal_noalloc(psa_ctx *ctx, const psa_graph *g, const psa_run_de
 
 /* Advance every job of `jobs` (all created on ctx, each listed once) by up
  * to k steps, clipped to each job's schedule, with one launch of the batch
- * kernel on the context's stream: one work item per (job, trial) -- or per
- * (job, group of four trials) for jobs created with trials_per_group 4 --
- * each workgroup dispatching to the kernel variant its job needs.  Jobs on
+ * kernel on the context's stream: one work item per (job, trial) or per
+ * (job, group of four trials), each workgroup dispatching to the kernel
+ * variant its job needs.  A job created with trials_per_group 1 or 4 keeps
+ * it; where it is left to the library (0), the choice is made per call, from
+ * the modelled end of the launch over all its jobs.  Jobs on
  * the dense path advance on a second stream (launched step by step, a second
  * coupling encoding's jobs on a third stream beside it), joined before
  * return.  The results are identical to stepping each job alone. */
