@@ -559,10 +559,7 @@ def bench_batch(args):
         rb = psa.tune_get(ctx, g, sp["steps"], sp["trials"], sp["seed"], batch=True)
         ra = psa.tune_get(ctx, g, sp["steps"], sp["trials"], sp["seed"], batch=False)
         t_tune += time.perf_counter() - t0
-        kb = psa.tune_kwargs(rb)
-        if kb["trials_per_group"] == 0:
-            kb["trials_per_group"] = 1
-        jobs.append(psa.Job(ctx, g, sp["steps"], sp["trials"], sp["seed"], **kb))
+        jobs.append(psa.Job(ctx, g, sp["steps"], sp["trials"], sp["seed"], **psa.tune_kwargs(rb)))
         alone.append(psa.Job(ctx, g, sp["steps"], sp["trials"], sp["seed"], **psa.tune_kwargs(ra)))
         graphs.append(g)
         outs.append((torch.empty(sp["trials"], dtype=torch.int64, device="cuda"),
