@@ -1156,7 +1156,7 @@ psa_status psa_jobs_energy_cut(psa_ctx *ctx, int32_t count, psa_job *const *jobs
             int64_t *tmp = static_cast<int64_t *>(job->d_scratch);
             psa::EnergyJob &e = table[static_cast<size_t>(j)];
             e = psa::energy_job(job->g->dev, job->run);
-            psa::energy_split(&e, all_waves, all_wgs);
+            psa::energy_split(&e, all_waves, all_wgs, false);
             e.wg0 = static_cast<int32_t>(wgs);
             e.q0 = static_cast<int32_t>(groups);
             e.part = tmp + 2 * job->run.trials;

@@ -439,7 +439,7 @@ struct EnergyJob {
     int32_t wg0 = 0, q0 = 0, cpl = 1, lpr = 1;
     int32_t quads = 4;           // trial groups per lane of the partial pass: 4 or 1
     int32_t narrow = 0;          // sums over 256 rows fit int32
-    int32_t long_rows = 0;       // mean degree 12 or more: 1, 48 or more: 2
+    int32_t degree = 0;          // mean degree of the rows
     int64_t w2 = 0;
     const int32_t *row_ptr = nullptr, *col = nullptr, *val = nullptr, *h = nullptr;  // h: null when all 0
     const int8_t *spins = nullptr;
@@ -491,16 +491,34 @@ inline int64_t energy_waves(const EnergyJob &e) {
 // read-out of fewer workgroups than compute units takes narrower groups of chunks
 // (20,000 p-bits of degree 20, 256 trials: 316 workgroups of 64-byte gathers instead
 // of 79 of 256-byte ones, 48 against 243 us).
+// Alone, rows of 48 entries and more keep sixteen trials per lane, and sixteen lanes
+// on a row, from 150,000 spins on, or once the gathers of four trials each outnumber
+// the loads in flight: 13 million spins times entries where a row's trials are one
+// load, 36 million otherwise (four / sixteen trials per lane: 3,000 p-bits of degree
+// 400, 16 trials 75 / 54, of 200, 16 trials 25 / 33, 64 trials 53 / 36; 4,800 of 400, 64
+// trials 209 / 103); past a million spins four lanes side by side and four on the
+// edges again, up to degree 150 (8,000 of 80, 256 trials 67 / 53; 4,800 of 200, 256
+// trials 119 / 137).  Rows of 350 entries and more of runs of over 16 trials stay with
+// four while their workgroups all run at once (3,000 of degree 400, 64 trials 91 / 98;
+// 1,500 of 400, 128 trials 88 / 101).  The runs of a batch share one kind of lane:
+// four trials.
 constexpr int64_t kEnergyWaves = 4096, kEnergyWgs = 256, kEnergyWide = 350000;
-inline void energy_split(EnergyJob *e, int64_t waves, int64_t wgs) {
+inline void energy_split(EnergyJob *e, int64_t waves, int64_t wgs, bool alone) {
     if (waves < kEnergyWaves) {
-        const int64_t spins = static_cast<int64_t>(e->n) * e->t4;
+        const int64_t spins = static_cast<int64_t>(e->n) * e->t4, gathered = spins * e->degree;
+        const bool at_once = e->degree >= 350 && e->t4 > 16 && static_cast<int64_t>(e->blocks) * (e->t4 / 4) <= kEnergyWgs;
+        if (alone && e->degree >= 48 && (spins >= 150000 ? !at_once : gathered >= (e->t4 <= 16 ? 13000000 : 36000000))) {
+            const bool wide = spins >= 1000000 && e->degree < 150;
+            e->cpl = wide ? 4 : 1;
+            e->lpr = wide ? 4 : 16;
+            return;
+        }
         const bool wide = spins >= kEnergyWide;
         // (rows of 12 to 47 entries: 4 lanes to 150,000 spins, 1,000 p-bits of
         // degree 20, 4 trials 7.6 against 8.4 with 16, 2,000 of 24, 100 trials 12.5 and 11.8)
         e->quads = 1;
         e->cpl = wide ? 4 : 1;
-        e->lpr = wide ? (e->long_rows ? 4 : 1) : (e->long_rows == 2 || (e->long_rows == 1 && spins >= 150000) ? 16 : 4);
+        e->lpr = wide ? (e->degree >= 12 ? 4 : 1) : (e->degree >= 48 || (e->degree >= 12 && spins >= 150000) ? 16 : 4);
     } else if (wgs < kEnergyWgs) {
         while (e->cpl > 1 && energy_batch_wgs(*e) < kEnergyWgs) {
             e->cpl /= 2;
@@ -508,15 +526,30 @@ inline void energy_split(EnergyJob *e, int64_t waves, int64_t wgs) {
         }
     }
 }
-// Split of the local fields: below kFieldWide spins four trials per lane, four
-// lanes side by side and four on a row's edges (us: 60 p-bits of degree 4, 100
-// trials 6.4 -> 4.0, 800 of degree 48, 256 trials 24.9 -> 8.2, 4,000 of degree 6, 256
-// trials 9.5 -> 8.9; past it 4,000 of degree 6, 1,000 trials 17.7 -> 31.7).
+// Split of the local fields below kFieldWide spins.  Up to 150,000 spins, and with
+// short rows or fewer than four chunks of trials also past them, the chip is short of
+// loads in flight: four trials per lane, up to four lanes side by side and four on a
+// row's edges, sixteen on long rows (us, a lane per row or a chunk per lane / as chosen:
+// 60 p-bits of degree 4, 100 trials 6.4 / 4.0; 800 of 48, 256 trials 24.9 / 8.2; 4,000 of
+// 6, 256 trials 9.5 / 8.9; with four and sixteen lanes on the edges 500 of 20, 64 trials
+// 5.3 / 5.2; 2,000 of 40, 16 trials 6.6 / 5.6; 3,000 of 400, 16 trials 26.5 / 11.2).
+// Past them the gathers bound it: sixteen trials per lane (64 trials, four and sixteen:
+// 3,000 of degree 120 14.2 / 11.7, of 400 44.8 / 19.0; 128 trials: 4,800 of 60 23.0 /
+// 13.7), sixteen lanes on the edges up to 400,000 spins or on rows of 300 entries.
+// Past kFieldWide the widest chunks (4,000 of degree 6, 1,000 trials 31.7 / 17.7).
 constexpr int64_t kFieldWide = 1200000;
 inline void field_split(EnergyJob *e) {
-    if (static_cast<int64_t>(e->n) * e->t4 >= kFieldWide) return;
-    e->quads = 1;
-    e->cpl = e->lpr = 4;
+    const int64_t spins = static_cast<int64_t>(e->n) * e->t4;
+    if (spins >= kFieldWide) return;
+    const int32_t groups = e->t4 / 4;
+    if (spins < 150000 || groups < 16 || e->degree < (spins < 400000 ? 90 : 12)) {
+        e->quads = 1;
+        e->cpl = groups >= 4 ? 4 : (groups >= 2 ? 2 : 1);
+        e->lpr = e->degree >= (spins < 150000 ? 32 : 90) ? 16 : 4;
+    } else {
+        e->cpl = 4;
+        e->lpr = spins < 400000 || e->degree >= 300 ? 16 : 4;
+    }
 }
 // Grid of at least `count` workgroups of at most 1,024 threads, its number b =
 // y * gridDim.x + x.  A launch holds fewer than 2^32 threads along x and at most

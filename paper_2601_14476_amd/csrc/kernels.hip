@@ -117,8 +117,9 @@ __device__ __forceinline__ int32_t energy_run_of(const EnergyJob *__restrict__ j
 // Read-out work split.  A lane holds sixteen trials (a chunk of Q = 4 trial
 // groups) of a row: the `cpl` lanes of consecutive chunks read a neighbour's
 // spins as one contiguous piece of up to 256 bytes, and `lpr` such groups share
-// a long row's edges; cpl lpr <= 16 lanes to a row.  Runs too small to fill
-// the chip that way take Q = 1, four trials to a lane (energy_split).
+// a long row's edges; at most 16 lanes to a row in the partial pass, at most a
+// wavefront for the local fields.  Runs too small to fill the chip that way
+// take Q = 1, four trials to a lane (energy_split, field_split).
 struct ReadLane {
     int32_t c, sub, row;      // chunk, share of the row, row of the block
     int32_t q0, nq;           // first trial group of the chunk, groups in it (none: <= 0)
@@ -385,14 +386,14 @@ EnergyJob energy_job(const DevGraph &g, const DevRun &run) {
     e.t4 = run.t4;
     e.trials = run.trials;
     e.blocks = (g.n + kEnergyRows - 1) / kEnergyRows;
-    read_out_split(run.t4, g.n > 0 ? g.nnz / g.n : 0, &e.cpl, &e.lpr);
+    e.degree = g.n > 0 ? static_cast<int32_t>(g.nnz / g.n) : 0;
+    read_out_split(run.t4, e.degree, &e.cpl, &e.lpr);
     e.w2 = g.w2;
     e.row_ptr = g.row_ptr;
     e.col = g.col;
     e.val = g.val;
     e.h = g.any_h ? g.h : nullptr;
     e.narrow = g.max_field < (1 << 23) ? 1 : 0;
-    e.long_rows = g.nnz >= 48 * static_cast<int64_t>(g.n) ? 2 : (g.nnz >= 12 * static_cast<int64_t>(g.n) ? 1 : 0);
     e.spins = run.spins;
     return e;
 }
@@ -422,7 +423,7 @@ static size_t energy_lds_bytes(const EnergyJob &e, int32_t block, bool narrow) {
 hipError_t launch_energy_cut(hipStream_t stream, const DevGraph &g, const DevRun &run,
                              int64_t *part, int64_t *energy, int64_t *cut) {
     EnergyJob e = energy_job(g, run);
-    energy_split(&e, energy_waves(e), energy_batch_wgs(e));
+    energy_split(&e, energy_waves(e), energy_batch_wgs(e), true);
     e.part = part;
     e.energy = energy;
     e.cut = cut;
