@@ -84,16 +84,20 @@ hipError_t launch_four_trials(hipStream_t stream, const AnnealArgs &args, const 
 //     1,200 of degree 6 3.3 and 3.5); TApSA 4, the
 //     window in LDS against 16 bytes per p-bit from memory (1,500 of degree 6, 1,000
 //     trials 5.6 and 8.1; 600 of degree 6, 1,000 4.7 and 6.0);
-//   period classes, which visit only the p-bits that fire: 4 with one row per
-//     lane (800 of degree 12, sub-steps of 10, 760 trials 15.7 and 21.3, 1,000 20.6 and
-//     21.3), 3 from 10,000 to 20,000 entries (300 of degree 60, 700 trials 42 and 47) and
-//     with two short rows (2,000 of degree 6, 760 trials 18.7 and 20.9), else 2 (2,000
-//     of degree 24, 500 trials 37 and 36).
+//   period classes, which visit only the p-bits that fire: by the entries, and longer
+//     with weights, whose four-trial sums take more instructions.  One row per lane: 4
+//     to 10,000 entries (800 of degree 12, sub-steps of 10, 760 trials 15.7 and 21.3,
+//     1,000 20.6 and 21.3), with weights to 30,000 (500 of degree 48, 1,000 trials 45
+//     and 52), 3 to 30,000 (300 of degree 72, 760 trials 39 and 43, 780 51 and 43), else
+//     2 (1,000 of degree 40, 520 trials 51 and 39).  Two rows: 3 to 25,000 (1,200 of
+//     degree 12, 760 trials 23.4 and 24.5; 1,100 of 24 32.3 and 30.4), with weights to
+//     40,000 (1,500 of 24, 760 trials 37.1 and 38.8), else 2.
 static int64_t one_trial_rounds(const DevGraph &g, const DevRun &run, const AnnealPlan &one) {
     const int64_t n = g.n;
     if (run.t_res > 0) {
-        if (one.lpt == 4) return g.nnz <= 10000 ? 4 : (g.nnz <= 20000 ? 3 : 2);
-        return one.lpt == 2 && g.nnz <= 8 * n ? 3 : 2;
+        const bool unit = one.csr == kCsrUnit;
+        if (one.lpt == 4) return g.nnz <= (unit ? 10000 : 30000) ? 4 : (g.nnz <= 30000 ? 3 : 2);
+        return one.lpt == 2 && g.nnz <= (unit ? 25000 : 40000) ? 3 : 2;
     }
     if (one.ell || one.csr != kCsrUnit || !one.csr_lds || one.lpt == 1) return 2;
     if (one.lpt == 4 ? g.max_degree > 64 : (g.nnz > 8 * n || g.max_degree > 32)) return 2;
