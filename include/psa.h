@@ -315,7 +315,9 @@ typedef struct psa_run_desc {
 #define PSA_ALG_TAPSA 2u
 
 /* Field-computation path of a run (psa_run_desc.flags).  AUTO picks by a
- * cost model (long rows -> dense); CSR walks the sparse rows from LDS /
+ * cost model (long rows -> dense; a run that is over after its schedule, as in
+ * psa_anneal, builds a graph's missing dense matrix only once such runs on the
+ * graph make up for it); CSR walks the sparse rows from LDS /
  * L2; DENSE multiplies the dense coupling matrix with the spins of all
  * trials on the int8 matrix cores.  The dense matrix is stored as 2-bit
  * fields times one scale when every stored coupling has the same magnitude

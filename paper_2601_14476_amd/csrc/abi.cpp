@@ -548,7 +548,7 @@ bool ahead_fits(const psa_ctx *ctx, const psa_graph *g, const psa_run_desc &d, c
 }
 
 psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
-                      const psa_run_desc *desc, Arena *arena, psa_job **out) {
+                      const psa_run_desc *desc, Arena *arena, psa_job **out, bool once = true) {
     if (!ctx || !g || !desc || !out) {
         set_error(std::string(who) + ": NULL argument");
         return PSA_EINVAL;
@@ -714,7 +714,7 @@ psa_status create_job(const char *who, psa_ctx *ctx, const psa_graph *g,
     j->identity_factors = desc->algorithm == PSA_ALG_PSA && desc->t_res == 0;
     for (int32_t i = 0; i < n && j->identity_factors; ++i)
         j->identity_factors = lam[i] == 1.0f && dlt[i] == 0.0f && thr[i] >= psa::kGateOneHost;
-    if (path == PSA_PATH_DENSE || (path == PSA_PATH_AUTO && psa::prefer_dense(g, j->run, j->plan, j->identity_factors)))
+    if (path == PSA_PATH_DENSE || (path == PSA_PATH_AUTO && psa::prefer_dense(const_cast<psa_graph *>(g), j->run, j->plan, j->identity_factors, once)))
         j->plan.dense = 1;
     if (j->plan.dense && arena) {
         set_error("the run needs the dense path, which the static scratch does not hold");
@@ -905,6 +905,13 @@ static void reserve_ahead(psa_ctx *ctx) {
     }
 }
 
+// A job stepped alone, with the buffer that its steps may draw thresholds into.
+static psa_status create_lone_job(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *desc, psa_job **out, bool once) {
+    const psa_status st = create_job("psa_job_create", ctx, g, desc, nullptr, out, once);
+    if (st == PSA_OK && (*out)->plan.ahead) reserve_ahead(ctx);
+    return st;
+}
+
 psa_status create_batch_job(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *desc, psa_job **out) {
     return guarded("psa_job_create", [&]() -> psa_status { return create_job("psa_job_create", ctx, g, desc, nullptr, out); });
 }
@@ -916,9 +923,7 @@ extern "C" {
 psa_status psa_job_create(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *desc,
                           psa_job **out) {
     return psa::guarded("psa_job_create", [&]() -> psa_status {
-        const psa_status st = create_job("psa_job_create", ctx, g, desc, nullptr, out);
-        if (st == PSA_OK && (*out)->plan.ahead) psa::reserve_ahead(ctx);
-        return st;
+        return psa::create_lone_job(ctx, g, desc, out, false);
     });
 }
 
@@ -1220,7 +1225,7 @@ psa_status psa_anneal(psa_ctx *ctx, const psa_graph *g, const psa_run_desc *desc
             return PSA_EINVAL;
         }
         psa_job *job = nullptr;
-        psa_status st = psa_job_create(ctx, g, desc, &job);
+        psa_status st = psa::create_lone_job(ctx, g, desc, &job, true);
         if (st != PSA_OK) return st;
         std::unique_ptr<psa_job, void (*)(psa_job *)> guard(job, job_free);
         if ((st = psa_job_step(job, desc->steps)) != PSA_OK) return st;

@@ -173,19 +173,26 @@ bool dense_one_bit(const psa_graph *g) {
 
 // A graph without its dense matrix pays for it at the first dense run: about 0.11
 // ns per entry of it, encoded and uploaded (5,000 p-bits 2.7 ms, where 10 steps of
-// 8 trials take 0.2 ms there and 0.7 on the rows).
+// 8 trials take 0.2 ms there and 0.7 on the rows).  A run that is over after its
+// schedule takes the rows until what such runs on the graph have forgone, each
+// its own modelled gain, comes to that cost; a job that its caller keeps may be reset
+// and stepped again and has the matrix at once (3 graphs of 800 to 5,000 p-bits, 27
+// trials, 53 steps a pass: 0.85 ms with it, 3.0 on the rows).
 constexpr double kDenseEncodeSecondsPerEntry = 0.11e-9;
 
-bool prefer_dense(const psa_graph *g, const DevRun &run, const AnnealPlan &plan, bool identity) {
+bool prefer_dense(psa_graph *g, const DevRun &run, const AnnealPlan &plan, bool identity, bool once) {
     if (g->info.n < 256) return false;
     const bool two_bit = dense_two_bit(g);
     if (!two_bit && std::any_of(g->val_host.begin(), g->val_host.end(),
                                 [](int32_t v) { return v < -127 || v > 127; }))
         return false;
     const double steps = static_cast<double>(run.steps) * std::max(run.t_res, 1);
-    const double encode = g->d_dense ? 0.0 : kDenseEncodeSecondsPerEntry * g->info.n * static_cast<double>(g->info.n);
-    return dense_step_seconds(g->info.n, run, two_bit, dense_one_bit(g), identity) + encode / steps <
-           0.7 * csr_step_seconds(g->dev, run, plan);
+    const double gain = 0.7 * csr_step_seconds(g->dev, run, plan) -
+                        dense_step_seconds(g->info.n, run, two_bit, dense_one_bit(g), identity);
+    if (gain <= 0.0) return false;
+    if (!once || g->d_dense) return true;
+    g->dense_gain += gain * steps;
+    return g->dense_gain > kDenseEncodeSecondsPerEntry * g->info.n * static_cast<double>(g->info.n);
 }
 
 // Work list of the dense runs `idx` of `table` (one encoding): items (job,

@@ -645,8 +645,9 @@ bool dense_two_bit(const psa_graph *g);
 bool dense_one_bit(const psa_graph *g);
 // Cost model of the automatic path choice: dense when the rows are long
 // enough that the matrix-core product beats the CSR walk, and the couplings
-// have a dense encoding.
-bool prefer_dense(const psa_graph *g, const DevRun &run, const AnnealPlan &plan, bool identity);
+// have a dense encoding.  once: the run is over after its schedule, so a matrix
+// still to be built has to pay for itself.
+bool prefer_dense(psa_graph *g, const DevRun &run, const AnnealPlan &plan, bool identity, bool once = true);
 // Build and upload the dense int8 coupling matrix of g (once); EUNSUPPORTED
 // if a coupling does not fit int8.
 psa_status ensure_dense_matrix(psa_graph *g);
@@ -794,6 +795,7 @@ struct psa_graph {
     int32_t dense_scale = 1;            // J = dense_scale * entry
     size_t dev_bytes = 0;               // device bytes of the CSR and its encodings
     size_t dense_bytes = 0;             // device bytes of d_dense
+    double dense_gain = 0.0;            // seconds that runs forwent without d_dense (prefer_dense)
 };
 
 struct psa_job {
