@@ -104,6 +104,22 @@ static int64_t one_trial_rounds(const DevGraph &g, const DevRun &run, const Anne
     return run.ring ? 4 : (run.xs || one.lpt == 4 || n <= 1600 ? 3 : 2);
 }
 
+// Lanes per task of a one-trial run that leaves them open: as many as the
+// workgroup has.  But two rows a lane of a weighted graph lie in LDS one behind the
+// other, and rows of one length put a wavefront's lanes on few banks (47 x 38
+// torus, weights, 140 trials: 2.5 us per step, streamed rows 1.4; random rows 2,000
+// of degree 6 2.4 and 1.9, SpSA 2.6 and 2.3, 1,100 of degree 6 2.0 and 1.9, SpSA 2.2
+// and 2.3, of 24 4.3 and 3.6; 1,500 of 60, past LDS, 30 and 6.0): these stream, pSA
+// always, SpSA but for few short rows of up to a trial per unit.  TApSA keeps its
+// sums in the lanes (1,100 of degree 6 2.2 and 3.2).
+static int32_t lanes_per_task(const DevGraph &g, const DevRun &run, size_t max_lds, int32_t num_cu) {
+    const int32_t tasks = g.n4 / 4;
+    const int32_t spread = tasks * 4 <= 1024 ? 4 : (tasks * 2 <= 1024 ? 2 : 1);
+    const bool streams = spread == 2 && !g.ux16 && g.e1 && !run.ring && run.t_res == 0 && 2 * ell1_stride(g.n4) <= max_lds &&
+                         (!run.xs || g.n >= 1300 || g.max_degree <= 8 || g.nnz >= 10 * static_cast<int64_t>(g.n) || run.trials > num_cu);
+    return streams ? 1 : spread;
+}
+
 bool plan_anneal(const DevGraph &g, const DevRun &run, int32_t tpw_req, int32_t lpt_req,
                  int32_t block_req, size_t max_lds, int32_t num_cu, AnnealPlan *plan,
                  std::string *why) {
@@ -120,9 +136,12 @@ bool plan_anneal(const DevGraph &g, const DevRun &run, int32_t tpw_req, int32_t 
         // units (one_trial_rounds; a unit runs 1,024 of their threads at once,
         // and one workgroup of the period-class sweep).
         AnnealPlan one;
-        const int32_t spread = tasks * 4 <= 1024 ? 4 : (tasks * 2 <= 1024 ? 2 : 1);
+        const int32_t spread = lanes_per_task(g, run, max_lds, num_cu);
         if (ell_ok && g.e4_mode >= 0 && plan_anneal(g, run, 1, lpt_req ? lpt_req : spread, block_req, max_lds, num_cu, &one, nullptr)) {
-            const int64_t threads = run.t_res > 0 ? 1024 : one.block;
+            // (streams of up to 2,048 p-bits: two workgroups of 512 threads on a unit
+            // get in each other's way: 2,000 of degree 6, 400 trials 3.0 and 4.0 us per
+            // step, 760 4.5 and 4.1)
+            const int64_t threads = run.t_res > 0 || (lpt_req == 0 && one.ell && g.n <= 2048) ? 1024 : one.block;
             p.tpw = run.trials * threads > one_trial_rounds(g, run, one) * static_cast<int64_t>(num_cu) * 1024 ? 4 : 1;
         } else {
             p.tpw = (run.t4 / 4 >= num_cu) ? 4 : 1;
@@ -138,8 +157,8 @@ bool plan_anneal(const DevGraph &g, const DevRun &run, int32_t tpw_req, int32_t 
         p.csr = g.ux16 ? kCsrUnit : (g.pk32 ? kCsrPack32 : kCsrPair);
         if (lpt_req == 1 || lpt_req == 2 || lpt_req == 4)
             p.lpt = lpt_req;
-        else  // spread tasks over more lanes while the workgroup has lanes to spare
-            p.lpt = tasks * 4 <= 1024 ? 4 : (tasks * 2 <= 1024 ? 2 : 1);
+        else
+            p.lpt = lanes_per_task(g, run, max_lds, num_cu);
         // but with workgroups to share the compute units, two lanes per task
         // issue less for short rows, whose random blocks outweigh their sums,
         // as long as two rows fit a lane's 32 cached slots (us per step with

@@ -10,7 +10,7 @@ CASES = [
     (800, 12, 1, "tapsa", 2048, 30, 1, 0), (2000, 12, 1, "tapsa", 1000, 30, 1, 0), (1500, 24, 1, "tapsa", 700, 30, 1, 0),
     (3000, 12, 1, "tapsa", 700, 30, 1, 0), (2000, 24, 1, "spsa", 2048, 30, 1, 0), (2000, 180, 0, "tapsa", 32, 30, 1, 1),
     (4500, 6, 1, "spsa", 256, 30, 1, 0),
-    (800, 180, 0, "psa", 64, 30, 1, 1), (2000, 180, 0, "psa0", 32, 30, 1, 1), (1500, 60, 0, "psa0", 128, 30, 1, 1),
+    (800, 180, 0, "psa", 64, 30, 1, 1), (2000, 180, 0, "psa0", 32, 30, 1, 1), (1500, 60, 0, "psa0", 128, 30, 1, 0),
     (3000, 180, 1, "psa", 128, 30, 1, 1), (3000, 24, 1, "psa", 128, 30, 1, 0), (4500, 6, 1, "psa", 1000, 30, 1, 0),
     (800, 24, 1, "psa", 500, 30, 1, 0), (300, 6, 1, "psa0", 64, 1000, 1, 0),
     # 2.7 ms of encoding against 10 or 2,000 steps
