@@ -51,7 +51,8 @@ namespace psa {
 // a job's items go whole to one XCD, costliest first, to the one that then ends
 // first: an XCD ends with its longest item as long as its items all run at
 // once, past that with its work spread over its slots, if that is later, and
-// one item more.  A list that fits the slots leaves no XCD more items than slots
+// one item more.  A list that fits the slots leaves no XCD more items than slots,
+// a chunk that no XCD can take whole going item by item where there is room
 // (12 graphs and a denser one, 256 items for 256 compute units: dealt by work
 // alone 5.9 ms, with the second rule alone 4.1, this way 3.4).
 void build_work_list(const std::vector<int32_t> &items, const std::vector<double> &cost, int32_t slots,
@@ -83,9 +84,15 @@ void build_work_list(const std::vector<int32_t> &items, const std::vector<double
                 best_end = end;
             }
         }
-        for (int32_t q = c.q0; q < c.q1; ++q) queue[best].push_back(make_int2(c.job, q));
-        sum[best] += n * each;
-        longest[best] = std::max(longest[best], each);
+        const bool split = all_run && static_cast<int64_t>(queue[best].size()) + n > slots;
+        for (int32_t q = c.q0; q < c.q1; ++q) {
+            if (split)
+                for (int x = 0; x < kXcds; ++x)
+                    if (queue[x].size() < queue[best].size()) best = x;
+            queue[best].push_back(make_int2(c.job, q));
+            sum[best] += each;
+            longest[best] = std::max(longest[best], each);
+        }
     }
     size_t len = 0;
     for (const auto &qu : queue) len = std::max(len, qu.size());
@@ -727,7 +734,7 @@ psa_status psa_jobs_step_batch(psa_ctx *ctx, int32_t count, psa_job *const *jobs
         }
         const int32_t block = psa::batch_block(max_lanes);
         std::vector<int2> work;
-        psa::build_work_list(trials, cost, ctx->num_cu / kXcds * (1024 / block), &work);
+        psa::build_work_list(trials, cost, psa::batch_slots(std::accumulate(trials.begin(), trials.end(), int64_t{0}), ctx->num_cu, block), &work);
         // the staging buffers are reused: the previous batched launch must be done
         PSA_HIP(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
         psa_status st;

@@ -694,6 +694,13 @@ void ctx_release(psa_ctx *ctx);
 // its tasks in lanes (2,000 p-bits of degree 6, 256 trials: 4.4 us per step with 512
 // threads, 1.75 with 1,024).
 constexpr int32_t batch_block(int32_t max_lanes) { return max_lanes > 512 ? 1024 : (max_lanes > 256 ? 512 : 256); }
+// Workgroups that the work list lets run at once on an XCD: one per compute unit
+// while they all have one, else as many as fit.  (12 graphs of 1,100 to 2,000 p-bits
+// of degree 6, weights, 10 trials: two workgroups to a unit on the XCD of the smallest
+// graphs 2.8 us per step, one 2.1.)
+constexpr int32_t batch_slots(int64_t items, int32_t num_cu, int32_t block) {
+    return num_cu / 8 * (items <= num_cu ? 1 : 1024 / block);
+}
 // Modelled time of one workgroup's step in a batch, and which of the runs jobs[idx]
 // take four trials per workgroup there (batch.cpp).
 struct BatchItemTime {
