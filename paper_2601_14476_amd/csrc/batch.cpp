@@ -531,7 +531,8 @@ namespace psa {
 BatchItemTime batch_item_time(const DevGraph &g, const DevRun &run, const AnnealPlan &plan) {
     const double n = g.n, nnz = static_cast<double>(g.nnz), deg = nnz / std::max(n, 1.0);
     constexpr double kUnitOps = kValuOpsPerSecond / 256.0, kUnitBytes = 4.0e12 / 256.0;
-    const double words = run.ring ? run.alpha : (run.xs ? (plan.tpw == 4 ? 0.5 : 1.3) : 0.0);
+    // (one trial's inputs of up to 2,048 p-bits stay in L2)
+    const double words = run.ring ? run.alpha : (run.xs ? (plan.tpw == 4 ? 0.5 : (n <= 2048.0 ? 0.25 : 1.3)) : 0.0);
     double alone, unit;
     if (plan.tpw == 4) {
         unit = 3.6 * n * (38.0 + 3.2 * deg) / kUnitOps;
