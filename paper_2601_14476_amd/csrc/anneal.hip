@@ -76,8 +76,9 @@ hipError_t launch_four_trials(hipStream_t stream, const AnnealArgs &args, const 
 // and four trials per workgroup).
 //   streaming sweep: 2 (4,000 p-bits of degree 6, 512 trials 5.8 and 6.0, 600 8.1
 //     and 5.9), and so resident lanes whose rows are weighted or outgrow their
-//     cached slots (64 for one row, 32 for two) (1,000 of degree 6, weights, 1,000 trials 5.9 and 3.7; 2,000 of
-//     24, 520 trials 14.3 and 6.3);
+//     cached slots (64 for one row, most of them; 32 for two) (1,000 of degree 6,
+//     weights, 1,000 trials 5.9 and 3.7; 2,000 of 24, 520 trials 14.3 and 6.3; 950 of 63,
+//     520 trials 9.6 and 8.2, but 800 of 47, up to 70, 5.9 and 7.0);
 //   resident lanes with cached rows: 3 (600 of degree 6, 760 trials 3.1 and 3.4,
 //     780 4.1 and 3.4; SpSA 1,500 of degree 6, 760 trials 4.1 and 4.7), but 2 where
 //     two rows fill more than 800 lanes (2,000 of degree 6, 760 trials 4.1 and 3.7;
@@ -100,7 +101,7 @@ static int64_t one_trial_rounds(const DevGraph &g, const DevRun &run, const Anne
         return one.lpt == 2 && g.nnz <= (unit ? 25000 : 40000) ? 3 : 2;
     }
     if (one.ell || one.csr != kCsrUnit || !one.csr_lds || one.lpt == 1) return 2;
-    if (one.lpt == 4 ? g.max_degree > 64 : (g.nnz > 8 * n || g.max_degree > 32)) return 2;
+    if (one.lpt == 4 ? g.nnz > 56 * n : (g.nnz > 8 * n || g.max_degree > 32)) return 2;
     return run.ring ? 4 : (run.xs || one.lpt == 4 || n <= 1600 ? 3 : 2);
 }
 

@@ -132,7 +132,10 @@ double csr_step_seconds(const DevGraph &g, const DevRun &run, const AnnealPlan &
         const double wait = run.ring && plan.tpw == 1 && g.n4 / 4 > 1024 ? 3.5e-6 * run.alpha * whole : 0.0;
         return std::max(kCsrStepFloorSeconds, n * run.trials * (ops / (kValuOpsPerSecond * share) + state)) + wait;
     }
-    if (plan.csr_lds) return std::max(kCsrStepFloorSeconds, whole * (1.0e-6 + nnz * 0.08e-9));
+    // (rows of unit weights: 950 p-bits of degree 45, 284 trials, two rounds 4.4 us, the
+    // dense step 5.3; 950 of 29, 520 trials, three rounds 5.0 and 6.8)
+    if (plan.csr_lds)
+        return std::max(kCsrStepFloorSeconds, whole * (1.0e-6 + nnz * (plan.csr == kCsrUnit ? 0.05e-9 : 0.08e-9)));
     // rows read from device memory by the few lanes of a workgroup: a latency
     // per 1,024 entries
     return whole * nnz / 1024.0 * (plan.csr == kCsrUnit ? 0.4e-6 : 0.23e-6) * (1.0 + std::min(run.trials, 256) / 200.0);
