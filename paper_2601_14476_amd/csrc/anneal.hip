@@ -166,9 +166,11 @@ bool plan_anneal(const DevGraph &g, const DevRun &run, int32_t tpw_req, int32_t 
         // four and two: 364 p-bits of degree 4, 843 trials, SpSA 2.93 and 1.39;
         // 1,000 of degree 6, 300 trials 2.17 and 1.37; 250 of degree 6, 300
         // trials 0.89 and 0.88; 404 of mean degree 11, 466 trials 1.14 and 1.50;
-        // 263 of 18, 438 trials 1.16 and 2.23)
+        // 263 of 18, 438 trials 1.16 and 2.23): from the first trial that has to share
+        // on where four lanes fill a unit (1,023 of degree 4, 284 trials 2.18 and 1.00),
+        // from a quarter more on below
         if (lpt_req == 0 && p.lpt == 4 && p.csr == kCsrUnit && g.nnz <= 8 * static_cast<int64_t>(g.n) && g.max_degree <= 16 &&
-            4 * static_cast<int64_t>(run.trials) > 5 * static_cast<int64_t>(num_cu))
+            (tasks * 4 > 512 ? 5 : 4) * static_cast<int64_t>(run.trials) > 5 * static_cast<int64_t>(num_cu))
             p.lpt = 2;
         // (a lane that keeps its task's input-stage state and edges in
         // registers steps SpSA and TApSA faster: 3,000 p-bits of degree 6, 30
